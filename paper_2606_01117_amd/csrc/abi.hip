@@ -98,15 +98,20 @@ hipError_t fwd_any(const haste::TailArgs &a, const void *X, const int32_t *idx, 
     return haste::fwd_valu(a, X, idx, W, bias, Y, s);
 }
 
-// the backward-weight kernel for a layer: small groups (G = 1, 2, 4, 8) and larger ones on the matrix
-// cores (both on the workspace's X^T copy), the rest on the vector ALUs
-// backward-feature: small-group kernel, else the general matrix-core kernel, else the VALU kernel
-size_t bwd_x_ws(const haste::TailArgs &a) {
+// backward-feature beside the any-group kernel: small-group kernels, else the general matrix-core
+// kernel, else the VALU kernel
+size_t bwd_x_other_ws(const haste::TailArgs &a) {
     if (haste::bwd_x_dn_supported(a)) return haste::bwd_x_dn_ws(a);
     if (haste::bwd_x_sg_supported(a)) return haste::bwd_x_sg_ws(a);
     return haste::bwd_x_mfma_supported(a) ? haste::bwd_x_mfma_ws(a) : haste::bwd_x_valu_ws(a);
 }
 
+size_t bwd_x_ws(const haste::TailArgs &a) {
+    return haste::bwd_x_any_preferred(a) ? haste::bwd_x_any_ws(a) : bwd_x_other_ws(a);
+}
+
+// the backward-weight kernel for a layer: small groups (G = 1, 2, 4, 8) and larger ones on the matrix
+// cores (both on the workspace's X^T copy), the rest on the vector ALUs
 bool bwd_w_uses_xt(const haste::TailArgs &a) {
     return haste::bwd_w_dn_supported(a) || haste::bwd_w_sg_supported(a) || haste::bwd_w_mfma_supported(a);
 }
@@ -249,10 +254,13 @@ int haste_bwd_x(const haste_desc_t *d, const int32_t *idx, const void *W, const 
     if (!haste::bwd_x_dn_supported(a) && !haste::bwd_x_sg_supported(a) && !haste::bwd_x_mfma_supported(a) &&
         !haste::valu_supported(a))
         return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
-    const size_t need = bwd_x_ws(a);
+    // a workspace of less than the queried size that another kernel can do with is still taken
+    const bool any = haste::bwd_x_any_preferred(a) && ws_bytes >= haste::bwd_x_any_ws(a);
+    const size_t need = any ? haste::bwd_x_any_ws(a) : bwd_x_other_ws(a);
     if (!ws || ws_bytes < need)
-        return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", need, ws ? ws_bytes : 0);
+        return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", bwd_x_ws(a), ws ? ws_bytes : 0);
     TRY(need_ptr(ws, "ws"));
+    if (any) return hip_status(haste::bwd_x_any(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_dn_supported(a)) return hip_status(haste::bwd_x_dn(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_sg_supported(a)) return hip_status(haste::bwd_x_sg(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_mfma_supported(a)) return hip_status(haste::bwd_x_mfma(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");

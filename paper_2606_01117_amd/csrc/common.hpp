@@ -93,6 +93,9 @@ struct Buf {
     __device__ __forceinline__ Buf(const void *base, uint32_t bytes)
         : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0,
                                               (int)(bytes < kOob ? bytes : kOob - 1), kRawBufferWord3)) {}
+    __device__ __forceinline__ uint16_t ld2(uint32_t off) const {
+        return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, 0);
+    }
     __device__ __forceinline__ uint32_t ld4(uint32_t off) const {
         return __builtin_bit_cast(uint32_t, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
     }
@@ -250,12 +253,19 @@ bool bwd_x_sg_supported(const TailArgs &a);
 size_t bwd_x_sg_ws(const TailArgs &a);
 hipError_t bwd_x_sg(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
                     hipStream_t s);
-// backward-feature for small groups (G = 1, 2, 4, 8, F_s <= 800) as a dense product over each
+// backward-feature for standard fixed fan-in (G = 1, F_s <= 768) as a dense product over each
 // 32-label step's weights scattered into an LDS tile
 bool bwd_x_dn_supported(const TailArgs &a);
 size_t bwd_x_dn_ws(const TailArgs &a);
 hipError_t bwd_x_dn(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
                     hipStream_t s);
+// the same product for groups of any size and supports of any width, the tiles written by producer
+// waves; preferred: where it is the faster kernel
+bool bwd_x_any_supported(const TailArgs &a);
+bool bwd_x_any_preferred(const TailArgs &a);
+size_t bwd_x_any_ws(const TailArgs &a);
+hipError_t bwd_x_any(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
+                     hipStream_t s);
 // forward for groups of 1 or 2 labels (F_s <= 768) as a dense product over each 32-label step's
 // weights scattered into an LDS tile
 bool fwd_dn_supported(const TailArgs &a);

@@ -1,0 +1,57 @@
+// Backward-feature on scattered tiles for any group: geometry and dispatch (kernel: tail_any.hpp),
+// with the instantiations for 64 rows and up to 768 features.
+#include "tail_any.hpp"
+
+namespace haste {
+
+hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s);
+hipError_t bwd_x_any_2_12(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s);
+
+// bf16; 64 rows of dY, and a segment's weights and supports, within the 31-bit range of a buffer
+// offset (the loads run five steps past a segment's end); the group of a label by multiply-high.
+bool bwd_x_any_supported(const TailArgs &a) {
+    if (a.dtype != HASTE_DTYPE_BF16 || a.F_s > kMaxFs || a.L * 128 >= ((int64_t)1 << 31)) return false;
+    const AxGeom g = ax_geom(a);
+    const int64_t far = g.lps + 256;
+    return g.ni != 0 && far * a.F_in * 4 < ((int64_t)1 << 31) && (far + a.G) * a.G < ((int64_t)1 << 32);
+}
+
+// Where another kernel takes the layer too, measured per call at F_s = 768 (us; 328K labels):
+//   - one label per group, up to 64 slots or 32 rows: the scattered-tile kernel whose waves all do both
+//     jobs (64 slots, 32 / 64 / 256 rows: 52 / 68 / 162 there, 58 / 63 / 167 here; 128 slots 69 / 92 /
+//     280 against 86 / 89 / 245);
+//   - groups in LDS accumulators (general kernel, plus its transposition of W): that costs a
+//     read-add-write per (group, slot, row), the dense product FR multiply-adds per label, so the
+//     accumulators win where a group has few slots for its labels (256 rows, G = 32: 32 / 64 / 128 slots
+//     61 / 90 / 166 there, 113 / 119 / 126 here; G = 16: 91 / 134 / 235 against 111 / 117 / 125), and
+//     up to 64 rows the transposition does not pay back (32 rows, G = 32: 45 / 54 / 79 against 44 / 48
+//     / 47; 64 rows 64 slots 52 / 52);
+//   - everything else (other group sizes and widths: vector ALUs, or small groups of wide inputs)
+//     20 times slower there.
+bool bwd_x_any_preferred(const TailArgs &a) {
+    if (!bwd_x_any_supported(a) || bwd_x_dn_supported(a)) return false;
+    if (bwd_x_mfma_supported(a)) {
+        const AxGeom g = ax_geom(a);
+        const int64_t per = a.G < 32 ? a.G : 32;
+        return a.B <= 64 || a.F_in * 768 >= 4 * per * (g.nsplit * 64 * g.nft);
+    }
+    return bwd_x_sg_supported(a) || valu_supported(a);
+}
+
+size_t bwd_x_any_ws(const TailArgs &a) {
+    const AxGeom g = ax_geom(a);
+    return (size_t)round_up(g.nseg * a.F_s * (g.nbt * 16 * g.mt) * 4, 256);
+}
+
+hipError_t bwd_x_any(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
+                     hipStream_t s) {
+    const AxGeom g = ax_geom(a);
+    float *part = reinterpret_cast<float *>(ws);
+    const hipError_t e = g.mt == 2    ? bwd_x_any_2_12(a, idx, W, dY, part, s)
+                         : g.nft == 8 ? bwd_x_any_4_8(a, idx, W, dY, part, s)
+                                      : AxRun<4, 12>{a, g, idx, W, dY, part, s}.run();
+    if (e != hipSuccess) return e;
+    return reduce_fmajor(part, (int)g.nseg, g.nbt * 16 * g.mt, a.B, a.F_s, dX, beta, s);
+}
+
+}  // namespace haste

@@ -1,0 +1,11 @@
+// Backward-feature on scattered tiles for any group: the instantiations for 64 rows and up to 512 features (each share of wider inputs too).
+#include "tail_any.hpp"
+
+namespace haste {
+
+hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s) {
+    const AxGeom g = ax_geom(a);
+    return AxRun<4, 8>{a, g, idx, W, dY, part, s}.run();
+}
+
+}  // namespace haste

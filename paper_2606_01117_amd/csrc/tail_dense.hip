@@ -1,11 +1,11 @@
-// Backward-feature for small groups as a dense matrix-core product over scattered weight tiles
-// (bf16, G in {1, 2, 4, 8}).
+// Backward-feature for standard fixed fan-in (one label per group) as a dense matrix-core product over
+// scattered weight tiles (bf16).
 //
 //   dX[rows, f] = sum over labels l of dY[rows, l] W'[l, f],   W'[l, f] = W[l, t] where
 //   idx[g(l), t] = f, and 0 where f is not in the support of l's group   (Section 3.2, the
 //   backward-feature product; W' is the weight grid of Fig. 2 (d) with its empty cells as zeros).
 //
-// With G <= 8 a group's tile of the segmented-accumulator kernels is mostly padding, and their
+// With one label per group a group's tile of the segmented-accumulator kernels is mostly padding, and their
 // LDS traffic per (label, slot, row) is a 4-byte read and a 4-byte write of the accumulator.  Here
 // the accumulator never leaves the registers: a workgroup owns 16 MT batch rows and all F_s
 // features (dX^T [F_s][16 MT] fp32 spread over its 8 waves' matrix-core accumulators) for a
@@ -48,7 +48,7 @@ typedef __attribute__((address_space(3))) bf16x8_t lds_bf16x8_t;
 template <int NWV, int MT, int F_IN, int NFT, bool TAILP>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * NWV, 64 * NWV), amdgpu_waves_per_eu(NWV / 4, NWV / 4)))
 void k_bwd_x_dn(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ dY,
-                float *__restrict__ part, int B, int Bp, int F_s, int FR, int64_t L, int gshift, int nbt,
+                float *__restrict__ part, int B, int Bp, int F_s, int FR, int64_t L, int nbt,
                 int64_t lps) {
     constexpr int T = 64 * NWV;                   // threads
     constexpr int RW = 16 * MT;                   // batch rows of the workgroup
@@ -96,8 +96,7 @@ void k_bwd_x_dn(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, c
     const int o = tid % LPL;
     const uint32_t lpos = (uint32_t)(((ls >> 3) << 4) | ((ls & 7) << 1));   // chunk and label bits
     const Buf wseg(W + l_begin * F_IN, (uint32_t)((l_end - l_begin) * F_IN * 2));
-    const int64_t g_begin = l_begin >> gshift;
-    const Buf iseg(idx + g_begin * F_IN, (uint32_t)(((l_end >> gshift) - g_begin) * F_IN * 4));
+    const Buf iseg(idx + l_begin * F_IN, (uint32_t)((l_end - l_begin) * F_IN * 4));
     // dY: lane -> row tid / PPR, labels PL (tid mod PPR) .. + PL - 1 of the step
     const int rows = B - b0 < RW ? B - b0 : RW;
     const int dr = tid / PPR, dp = tid % PPR;
@@ -128,8 +127,7 @@ void k_bwd_x_dn(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, c
                 r.wv[4 * i + 3] = x.w;
             }
         }
-        const int64_t gl = ((l_begin + lr) >> gshift) - g_begin;
-        const uint32_t io = (uint32_t)(gl * F_IN * 4 + E * 4 * o);
+        const uint32_t io = (uint32_t)(lr * F_IN * 4 + E * 4 * o);
         if constexpr (E == 2) {
             const uint2 x = iseg.ld8(io);
             r.f[0] = (int32_t)x.x;
@@ -556,9 +554,8 @@ static hipError_t launch_dn(const haste::TailArgs &a, const DnGeom &g, const int
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)g.lds);
     if (e != hipSuccess) return e;
-    const int gshift = a.G == 1 ? 0 : a.G == 2 ? 1 : a.G == 4 ? 2 : 3;
     hipLaunchKernelGGL(kern, dim3((unsigned)(g.nseg * g.nbt)), dim3(64 * NWV), g.lds, s, idx, (const bf16_t *)W,
-                       (const bf16_t *)dY, part, (int)a.B, g.nbt * 16 * MT, (int)a.F_s, g.FR, a.L, gshift, g.nbt, g.lps);
+                       (const bf16_t *)dY, part, (int)a.B, g.nbt * 16 * MT, (int)a.F_s, g.FR, a.L, g.nbt, g.lps);
     return hipGetLastError();
 }
 
@@ -930,12 +927,13 @@ static hipError_t wd_f(const haste::TailArgs &a, const void *Xb, const int32_t *
 
 namespace haste {
 
-// bf16, G in {1, 2, 4, 8}, F_in in {32, 64, 128}; F_s up to 768 (three [768][32] tiles fill the
-// LDS); dY rows dword-aligned (L even) and a workgroup's rows within the 31-bit range of a buffer offset;
+// bf16, G = 1, F_in in {32, 64}, or 128 for up to 32 rows (larger groups, and wider supports over more
+// rows, are faster with producer waves: bwd_x_any_preferred); F_s up to 768 (three [768][32] tiles
+// fill the LDS); dY rows dword-aligned (L even) and a workgroup's rows within the 31-bit range of a buffer offset;
 // a segment's weight and support offsets within that range too.
 bool bwd_x_dn_supported(const TailArgs &a) {
-    if (a.dtype != HASTE_DTYPE_BF16 || !(a.G == 1 || a.G == 2 || a.G == 4 || a.G == 8)) return false;
-    if (!(a.F_in == 32 || a.F_in == 64 || a.F_in == 128)) return false;
+    if (a.dtype != HASTE_DTYPE_BF16 || a.G != 1) return false;
+    if (!(a.F_in == 32 || a.F_in == 64 || (a.F_in == 128 && a.B <= 32))) return false;
     if (a.F_s <= 0 || a.L % 2 != 0 || a.L * 64 * 2 >= ((int64_t)1 << 31)) return false;
     const DnGeom g = dn_geom(a);
     return g.nft != 0 && g.lds <= 160 * 1024 && (g.lps + 1024) * a.F_in * 4 < ((int64_t)1 << 31);

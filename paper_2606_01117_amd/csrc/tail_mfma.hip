@@ -1779,9 +1779,10 @@ static hipError_t bwd_x_main(const TailArgs &a, const BwdXGeom &g, const int32_t
 
 // ---- the tail's training pass: fused forward + loss gradient + dW, then backward-feature ----------
 // Groups of 32 labels, where a fused-kernel wave's unit is one group: that kernel also writes the
-// transposed weights and lane-ordered supports backward-feature reads (the pre-pass is skipped).
+// transposed weights and lane-ordered supports backward-feature reads (the pre-pass is skipped).  Where
+// the scattered-tile kernel is the faster backward-feature, the two calls run instead.
 bool tail_step_fused(const TailArgs &a, int P) {
-    return a.G == 32 && fwd_bce_mfma_supported(a, P) && bwd_x_mfma_supported(a);
+    return a.G == 32 && fwd_bce_mfma_supported(a, P) && bwd_x_mfma_supported(a) && !bwd_x_any_preferred(a);
 }
 
 size_t tail_step_ws(const TailArgs &a, int P) { return round_up(bwd_x_mfma_ws(a), 256) + fwd_bce_mfma_ws(a, P); }
