@@ -81,17 +81,20 @@ bool fwd_kernel_exists(const haste::TailArgs &a) {
 
 // the small-group forward kernels form the loss gradient as they store (given the sorted positives)
 bool fwd_small_bce(const haste::TailArgs &a, int P) {
-    return P <= haste::kSortPosMax && (haste::fwd_dn_supported(a) || haste::fwd_sg_supported(a));
+    return P <= haste::kSortPosMax &&
+           (haste::fwd_any_preferred(a) || haste::fwd_dn_supported(a) || haste::fwd_sg_supported(a));
 }
 
 hipError_t fwd_small(const haste::TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias,
                      void *Y, hipStream_t s, const int32_t *spos, int P) {
+    if (haste::fwd_any_preferred(a)) return haste::fwd_any(a, X, idx, W, bias, Y, s, spos, P);
     if (haste::fwd_dn_supported(a)) return haste::fwd_dn(a, X, idx, W, bias, Y, s, spos, P);
     return haste::fwd_sg(a, X, idx, W, bias, Y, s, spos, P);
 }
 
-hipError_t fwd_any(const haste::TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias,
+hipError_t fwd_run(const haste::TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias,
                    void *Y, hipStream_t s) {
+    if (haste::fwd_any_preferred(a)) return haste::fwd_any(a, X, idx, W, bias, Y, s);
     if (haste::fwd_dn_supported(a)) return haste::fwd_dn(a, X, idx, W, bias, Y, s);
     if (haste::fwd_sg_supported(a)) return haste::fwd_sg(a, X, idx, W, bias, Y, s);
     if (haste::fwd_mfma_supported(a)) return haste::fwd_mfma(a, X, idx, W, bias, Y, s);
@@ -116,11 +119,23 @@ bool bwd_w_uses_xt(const haste::TailArgs &a) {
     return haste::bwd_w_dn_supported(a) || haste::bwd_w_sg_supported(a) || haste::bwd_w_mfma_supported(a);
 }
 
-hipError_t bwd_w_any(const haste::TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW,
-                     float *dbias, int beta, void *ws, hipStream_t s) {
+// layers of other groups and supports take the matrix-core kernel where the workspace holds the X^T
+// copy; they never had to bring one, so a smaller workspace takes them to the vector ALUs
+bool bwd_w_takes_xt(const haste::TailArgs &a) {
+    return !bwd_w_uses_xt(a) && haste::bwd_w_any_supported(a) && haste::valu_supported(a);
+}
+
+size_t bwd_w_ws(const haste::TailArgs &a) {
+    return bwd_w_uses_xt(a) || bwd_w_takes_xt(a) ? haste::bwd_w_mfma_ws(a) : 0;
+}
+
+hipError_t bwd_w_run(const haste::TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW,
+                     float *dbias, int beta, void *ws, size_t ws_bytes, hipStream_t s) {
     if (haste::bwd_w_dn_supported(a)) return haste::bwd_w_dn(a, X, idx, dY, dW, dbias, beta, ws, s);
     if (haste::bwd_w_sg_supported(a)) return haste::bwd_w_sg(a, X, idx, dY, dW, dbias, beta, ws, s);
     if (haste::bwd_w_mfma_supported(a)) return haste::bwd_w_mfma(a, X, idx, dY, dW, dbias, beta, ws, s);
+    if (bwd_w_takes_xt(a) && ws && aligned16(ws) && ws_bytes >= haste::bwd_w_mfma_ws(a))
+        return haste::bwd_w_mfma(a, X, idx, dY, dW, dbias, beta, ws, s);
     return haste::bwd_w_valu(a, X, idx, dY, dW, dbias, beta, s);
 }
 
@@ -156,14 +171,14 @@ size_t haste_workspace_bytes(const haste_desc_t *d, int op) {
     if (a.B == 0 || a.L == 0) return 0;
     switch (op) {
         case HASTE_OP_FWD: return 0;
-        case HASTE_OP_BWD_W: return bwd_w_uses_xt(a) ? haste::bwd_w_mfma_ws(a) : 0;
+        case HASTE_OP_BWD_W: return bwd_w_ws(a);
         case HASTE_OP_BWD_X: return bwd_x_ws(a);
         // the fused kernel and the backward-weight kernel stage the same X^T copy; the fused kernel
         // also buckets rows of many positives (provided for up to kFusedPosWs per row)
         // small groups: the sorted positives (for rows of up to kSortPosMax) after the X^T copy
         case HASTE_OP_FWD_BCE: {
             if (haste::fwd_bce_mfma_supported(a, haste::kFusedPosWs)) return haste::fwd_bce_mfma_ws(a, haste::kFusedPosWs);
-            const size_t xws = bwd_w_uses_xt(a) ? haste::bwd_w_mfma_ws(a) : 0;
+            const size_t xws = bwd_w_ws(a);
             if (!fwd_small_bce(a, 0)) return xws;
             return (size_t)haste::round_up((int64_t)xws, 256) +
                    (size_t)haste::round_up(a.B * haste::kSortPosMax * 4, 256);
@@ -204,7 +219,7 @@ int haste_fwd(const haste_desc_t *d, const void *X, const int32_t *idx, const vo
     TRY(need_ptr(Y, "Y"));
     if (bias && !aligned16(bias)) return fail(HASTE_ERR_INVALID, "bias is not 16-byte aligned");
     if (!fwd_kernel_exists(a)) return fail(HASTE_ERR_UNSUPPORTED, "no forward kernel for this shape");
-    return hip_status(fwd_any(a, X, idx, W, bias, Y, as_stream(stream)), "haste_fwd");
+    return hip_status(fwd_run(a, X, idx, W, bias, Y, as_stream(stream)), "haste_fwd");
 }
 
 int haste_bwd_w(const haste_desc_t *d, const void *X, const int32_t *idx, const void *dY, float *dW, float *dbias,
@@ -230,10 +245,10 @@ int haste_bwd_w(const haste_desc_t *d, const void *X, const int32_t *idx, const 
         if (!ws || ws_bytes < need)
             return fail(HASTE_ERR_WORKSPACE, "haste_bwd_w needs %zu workspace bytes, got %zu", need, ws ? ws_bytes : 0);
         TRY(need_ptr(ws, "ws"));
-        return hip_status(bwd_w_any(a, X, idx, dY, dW, dbias, beta, ws, s), "haste_bwd_w");
+    } else if (!haste::valu_supported(a)) {
+        return fail(HASTE_ERR_UNSUPPORTED, "no backward-weight kernel for this shape");
     }
-    if (!haste::valu_supported(a)) return fail(HASTE_ERR_UNSUPPORTED, "no backward-weight kernel for this shape");
-    return hip_status(haste::bwd_w_valu(a, X, idx, dY, dW, dbias, beta, s), "haste_bwd_w");
+    return hip_status(bwd_w_run(a, X, idx, dY, dW, dbias, beta, ws, ws_bytes, s), "haste_bwd_w");
 }
 
 int haste_bwd_x(const haste_desc_t *d, const int32_t *idx, const void *W, const void *dY, float *dX, int beta,
@@ -351,11 +366,11 @@ int haste_fwd_bce(const haste_desc_t *d, const void *X, const int32_t *idx, cons
     } else {
         // composed: logits into dY, the gradient in place
         if (!fwd_kernel_exists(a)) return fail(HASTE_ERR_UNSUPPORTED, "no forward kernel for this shape");
-        e = fwd_any(a, X, idx, W, bias, dY, s);
+        e = fwd_run(a, X, idx, W, bias, dY, s);
         if (e == hipSuccess) e = haste::bce_grad(a.B, a.L, a.dtype, dY, P > 0 ? pos : nullptr, P, dY, s);
     }
     if (e == hipSuccess && dW)
-        e = bwd_w_any(a, X, idx, dY, dW, dbias, beta, ws, s);
+        e = bwd_w_run(a, X, idx, dY, dW, dbias, beta, ws, ws_bytes, s);
     return hip_status(e, "haste_fwd_bce");
 }
 

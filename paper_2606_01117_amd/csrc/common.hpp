@@ -106,6 +106,12 @@ struct Buf {
         return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
     }
     // POLICY: cache-policy bits of the instruction (kStreaming marks data not read again soon)
+    __device__ __forceinline__ void st2(uint16_t v, uint32_t off) const {
+        __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)off, 0, 0);
+    }
+    __device__ __forceinline__ void st4(uint32_t v, uint32_t off) const {
+        __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, 0);
+    }
     template <int POLICY = 0>
     __device__ __forceinline__ void st8(uint2 v, uint32_t off) const {
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0)), v),
@@ -266,6 +272,11 @@ bool bwd_x_any_preferred(const TailArgs &a);
 size_t bwd_x_any_ws(const TailArgs &a);
 hipError_t bwd_x_any(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
                      hipStream_t s);
+// forward on the same tiles; spos as in fwd_sg
+bool fwd_any_supported(const TailArgs &a);
+bool fwd_any_preferred(const TailArgs &a);
+hipError_t fwd_any(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
+                   hipStream_t s, const int32_t *spos = nullptr, int P = 0);
 // forward for groups of 1 or 2 labels (F_s <= 768) as a dense product over each 32-label step's
 // weights scattered into an LDS tile
 bool fwd_dn_supported(const TailArgs &a);
@@ -277,6 +288,7 @@ bool bwd_w_dn_supported(const TailArgs &a);
 hipError_t bwd_w_dn(const TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW, float *dbias,
                     int beta, void *ws, hipStream_t s);
 bool bwd_w_mfma_supported(const TailArgs &a);
+bool bwd_w_any_supported(const TailArgs &a);   // the same kernel for any group and support
 size_t bwd_w_mfma_ws(const TailArgs &a);
 hipError_t bwd_w_mfma(const TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW,
                       float *dbias, int beta, void *ws, hipStream_t s);

@@ -7,6 +7,41 @@ namespace haste {
 hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s);
 hipError_t bwd_x_any_2_12(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s);
 
+hipError_t fwd_any_48(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
+                      const int32_t *spos, int P, hipStream_t s);
+hipError_t fwd_any_32(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
+                      const int32_t *spos, int P, hipStream_t s);
+
+// forward: as backward-feature, with up to 768 features (the tiles and two steps' logits fill the LDS)
+bool fwd_any_supported(const TailArgs &a) {
+    if (a.F_s > 768 || !bwd_x_any_supported(a)) return false;
+    const FaGeom g = fa_geom(a);
+    const int64_t far = g.lps + 256;
+    return far * a.F_in * 4 < ((int64_t)1 << 31) && (far + a.G) * a.G < ((int64_t)1 << 32);
+}
+
+// Where another kernel takes the layer too, measured per call at F_s = 768 (us; 328K labels):
+//   - groups of 1 or 2 labels: the scattered tiles of 32 rows per workgroup are written once per 32 rows
+//     there, once per 128 here (G = 1, 64 slots, 32 / 64 / 128 / 256 rows: 37 / 60 / 111 / 204 there, 51 /
+//     54 / 65 / 110 here);
+//   - groups of 4 or 8: their gathers cost about (20 + 3 F_in / G) / 3.3 us per 32 rows, this 53 per 128
+//     (256 rows, G = 4, 32 / 64 / 128 slots: 101 / 153 / 284 there, 104 / 107 / 113 here; G = 8: 79 /
+//     104 / 169 against 102 / 104 / 109);
+//   - larger groups share each gather among 16 labels or more (G = 16, 64 slots: 65 there, 104 here);
+//   - everything else (other group sizes and widths) runs on the vector ALUs, 8 times slower.
+bool fwd_any_preferred(const TailArgs &a) {
+    if (!fwd_any_supported(a)) return false;
+    if (fwd_dn_supported(a)) return a.B > 32;
+    if (fwd_sg_supported(a))
+        return cdiv(a.B, 32) * (20 + 3 * a.F_in / a.G) * 48 > 177 * cdiv(a.B, 128) * fa_geom(a).nc;
+    return !fwd_mfma_supported(a) && valu_supported(a);
+}
+
+hipError_t fwd_any(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
+                   hipStream_t s, const int32_t *spos, int P) {
+    return a.F_s <= 512 ? fwd_any_32(a, X, idx, W, bias, Y, spos, P, s) : fwd_any_48(a, X, idx, W, bias, Y, spos, P, s);
+}
+
 // bf16; 64 rows of dY, and a segment's weights and supports, within the 31-bit range of a buffer
 // offset (the loads run five steps past a segment's end); the group of a label by multiply-high.
 bool bwd_x_any_supported(const TailArgs &a) {

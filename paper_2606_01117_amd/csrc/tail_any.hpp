@@ -1,5 +1,5 @@
-// Backward-feature as a dense matrix-core product over scattered weight tiles, for groups of any
-// size and supports of any width (bf16).
+// Backward-feature and forward as dense matrix-core products over scattered weight tiles, for groups of
+// any size and supports of any width (bf16).  Backward-feature first:
 //
 //   dX[rows, f] = sum over labels l of dY[rows, l] W'[l, f],   W'[l, f] = W[l, t] where
 //   idx[g(l), t] = f, and 0 where f is not in the support of l's group   (Section 3.2, the
@@ -73,6 +73,131 @@ __device__ __forceinline__ u32x4_t load_row8(const Buf &b, uint32_t o, int64_t n
     }
 }
 
+// The producers' side of a [FR][32 labels] tile: four waves write a step's weights and clear an earlier
+// step's.  Wave wv writes labels 8 wv .. 8 wv + 7 of every step, one 16-byte chunk of each tile row (with
+// random features and the chunk swizzle those cells lie in all of a tile's banks), so that its clears
+// and writes of a cell are ordered by its own program order.  A lane owns one pack of PK labels and NI
+// slot pairs of their group.  SPARE: features outside f0 .. f0 + FR - 1 (and pairs past the support) are
+// written to a spare cell at offset `none`; without it every feature lies in the tile, and lanes with
+// no pair of their own repeat the last one.
+template <int PK, int NI, int READ, int FR, bool SPARE>
+struct AxTiles {
+    static constexpr int TB = FR * 64;            // bytes of a tile
+    static constexpr int LPK = 8 * PK;            // lanes of one pack
+    static constexpr int NV = PK / 2 > 0 ? PK / 2 : 1;
+    static constexpr uint32_t kNo = 0xffffu;      // no cell (a tile's last byte is never a cell's first)
+    struct Slot {                                 // a step's loads
+        uint32_t w[NI][PK];
+        int32_t f[NI][2];
+    };
+    Buf wseg, iseg;
+    uint32_t lbase, none, lcol, r0, gmul;
+    int lo, F_in, f0;
+    int sl[NI];                                   // the pairs' first slots (-2: none)
+
+    // pt: producer thread 0 .. 255; the segment's labels are l_begin .. l_end - 1
+    __device__ __forceinline__ AxTiles(const int32_t *idx, const bf16_t *W, int64_t l_begin, int64_t l_end, int G,
+                                       uint32_t gmul_, int F_in_, int f0_, uint32_t lbase_, uint32_t none_, int pt)
+        : wseg(W + l_begin * F_in_, (uint32_t)((l_end - l_begin) * F_in_ * 2)),
+          iseg(idx + l_begin / G * F_in_, (uint32_t)(((l_end + G - 1) / G - l_begin / G) * F_in_ * 4)), lbase(lbase_),
+          none(none_), r0((uint32_t)(l_begin % G)), gmul(gmul_), F_in(F_in_), f0(f0_) {
+        const int lane = pt & 63;
+        lo = 8 * (pt >> 6) + lane / LPK * PK;
+        lcol = (uint32_t)((lo >> 3) << 4 | (lo & 7) << 1);
+        const int last = (F_in - 1) & ~1;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int t = 2 * (lane % LPK + LPK * i);
+            sl[i] = t <= last ? t : SPARE ? -2 : last;
+        }
+    }
+    // step st of the segment; labels past its end have zero weights
+    __device__ __forceinline__ void load(int st, Slot &r) const {
+        const uint32_t lr = (uint32_t)(st * 32 + lo);
+        const uint32_t wo = lr * (uint32_t)F_in * 2u, io0 = div_by(lr + r0, gmul) * (uint32_t)F_in * 4u;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const bool ok = !SPARE || sl[i] >= 0;
+#pragma unroll
+            for (int j = 0; j < PK; ++j) {
+                const uint32_t o = wo + (uint32_t)(j * F_in + sl[i]) * 2u;
+                if constexpr (READ == kRead2)
+                    r.w[i][j] = (uint32_t)wseg.ld2(ok ? o : kOob) | ((uint32_t)wseg.ld2(ok ? o + 2 : kOob) << 16);
+                else
+                    r.w[i][j] = wseg.ld4(ok ? o : kOob);
+            }
+            const uint32_t io = ok ? io0 + (uint32_t)sl[i] * 4u : kOob;
+            if constexpr (READ == kRead2) {
+                r.f[i][0] = (int32_t)iseg.ld4(io);
+                r.f[i][1] = (int32_t)iseg.ld4(ok ? io + 4 : kOob);
+            } else {
+                const uint2 v = iseg.ld8(io);
+                r.f[i][0] = (int32_t)v.x;
+                r.f[i][1] = (int32_t)v.y;
+            }
+        }
+    }
+    __device__ __forceinline__ uint32_t cell(uint32_t fr) const { return (fr << 6) | (lcol ^ ((fr << 2) & 0x30u)); }
+    __device__ __forceinline__ void put(uint32_t a, const uint32_t (&v)[NV]) const {
+        if constexpr (PK == 1) *(lds_u16_t *)(uintptr_t)a = (uint16_t)v[0];
+        else if constexpr (PK == 2) *(lds_u32_t *)(uintptr_t)a = v[0];
+        else if constexpr (PK == 4) *(lds_u32x2_t *)(uintptr_t)a = u32x2_t{v[0], v[1]};
+        else *(lds_u32x4_t *)(uintptr_t)a = u32x4_t{v[0], v[1], v[2], v[3]};
+    }
+    // Cells written by a step, as offsets from the tile's base, a pair of slots per word (a tile is less
+    // than 64 KiB).  Before the first step: none, or this lane's own cell of feature 0 (still zero).
+    __device__ __forceinline__ void no_cells(uint32_t (&c)[NI]) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) c[i] = SPARE ? kNo | (kNo << 16) : lcol | (lcol << 16);
+    }
+    __device__ __forceinline__ void scatter(const Slot &r, int tb, uint32_t (&c)[NI]) const {
+        const uint32_t base = lbase + (uint32_t)(tb * TB);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            uint32_t v0[NV], v1[NV];
+            if constexpr (PK == 1) {
+                v0[0] = r.w[i][0];
+                v1[0] = r.w[i][0] >> 16;
+            } else {
+#pragma unroll
+                for (int j = 0; j < PK / 2; ++j) {
+                    v0[j] = __builtin_amdgcn_perm(r.w[i][2 * j + 1], r.w[i][2 * j], 0x05040100u);
+                    v1[j] = __builtin_amdgcn_perm(r.w[i][2 * j + 1], r.w[i][2 * j], 0x07060302u);
+                }
+            }
+            const bool two = READ != kRead2 || sl[i] + 1 < F_in;
+            if constexpr (SPARE) {
+                const uint32_t fa = (uint32_t)(r.f[i][0] - f0), fb = (uint32_t)(r.f[i][1] - f0);
+                const bool ok0 = sl[i] >= 0 && fa < (uint32_t)FR, ok1 = sl[i] >= 0 && fb < (uint32_t)FR && two;
+                const uint32_t c0 = ok0 ? cell(fa) : kNo, c1 = ok1 ? cell(fb) : kNo;
+                c[i] = c0 | (c1 << 16);
+                put(ok0 ? base + c0 : none, v0);
+                put(ok1 ? base + c1 : none, v1);
+            } else {
+                const uint32_t fa = min((uint32_t)r.f[i][0], (uint32_t)(FR - 1));
+                const uint32_t fb = two ? min((uint32_t)r.f[i][1], (uint32_t)(FR - 1)) : fa;
+                if (!two)
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) v1[j] = v0[j];
+                const uint32_t c0 = cell(fa), c1 = cell(fb);
+                c[i] = c0 | (c1 << 16);
+                put(base + c0, v0);
+                put(base + c1, v1);
+            }
+        }
+    }
+    __device__ __forceinline__ void clear(int tb, const uint32_t (&c)[NI]) const {
+        const uint32_t base = lbase + (uint32_t)(tb * TB);
+        const uint32_t z[NV] = {};
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const uint32_t c0 = c[i] & 0xffffu, c1 = c[i] >> 16;
+            put(SPARE && c0 == kNo ? none : base + c0, z);
+            put(SPARE && c1 == kNo ? none : base + c1, z);
+        }
+    }
+};
+
 // MT: 16-row tiles per workgroup.  NFT: 16-feature tiles per consumer wave (tiles w, w + 4, ...).
 // PK: labels per tile write.  NI: slot pairs per producer lane and step (32 / PK packs of
 // ceil(F_in / 2) pairs over 256 lanes).  READ: as above.  The workgroup covers features f0 .. f0 +
@@ -112,26 +237,9 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
 
     if (wave >= kAxCons) {
         // ---- producers ----
-        constexpr uint32_t kNone = 3 * TB + 3 * SB;   // the spare cell, as an offset from the first tile
         const int pt = tid - 64 * kAxCons;
-        // Wave wv writes labels 8 wv .. 8 wv + 7 of every step, one 16-byte chunk of each tile row (with
-        // random features and the chunk swizzle those cells lie in all of a tile's banks), so that its
-        // clears and writes of a cell are ordered by its own program order.  This lane: the pack of
-        // labels lo .. lo + PK - 1, slots sl[i] and sl[i] + 1 (-2: none).
-        constexpr int LPK = 8 * PK;               // lanes of one pack
-        const int wv = pt >> 6;
-        const int lo = 8 * wv + lane / LPK * PK;
-        int sl[NI];
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int p = lane % LPK + LPK * i;
-            sl[i] = 2 * p < F_in ? 2 * p : -2;
-        }
-        const Buf wseg(W + l_begin * F_in, (uint32_t)((l_end - l_begin) * F_in * 2));
-        const int64_t g0 = l_begin / G;
-        const uint32_t r0 = (uint32_t)(l_begin - g0 * G);   // labels of group g0 before the segment
-        const int64_t g_end = (l_end + G - 1) / G;
-        const Buf iseg(idx + g0 * F_in, (uint32_t)((g_end - g0) * F_in * 4));
+        using Tiles = AxTiles<PK, NI, READ, FR, true>;
+        const Tiles tl(idx, W, l_begin, l_end, G, gmul, F_in, f0, lbase, lbase + 3 * TB + 3 * SB, pt);
         // dY: lane -> row pt / 4 of 64 (MT = 2: row pt / 4 of 32, lanes past them none), 8 labels
         const int rows = B - b0 < RW ? B - b0 : RW;
         const int dr = pt >> 2, dp = pt & 3;
@@ -140,93 +248,22 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
         const uint32_t yst = sbase + (uint32_t)(dr * kAxStageRow + 16 * dp);
 
         struct Slot {
-            uint32_t w[NI][PK];
-            int32_t f[NI][2];
+            typename Tiles::Slot w;
             u32x4_t y;
         };
         constexpr int RD = ax_ring(NI);
         Slot rg[RD];
         auto load_step = [&](int st, Slot &r) __attribute__((always_inline)) {
-            const uint32_t lr = (uint32_t)(st * 32 + lo);
-            const uint32_t wo = lr * (uint32_t)F_in * 2u, io0 = div_by(lr + r0, gmul) * (uint32_t)F_in * 4u;
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const bool ok = sl[i] >= 0;
-#pragma unroll
-                for (int j = 0; j < PK; ++j) {
-                    const uint32_t o = wo + (uint32_t)(j * F_in + sl[i]) * 2u;
-                    if constexpr (READ == kRead2) r.w[i][j] = (uint32_t)wseg.ld2(ok ? o : kOob) | ((uint32_t)wseg.ld2(ok ? o + 2 : kOob) << 16);
-                    else r.w[i][j] = wseg.ld4(ok ? o : kOob);
-                }
-                const uint32_t io = ok ? io0 + (uint32_t)sl[i] * 4u : kOob;
-                if constexpr (READ == kRead2) {
-                    r.f[i][0] = (int32_t)iseg.ld4(io);
-                    r.f[i][1] = (int32_t)iseg.ld4(ok ? io + 4 : kOob);
-                } else {
-                    const uint2 v = iseg.ld8(io);
-                    r.f[i][0] = (int32_t)v.x;
-                    r.f[i][1] = (int32_t)v.y;
-                }
-            }
+            tl.load(st, r.w);
             const int64_t lab = l_begin + (int64_t)st * 32 + 8 * dp;
             r.y = load_row8<READ>(dseg, (uint32_t)(((int64_t)dr * L + lab) * 2), dr < rows ? l_end - lab : 0);
         };
-        // offsets from the tile's base of the cells written by a step, to be cleared three steps later
-        // (a pair of slots per word: a tile is less than 64 KiB)
-        uint32_t ca[3][NI];
-        const uint32_t lcol = (uint32_t)((lo >> 3) << 4 | (lo & 7) << 1);   // chunk and label of the pack
-        auto cell = [&](int32_t f) __attribute__((always_inline)) -> uint32_t {
-            const uint32_t fr = (uint32_t)(f - f0);
-            return (fr << 6) | (lcol ^ ((fr << 2) & 0x30u));
-        };
-        auto put = [&](uint32_t a, const uint32_t (&v)[PK / 2 > 0 ? PK / 2 : 1]) __attribute__((always_inline)) {
-            if constexpr (PK == 1) *(lds_u16_t *)(uintptr_t)a = (uint16_t)v[0];
-            else if constexpr (PK == 2) *(lds_u32_t *)(uintptr_t)a = v[0];
-            else if constexpr (PK == 4) *(lds_u32x2_t *)(uintptr_t)a = u32x2_t{v[0], v[1]};
-            else *(lds_u32x4_t *)(uintptr_t)a = u32x4_t{v[0], v[1], v[2], v[3]};
-        };
-        constexpr uint32_t kNo = 0xffffu;          // no cell (a tile's last byte is never a cell's first)
-        auto scatter = [&](const Slot &r, int tb, uint32_t (&c)[NI]) __attribute__((always_inline)) {
-            const uint32_t base = lbase + (uint32_t)(tb * TB);
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                uint32_t v0[PK / 2 > 0 ? PK / 2 : 1], v1[PK / 2 > 0 ? PK / 2 : 1];
-                if constexpr (PK == 1) {
-                    v0[0] = r.w[i][0];
-                    v1[0] = r.w[i][0] >> 16;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < PK / 2; ++j) {
-                        v0[j] = __builtin_amdgcn_perm(r.w[i][2 * j + 1], r.w[i][2 * j], 0x05040100u);
-                        v1[j] = __builtin_amdgcn_perm(r.w[i][2 * j + 1], r.w[i][2 * j], 0x07060302u);
-                    }
-                }
-                const bool ok0 = sl[i] >= 0 && (uint32_t)(r.f[i][0] - f0) < (uint32_t)FR;
-                const bool ok1 = sl[i] >= 0 && (uint32_t)(r.f[i][1] - f0) < (uint32_t)FR &&
-                                 (READ != kRead2 || sl[i] + 1 < F_in);
-                const uint32_t c0 = ok0 ? cell(r.f[i][0]) : kNo, c1 = ok1 ? cell(r.f[i][1]) : kNo;
-                c[i] = c0 | (c1 << 16);
-                put(ok0 ? base + c0 : lbase + kNone, v0);
-                put(ok1 ? base + c1 : lbase + kNone, v1);
-            }
-        };
-        auto clear = [&](int tb, const uint32_t (&c)[NI]) __attribute__((always_inline)) {
-            const uint32_t base = lbase + (uint32_t)(tb * TB);
-            const uint32_t z[PK / 2 > 0 ? PK / 2 : 1] = {};
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const uint32_t c0 = c[i] & 0xffffu, c1 = c[i] >> 16;
-                put(c0 != kNo ? base + c0 : lbase + kNone, z);
-                put(c1 != kNo ? base + c1 : lbase + kNone, z);
-            }
-        };
+        uint32_t ca[3][NI];                       // cells written, to be cleared three steps later
         auto stage_y = [&](const Slot &r, int sb) __attribute__((always_inline)) {
             if (ylane) *(lds_u32x4_t *)(uintptr_t)(yst + (uint32_t)(sb * SB)) = r.y;
         };
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int i = 0; i < NI; ++i) ca[k][i] = kNo | (kNo << 16);
+        for (int k = 0; k < 3; ++k) tl.no_cells(ca[k]);
         // step s waits in ring slot s mod RD, is written into tile and stage s mod 3, and leaves its
         // cells in ca[s mod 3]
 #pragma unroll
@@ -234,15 +271,15 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
             load_step(k, rg[k]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        scatter(rg[0], 0, ca[0]);
+        tl.scatter(rg[0].w, 0, ca[0]);
         stage_y(rg[0], 0);
         load_step(RD, rg[0]);
         __syncthreads();                          // step 0 in its tile
         // interval t: tile (t + 1) mod 3, last read in interval t - 2, loses step t - 2 and takes step t + 1
         auto interval = [&](int t, auto uc) __attribute__((always_inline)) {
             constexpr int N = (decltype(uc)::value + 1) % 3;
-            clear(N, ca[N]);
-            scatter(rg[N % RD], N, ca[N]);
+            tl.clear(N, ca[N]);
+            tl.scatter(rg[N % RD].w, N, ca[N]);
             stage_y(rg[N % RD], N);
             __builtin_amdgcn_sched_barrier(0);
             load_step(t + 1 + RD, rg[N % RD]);
@@ -324,6 +361,251 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Forward on the same tiles: Y[rows, l] = bias[l] + sum over f of X[rows, f] W'[l, f], or with the rows'
+// positives the loss gradient of the rounded logits.
+//
+// A workgroup owns 128 batch rows and a segment of labels: consumer wave w keeps X for rows 32 w ..
+// 32 w + 31 and all FR features in registers (192 at FR = 768) and per step forms D[32 labels][32 rows]
+// with v_mfma_f32_32x32x16_bf16, A read from the feature-major tile with ds_read_b64_tr_b16 (two reads
+// per 16 features).  Every row costs the tile's writes once per 128 rows, and the reads of a tile (48
+// KiB per wave, about 105 bytes per cycle and CU) set the pace, a little above the products.  The bf16
+// logits go to a [32 rows][32 labels] LDS block of the wave, from which its producer wave stores them two
+// steps later (and takes the sigmoid, whose transcendentals the consumers then need not wait for).
+//
+// An empty cell contributes X times zero, which is zero only for finite X.  A workgroup whose rows hold an
+// infinity or a NaN therefore takes each label's own slots one by one instead.
+// ---------------------------------------------------------------------------------------------
+constexpr int kFaStage = 2 * 4 * 2048;            // two steps of four waves' blocks
+__host__ __device__ constexpr int fa_lds(int fr) { return 3 * fr * 64 + kFaStage; }
+
+// element e of row b is a positive of the row (sorted ascending)
+__device__ __forceinline__ bool is_positive(const int32_t *row, int P, int64_t e) {
+    int lo = 0, hi = P;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if ((int64_t)row[mid] < e) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo < P && (int64_t)row[lo] == e;
+}
+
+// NC: 16-feature K chunks (FR = 16 NC >= F_s).
+template <int NC, int PK, int NI, int READ>
+__global__ __attribute__((amdgpu_flat_work_group_size(kAxThreads, kAxThreads), amdgpu_waves_per_eu(2, 2)))
+void k_fwd_any(const bf16_t *__restrict__ X, const int32_t *__restrict__ idx, const bf16_t *__restrict__ W,
+               const float *__restrict__ bias, bf16_t *__restrict__ Y, int B, int F_s, int64_t L, int G, uint32_t gmul,
+               int F_in, int nbt, int64_t lps, const int32_t *__restrict__ spos, int P) {
+    constexpr int FR = 16 * NC, TB = FR * 64;
+    extern __shared__ __align__(16) char ax[];
+    const int w = blockIdx.x, xcd = w % kXcds, jj = w / kXcds;
+    const int bt = jj % nbt;
+    const int64_t seg = (int64_t)(jj / nbt) * kXcds + xcd;
+    const int b0 = bt * 128;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t l_begin = seg * lps;
+    const int64_t l_end = l_begin + lps < L ? l_begin + lps : L;
+    if (l_begin >= l_end) return;                 // workgroup-uniform
+    const int n = (int)((l_end - l_begin + 31) / 32);   // steps
+    const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)ax;
+    const uint32_t sbase = lbase + 3 * TB;
+    for (int e = tid; e < 3 * TB / 16; e += kAxThreads) *(lds_u32x4_t *)(uintptr_t)(lbase + 16 * e) = u32x4_t{0u, 0u, 0u, 0u};
+    if (tid == 0) *(lds_u32_t *)(uintptr_t)sbase = 0u;   // becomes 1 if X is not finite
+
+    // X of the consumers' rows: lane -> row l32, features 16 c + 8 h .. + 7
+    const int l32 = lane & 31, h = lane >> 5;
+    const int row0 = b0 + 32 * (wave & 3);
+    const int rows = B - row0 < 32 ? B - row0 : 32;   // of this wave (or its consumer); none if <= 0
+    bf16x8_t xb[NC];
+    bool bad = false;
+    if (wave < kAxCons && rows > 0) {
+        const Buf xr(X + (int64_t)row0 * F_s, (uint32_t)(rows * F_s * 2));
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int f = 16 * c + 8 * h;
+            const int nv = l32 < rows ? F_s - f : 0;
+            const uint32_t o = (uint32_t)((l32 * F_s + f) * 2);
+            uint4 v;
+            if ((F_s & 7) == 0) {                 // kernel-uniform
+                v = xr.ld16(nv > 0 ? o : kOob);
+            } else {
+                uint32_t e[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) e[k] = xr.ld2(nv > k ? o + 2 * k : kOob);
+                v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+            }
+            const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) bad |= (d[k] & 0x7f80u) == 0x7f80u || (d[k] & 0x7f800000u) == 0x7f800000u;
+            xb[c] = as_bf16x8(v);
+        }
+    }
+    __syncthreads();                              // tiles zeroed
+    if (bad) *(lds_u32_t *)(uintptr_t)sbase = 1u;
+    __syncthreads();
+    if (*(lds_u32_t *)(uintptr_t)sbase != 0u) {   // workgroup-uniform
+        const int nr = B - b0 < 128 ? B - b0 : 128;
+        for (int64_t l = l_begin + tid; l < l_end; l += kAxThreads) {
+            const int32_t *ip = idx + l / G * F_in;
+            for (int r = b0; r < b0 + nr; ++r) {
+                float a = 0.0f;
+                for (int t = 0; t < F_in; ++t) a = fmaf(bf16_to_f32(X[(int64_t)r * F_s + ip[t]]), bf16_to_f32(W[l * F_in + t]), a);
+                bf16_t y = f32_to_bf16(bias ? a + bias[l] : a);
+                if (spos) y = f32_to_bf16(bce_grad_f32(bf16_to_f32(y), is_positive(spos + (int64_t)r * P, P, l)));
+                Y[(int64_t)r * L + l] = y;
+            }
+        }
+        return;
+    }
+
+    if (wave >= kAxCons) {
+        // ---- producers ----
+        const int pt = tid - 64 * kAxCons;
+        using Tiles = AxTiles<PK, NI, READ, FR, false>;
+        const Tiles tl(idx, W, l_begin, l_end, G, gmul, F_in, 0, lbase, 0u, pt);
+        // output of consumer wave - 4: this lane's rows (lane / 4) and 16 + (lane / 4), labels 8 (lane mod 4) ..
+        const int orow = lane >> 2, piece = lane & 3;
+        const Buf yo(Y + (int64_t)row0 * L, (uint32_t)(rows > 0 ? (int64_t)rows * L * 2 : 0));
+        // whole half-lines stream past the L2; pieces that straddle lines must meet there (328K labels in
+        // groups of 24, rows not 128-byte aligned: 179 us streaming, 109 through the L2; aligned 108, 114)
+        const bool lines = L % 64 == 0;
+        PosCursor tg[2];
+        if (spos) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (orow + 16 * k < rows) tg[k].init(spos + (int64_t)(row0 + orow + 16 * k) * P, P, l_begin + 8 * piece);
+        }
+        const uint32_t rd = sbase + (uint32_t)((wave & 3) * 2048 + orow * 64 + ((piece ^ ((orow >> 2) & 3)) << 4));
+        auto flush = [&](int t) __attribute__((always_inline)) {
+            const int64_t lab = l_begin + (int64_t)t * 32 + 8 * piece;
+            const int64_t nv = l_end - lab;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int r = orow + 16 * k;
+                if (r >= rows || nv <= 0) continue;
+                u32x4_t v = *(lds_u32x4_t *)(uintptr_t)(rd + (uint32_t)((t & 1) * 8192 + k * 1024));
+                if (spos) {                       // kernel-uniform
+                    const uint32_t m = tg[k].bits(lab, 8);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[j] = bce_pair(v[j], m >> (2 * j));
+                }
+                const uint32_t o = (uint32_t)(((int64_t)r * L + lab) * 2);
+                if constexpr (READ == kRead16) {
+                    if (lines) yo.st16<kStreaming>(__builtin_bit_cast(uint4, v), o);
+                    else yo.st16(__builtin_bit_cast(uint4, v), o);
+                } else if constexpr (READ == kRead4) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) yo.st4(v[j], nv > 2 * j ? o + 4 * j : kOob);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) yo.st2((uint16_t)(v[j >> 1] >> (16 * (j & 1))), nv > j ? o + 2 * j : kOob);
+                }
+            }
+        };
+        constexpr int RD = ax_ring(NI);
+        typename Tiles::Slot rg[RD];
+        uint32_t ca[3][NI];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) tl.no_cells(ca[k]);
+#pragma unroll
+        for (int k = 0; k < RD; ++k) {
+            tl.load(k, rg[k]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        tl.scatter(rg[0], 0, ca[0]);
+        tl.load(RD, rg[0]);
+        __syncthreads();                          // step 0 in its tile
+        // interval t: as in backward-feature; the logits of step t - 2 were written in interval t - 1
+        auto interval = [&](int t, auto uc) __attribute__((always_inline)) {
+            constexpr int N = (decltype(uc)::value + 1) % 3;
+            tl.clear(N, ca[N]);
+            tl.scatter(rg[N % RD], N, ca[N]);
+            __builtin_amdgcn_sched_barrier(0);
+            tl.load(t + 1 + RD, rg[N % RD]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (t >= 2) flush(t - 2);
+            __syncthreads();
+        };
+        for (int t = 0; t < n; t += 3) {
+            interval(t, std::integral_constant<int, 0>{});
+            if (t + 1 >= n) break;
+            interval(t + 1, std::integral_constant<int, 1>{});
+            if (t + 2 >= n) break;
+            interval(t + 2, std::integral_constant<int, 2>{});
+        }
+        if (n >= 2) flush(n - 2);
+        __syncthreads();                          // the last step's logits
+        flush(n - 1);
+        return;
+    }
+
+    // ---- consumers ----
+    __syncthreads();                              // step 0 in its tile
+    if (rows <= 0) {                              // wave-uniform: no rows, only the barriers
+        for (int t = 0; t <= n; ++t) __syncthreads();
+        return;
+    }
+    __builtin_amdgcn_s_setprio(2);
+    constexpr int RING = NC % 6 == 0 ? 6 : 8, PD = RING - 1;   // operands held; read ahead
+    static_assert(NC % RING == 0, "whole rings per step");
+    // A operand source lanes (ds_read_b64_tr_b16): 16-lane group g = lane / 16 names labels 16 (g & 1) ..
+    // of features 16 c + 8 (g >> 1) + 4 i + jq (read i), 4 labels 4 aq .. + 3 per lane
+    const int g = lane >> 4, jq = (lane & 15) >> 2, aq = lane & 3;
+    uint32_t ao[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        ao[i] = lbase + (uint32_t)((8 * (g >> 1) + 4 * i + jq) * 64 +
+                                   (((2 * (g & 1) + (aq >> 1)) ^ ((2 * (g >> 1) + i) & 3)) << 4) + 8 * (aq & 1));
+    auto read_a = [&](uint32_t tile, int c) __attribute__((always_inline)) -> bf16x8_t {
+        const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t *)(uintptr_t)(ao[0] + tile + 1024 * c));
+        const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_t *)(uintptr_t)(ao[1] + tile + 1024 * c));
+        const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+        return as_bf16x8(make_uint4(l2.x, l2.y, h2.x, h2.y));
+    };
+    // this lane's logits of a step: row l32, labels 8 i + 4 h .. + 3
+    const uint32_t wr = sbase + (uint32_t)(wave * 2048 + l32 * 64 + 8 * h);
+    bf16x8_t oa[RING];
+#pragma unroll
+    for (int c = 0; c < PD; ++c) oa[c] = read_a(0u, c);
+    const Buf bseg(bias ? bias + l_begin : bias, (uint32_t)(bias ? (l_end - l_begin) * 4 : 0));
+    int s3 = 0;                                   // the step's tile
+    for (int t = 0; t < n; ++t) {
+        const uint32_t cur = (uint32_t)(s3 * TB);
+        s3 = s3 == 2 ? 0 : s3 + 1;
+        const uint32_t nxt = (uint32_t)(s3 * TB);
+        f32x16_t acc = f32x16_t{0};
+        if (bias) {                               // kernel-uniform; labels past the segment read as zero
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x4_t v = __builtin_bit_cast(f32x4_t, bseg.ld16((uint32_t)(128 * t + 16 * h + 32 * i)));
+                acc[4 * i] = v[0];
+                acc[4 * i + 1] = v[1];
+                acc[4 * i + 2] = v[2];
+                acc[4 * i + 3] = v[3];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if (c == NC - PD) {
+                // the next step is in its tile (this one's reads may still be in flight: its tile is
+                // written again two barriers on)
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            oa[(c + PD) % RING] = c + PD < NC ? read_a(cur, c + PD) : read_a(nxt, c + PD - NC);
+            __builtin_amdgcn_sched_barrier(0);
+            acc = mfma32x32x16(oa[c % RING], xb[c], acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(lds_u32x2_t *)(uintptr_t)(wr + (uint32_t)((t & 1) * 8192 + ((i ^ ((l32 >> 2) & 3)) << 4))) =
+                u32x2_t{pack_bf16(acc[4 * i], acc[4 * i + 1]), pack_bf16(acc[4 * i + 2], acc[4 * i + 3])};
+    }
+    __syncthreads();                              // the last step's logits are written
+}
+
 // Labels that share a tile write: the largest power of two that divides G, up to 8, or 4 where that
 // gives every producer lane its slot pair (up to 64 slots; with 8 half of the lanes would write
 // nothing: 118 against 107 us on 328K labels in groups of 8, and 124 against 142 with 128 slots).
@@ -364,6 +646,86 @@ inline AxGeom ax_geom(const haste::TailArgs &a) {
     return g;
 }
 
+struct FaGeom {
+    int nc, nbt, pk, ni;
+    int64_t nseg, lps;
+};
+
+inline FaGeom fa_geom(const haste::TailArgs &a) {
+    const AxGeom x = ax_geom(a);
+    FaGeom g;
+    g.nc = a.F_s <= 512 ? 32 : 48;
+    g.nbt = (int)haste::cdiv(a.B, 128);
+    g.pk = x.pk;
+    g.ni = x.ni;
+    int64_t nseg = haste::round_up(haste::cdiv(kXcds * kCusPerXcd, g.nbt), kXcds);
+    const int64_t max_seg = haste::round_up(haste::cdiv(a.L, 64), kXcds);
+    g.nseg = nseg < max_seg ? nseg : max_seg;
+    g.lps = haste::round_up(haste::cdiv(a.L, g.nseg), 64);
+    return g;
+}
+
+// f.go<PK, NI, READ>() for the layer's packs, slot pairs and access width
+template <class F>
+hipError_t ax_pick(const haste::TailArgs &a, int pk, int ni, bool wide, const F &f) {
+    auto read = [&](auto p, auto i) -> hipError_t {
+        constexpr int PK = decltype(p)::value, NI = decltype(i)::value;
+        if (a.F_in % 2 == 0) {
+            if (a.L % 8 == 0 && wide) return f.template go<PK, NI, kRead16>();
+            if constexpr (PK < 8)
+                if (a.L % 2 == 0) return f.template go<PK, NI, kRead4>();
+        }
+        return f.template go<PK, NI, kRead2>();
+    };
+#define HASTE_AX(p, i) \
+    case 100 * p + i: return read(std::integral_constant<int, p>{}, std::integral_constant<int, i>{})
+    switch (100 * pk + ni) {
+        HASTE_AX(1, 4);
+        HASTE_AX(1, 8);
+        HASTE_AX(1, 16);
+        HASTE_AX(2, 2);
+        HASTE_AX(2, 4);
+        HASTE_AX(2, 8);
+        HASTE_AX(4, 1);
+        HASTE_AX(4, 2);
+        HASTE_AX(4, 4);
+        HASTE_AX(8, 1);
+        HASTE_AX(8, 2);
+    }
+#undef HASTE_AX
+    return hipErrorInvalidValue;
+}
+
+inline bool ax_wide(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// one launch of the forward for NC feature chunks
+template <int NC>
+struct FaRun {
+    const haste::TailArgs &a;
+    const FaGeom &g;
+    const void *X;
+    const int32_t *idx;
+    const void *W;
+    const float *bias;
+    void *Y;
+    const int32_t *spos;
+    int P;
+    hipStream_t s;
+
+    template <int PK, int NI, int READ>
+    hipError_t go() const {
+        auto kern = k_fwd_any<NC, PK, NI, READ>;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           fa_lds(16 * NC));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(g.nseg * g.nbt)), dim3(kAxThreads), fa_lds(16 * NC), s, (const bf16_t *)X, idx,
+                           (const bf16_t *)W, bias, (bf16_t *)Y, (int)a.B, (int)a.F_s, a.L, (int)a.G, div_mul(a.G), (int)a.F_in,
+                           g.nbt, g.lps, spos, P);
+        return hipGetLastError();
+    }
+    hipError_t run() const { return ax_pick(a, g.pk, g.ni, ax_wide(Y), *this); }
+};
+
 // one launch of the kernel for MT row tiles and NFT feature tiles
 template <int MT, int NFT>
 struct AxRun {
@@ -385,31 +747,7 @@ struct AxRun {
                            (int)a.F_in, g.nbt, g.nsplit, g.lps);
         return hipGetLastError();
     }
-    template <int PK, int NI>
-    hipError_t read() const {
-        if (a.F_in % 2 == 0) {
-            if (a.L % 8 == 0 && (reinterpret_cast<uintptr_t>(dY) & 15) == 0) return go<PK, NI, kRead16>();
-            if constexpr (PK < 8)
-                if (a.L % 2 == 0) return go<PK, NI, kRead4>();
-        }
-        return go<PK, NI, kRead2>();
-    }
-    hipError_t run() const {
-        switch (g.pk * 100 + g.ni) {
-            case 104: return read<1, 4>();
-            case 108: return read<1, 8>();
-            case 116: return read<1, 16>();
-            case 202: return read<2, 2>();
-            case 204: return read<2, 4>();
-            case 208: return read<2, 8>();
-            case 401: return read<4, 1>();
-            case 402: return read<4, 2>();
-            case 404: return read<4, 4>();
-            case 801: return read<8, 1>();
-            case 802: return read<8, 2>();
-        }
-        return hipErrorInvalidValue;
-    }
+    hipError_t run() const { return ax_pick(a, g.pk, g.ni, ax_wide(dY), *this); }
 };
 
 }  // namespace

@@ -339,7 +339,8 @@ __device__ __forceinline__ f32x4_t mfma16x16x32(const bf16x8_t &a, const bf16x8_
 
 // --------------------------------------------------------------------------------------------
 // Backward-weight, slab-staged.  A workgroup of 8 waves takes 16 consecutive units (a contiguous
-// span of at most 512 labels, two units per wave) and sweeps the batch in 32-row slabs.  Per slab
+// span of at most 512 labels, two units per wave; 8 where the supports have more than 128 slots, whose
+// accumulators fill the registers) and sweeps the batch in 32-row slabs.  Per slab
 // it stages in LDS, cooperatively and with whole-line loads, the X^T block of all F_s features
 // (contiguous in Xb, 64 bytes per feature) and the span's dY rows (up to 1 KB per row); each wave
 // then gathers its units' support rows from the staged block, one 16-byte LDS read per slot tile,
@@ -350,27 +351,36 @@ __device__ __forceinline__ f32x4_t mfma16x16x32(const bf16x8_t &a, const bf16x8_
 //   B operand (rows x labels) = dY, two ds_read_b64_tr_b16 (4 rows each) per 16-label tile;
 //   result lane (label l16, q) holds slots 4q .. 4q+3 of one label: a 16-byte store into dW.
 // dbias comes from the same B operands against an all-ones A operand.
+// F_IN is the number of slots the tiles hold; supports of F_in < F_IN slots repeat their last one, and
+// the products of the repeats are not stored.  (131K labels, G = 32, 256 slots, 256 rows: 3.0 ms on the
+// vector ALUs, 54 us here.)
 // --------------------------------------------------------------------------------------------
 constexpr int kBw2Waves = 8;
-constexpr int kBw2Units = 2 * kBw2Waves;        // units per workgroup (two per wave)
+__host__ __device__ constexpr int bw2_upw(int f_in) { return f_in > 128 ? 1 : 2; }   // units per wave
+__host__ __device__ constexpr int bw2_units(int f_in) { return bw2_upw(f_in) * kBw2Waves; }
 constexpr int kBw2XRow = 80;                    // bytes per staged X^T feature row: 32 rows + 8 pad
 constexpr int kBw2YRow = 1056;                  // bytes per staged dY row: 512 labels + 16 pad
 constexpr int kBw2MaxXLoads = kMaxFs * 4 / (kBw2Waves * 64);   // 16-byte X^T loads per thread and slab
 
-// the staged slabs, or at the end the per-wave dW staging ([32 labels][F_in + 4] fp32 per wave)
+// labels whose dW a wave stages at a time
+__host__ __device__ constexpr int bw2_out_labels(int f_in) { return f_in > 128 ? 16 : 32; }
+
+// the staged slabs, or at the end the per-wave dW staging ([labels][F_in + 4] fp32 per wave)
 static size_t bw2_lds(int F_s, int F_in) {
     const size_t slabs = (size_t)haste::round_up((int64_t)F_s * kBw2XRow, 16) + 32 * kBw2YRow;
-    const size_t out = (size_t)kBw2Waves * 32 * (F_in + 4) * 4;
+    const size_t out = (size_t)kBw2Waves * bw2_out_labels(F_in) * (F_in + 4) * 4;
     return slabs > out ? slabs : out;
 }
 
-template <int F_IN>
+// HALVES: units that do not all start at even labels of dY, read 2 bytes at a time.
+template <int F_IN, bool HALVES>
 __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, const int32_t *__restrict__ idx,
                                                 const bf16_t *__restrict__ dY, float *__restrict__ dW,
                                                 float *__restrict__ dbias, int beta, int B, int Bp, int F_s,
-                                                int64_t L, int G, int64_t K) {
+                                                int64_t L, int G, int64_t K, int F_in) {
     extern __shared__ __align__(16) char bw2s[];
     constexpr int NST = F_IN / 16;              // 16-slot M-tiles
+    constexpr int UPW = bw2_upw(F_IN), UNITS = bw2_units(F_IN);
     char *xs = bw2s;
     char *ys = bw2s + ((F_s * kBw2XRow + 15) & ~15);
     const int tid = threadIdx.x;
@@ -378,7 +388,7 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
     const int l16 = lane & 15, q = lane >> 4;
     const int ntn = (G + 31) >> 5;
     const int64_t nunits = K * ntn;
-    const int64_t u0 = (int64_t)blockIdx.x * kBw2Units;
+    const int64_t u0 = (int64_t)blockIdx.x * UNITS;
     auto lab_of = [&](int64_t v) {
         const int64_t k = v / ntn;
         return k * G + 32 * (int)(v - k * ntn);
@@ -387,26 +397,33 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
         const int t = (int)(v % ntn);
         return G - 32 * t < 32 ? G - 32 * t : 32;
     };
-    const int64_t ul = u0 + kBw2Units - 1 < nunits ? u0 + kBw2Units - 1 : nunits - 1;
+    const int64_t ul = u0 + UNITS - 1 < nunits ? u0 + UNITS - 1 : nunits - 1;
     const int64_t lab0 = lab_of(u0);
     const int span = (int)(lab_of(ul) + nlab_of(ul) - lab0);   // at most 512 labels
 
     // this wave's units (a unit past the end repeats the last one and is never stored)
-    int64_t vu[2];
-    int off[2], nl[2];
-    int f[2][NST];
+    int64_t vu[UPW];
+    int off[UPW], nl[UPW];
+    int f[UPW][NST];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int64_t v = u0 + 2 * wave + j;
+    for (int j = 0; j < UPW; ++j) {
+        const int64_t v = u0 + UPW * wave + j;
         vu[j] = v < nunits ? v : nunits - 1;
-        off[j] = (int)(lab_of(vu[j]) - lab0);
+        off[j] = 32 * (int)(vu[j] - u0);
         nl[j] = v < nunits ? nlab_of(vu[j]) : 0;
         const int64_t k = vu[j] / ntn;
 #pragma unroll
-        for (int st = 0; st < NST; ++st) f[j][st] = idx[k * F_IN + 16 * st + l16];
+        for (int st = 0; st < NST; ++st) f[j][st] = idx[k * F_in + (16 * st + l16 < F_in ? 16 * st + l16 : F_in - 1)];
     }
 
-    // cooperative slab loads: X^T block (4 F_s chunks of 16 bytes) and dY (32 rows x 64 chunks)
+    // cooperative slab loads: X^T block (4 F_s chunks of 16 bytes) and dY (32 rows x 64 chunks: unit
+    // part / 4 of the span takes columns 32 (part / 4) .., whatever its labels, so that the operand
+    // reads are aligned); this thread's chunk of every row: labels yl .. yl + yn - 1 of the span
+    const int part = tid & 63;
+    const int64_t yu = u0 + (part >> 2);
+    const bool yok = part >> 2 < UNITS && yu < nunits;
+    const int yl = yok ? (int)(lab_of(yu) - lab0) + 8 * (part & 3) : 0;
+    const int yn = yok ? nlab_of(yu) - 8 * (part & 3) : 0;
     const int nxc = 4 * F_s;
     uint4 xr[kBw2MaxXLoads], yr[4];
     auto load = [&](int blk) {
@@ -419,9 +436,16 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
         const Buf db(dY + (int64_t)b0 * L + lab0, (uint32_t)(rows > 0 ? ((int64_t)(rows - 1) * L + span) * 2 : 0));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int c = tid + 512 * i, row = c >> 6, part = c & 63;
-            const bool ok = row < rows && 8 * part < span;
-            yr[i] = db.ld16(ok ? (uint32_t)(((int64_t)row * L + 8 * part) * 2) : kOob);
+            const int row = (tid >> 6) + 8 * i;
+            const uint32_t o = (uint32_t)(((int64_t)row * L + yl) * 2);
+            if constexpr (!HALVES) {
+                yr[i] = db.ld16(row < rows && yn > 0 ? o : kOob);
+            } else {
+                uint32_t h[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h[e] = db.ld2(row < rows && yn > e ? o + 2 * e : kOob);
+                yr[i] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+            }
         }
     };
     auto store = [&]() {
@@ -437,9 +461,9 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
         }
     };
 
-    f32x4_t acc[2][NST][2], db[2][2];
+    f32x4_t acc[UPW][NST][2], db[UPW][2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < UPW; ++j) {
 #pragma unroll
         for (int lt = 0; lt < 2; ++lt) {
             db[j][lt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -459,7 +483,7 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
         __syncthreads();
         if (blk + 1 < nblk) load(blk + 1);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < UPW; ++j) {
             uint4 yv[2];
 #pragma unroll
             for (int lt = 0; lt < 2; ++lt) {
@@ -482,33 +506,49 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
         }
     }
 
-    // dW: a unit's block [32 labels][F_IN] fp32 is contiguous in dW, so each wave stages its
-    // unit's products (lane (label 16 lt + l16, q) holds slots 16 st + 4q .. +3) in its own LDS
-    // region and writes the block back as whole 1 KB runs (streaming stores; labels past the unit
-    // are not written).  dbias from the q = 0 lanes.
+    // dW: a unit's block [32 labels][F_in] fp32 is contiguous in dW, so each wave stages its unit's
+    // products (lane (label 16 lt + l16, q) holds slots 16 st + 4q .. +3) in its own LDS region (half a
+    // unit at a time where 256 slots would not fit) and writes the block back as whole runs (streaming
+    // stores; labels past the unit are not written).  dbias from the q = 0 lanes.
     __syncthreads();   // every wave is done with the staged slabs
     constexpr int OS = F_IN + 4;                       // staged row stride (floats)
-    float *ostg = reinterpret_cast<float *>(bw2s) + wave * 32 * OS;
+    constexpr int LTB = bw2_out_labels(F_IN) / 16;     // label tiles staged at a time
+    float *ostg = reinterpret_cast<float *>(bw2s) + wave * (16 * LTB) * OS;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < UPW; ++j) {
         const int64_t lb = lab_of(vu[j]);
 #pragma unroll
-        for (int lt = 0; lt < 2; ++lt)
+        for (int t0 = 0; t0 < 2; t0 += LTB) {
 #pragma unroll
-            for (int st = 0; st < NST; ++st)
-                *reinterpret_cast<float4 *>(ostg + (16 * lt + l16) * OS + 16 * st + 4 * q) =
-                    make_float4(acc[j][st][lt][0], acc[j][st][lt][1], acc[j][st][lt][2], acc[j][st][lt][3]);
-        const Buf ob(dW + lb * F_IN, (uint32_t)(nl[j] * F_IN * 4));   // this unit's labels only
+            for (int lt = 0; lt < LTB; ++lt)
 #pragma unroll
-        for (int i = 0; i < F_IN / 8; ++i) {
-            const int e = 64 * i + lane;                   // float4 e of the block
-            const int r = e / (F_IN / 4), c = (e % (F_IN / 4)) * 4;
-            float4 v = *reinterpret_cast<const float4 *>(ostg + r * OS + c);
-            if (beta) {
-                const float4 o = __builtin_bit_cast(float4, ob.ld16((uint32_t)(e * 16)));
-                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+                for (int st = 0; st < NST; ++st)
+                    *reinterpret_cast<float4 *>(ostg + (16 * lt + l16) * OS + 16 * st + 4 * q) =
+                        make_float4(acc[j][st][t0 + lt][0], acc[j][st][t0 + lt][1], acc[j][st][t0 + lt][2],
+                                    acc[j][st][t0 + lt][3]);
+            const int64_t l0 = lb + 16 * t0;
+            const int nv = nl[j] - 16 * t0 < 16 * LTB ? nl[j] - 16 * t0 : 16 * LTB;   // the block's labels
+            if (F_in == F_IN) {
+                const Buf ob(dW + l0 * F_IN, (uint32_t)(nv > 0 ? nv * F_IN * 4 : 0));
+#pragma unroll
+                for (int i = 0; i < LTB * F_IN / 16; ++i) {
+                    const int e = 64 * i + lane;                   // float4 e of the block
+                    const int r = e / (F_IN / 4), c = (e % (F_IN / 4)) * 4;
+                    float4 v = *reinterpret_cast<const float4 *>(ostg + r * OS + c);
+                    if (beta) {
+                        const float4 o = __builtin_bit_cast(float4, ob.ld16((uint32_t)(e * 16)));
+                        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+                    }
+                    ob.st16<kStreaming>(__builtin_bit_cast(uint4, v), (uint32_t)(e * 16));
+                }
+            } else {
+                float *out = dW + l0 * F_in;
+                for (int r = 0; r < nv; ++r)
+                    for (int c = lane; c < F_in; c += 64) {
+                        const float v = ostg[r * OS + c];
+                        out[r * F_in + c] = beta ? out[r * F_in + c] + v : v;
+                    }
             }
-            ob.st16<kStreaming>(__builtin_bit_cast(uint4, v), (uint32_t)(e * 16));
         }
         if (dbias && q == 0) {
 #pragma unroll
@@ -1450,6 +1490,13 @@ bool bwd_w_mfma_supported(const TailArgs &a) { return fwd_mfma_supported(a); }
 // X^T staged in 32-row batch blocks (the batch padded to whole blocks)
 size_t bwd_w_mfma_ws(const TailArgs &a) { return (size_t)a.F_s * (size_t)round_up(a.B, 32) * 2 + 256; }
 
+// any group size and support width up to 256 slots; 32 rows of dY within the 31-bit buffer range, and
+// an X^T copy that haste_fwd_bce_static's array holds too (so that both calls take the same kernel)
+bool bwd_w_any_supported(const TailArgs &a) {
+    return a.dtype == HASTE_DTYPE_BF16 && a.F_in <= 256 && a.F_s <= kMaxFs && a.L * 64 + 1024 < ((int64_t)1 << 31) &&
+           bwd_w_mfma_ws(a) <= haste_fwd_bce_static_max_bytes() && bw2_lds((int)a.F_s, 256) <= kLdsBudget;
+}
+
 // X^T in 32-row batch blocks, [B/32][F_s][32] (rows past B zero), into the workspace
 hipError_t transpose_x(const TailArgs &a, const void *X, void *ws, hipStream_t s) {
     const int Bp = (int)round_up(a.B, 32);
@@ -1469,19 +1516,22 @@ hipError_t bwd_w_mfma(const TailArgs &a, const void *X, const int32_t *idx, cons
     const int64_t K = a.L / a.G;
     const int64_t units = K * cdiv(a.G, 32);
     {
-        const size_t lds = bw2_lds((int)a.F_s, (int)a.F_in);
-        const dim3 grid2((unsigned)cdiv(units, kBw2Units));
+        const int fin = (int)(a.F_in <= 32 ? 32 : a.F_in <= 64 ? 64 : a.F_in <= 128 ? 128 : 256);   // slots of the tiles
+        const size_t lds = bw2_lds((int)a.F_s, fin);
+        const dim3 grid2((unsigned)cdiv(units, bw2_units(fin)));
+        const bool halves = a.L % 2 != 0 || a.G % 2 != 0;
         auto launch2 = [&](auto kern) {
             hipError_t e2 = allow_lds(kern, lds);
             if (e2 != hipSuccess) return e2;
             hipLaunchKernelGGL(kern, grid2, dim3(kBw2Waves * 64), lds, s, Xb, idx, (const bf16_t *)dY, dW, dbias, beta,
-                               (int)a.B, Bp, (int)a.F_s, a.L, (int)a.G, K);
+                               (int)a.B, Bp, (int)a.F_s, a.L, (int)a.G, K, (int)a.F_in);
             return hipGetLastError();
         };
-        switch (a.F_in) {
-            case 32: return launch2(k_bwd_w2<32>);
-            case 64: return launch2(k_bwd_w2<64>);
-            case 128: return launch2(k_bwd_w2<128>);
+        switch (fin) {
+            case 32: return halves ? launch2(k_bwd_w2<32, true>) : launch2(k_bwd_w2<32, false>);
+            case 64: return halves ? launch2(k_bwd_w2<64, true>) : launch2(k_bwd_w2<64, false>);
+            case 128: return halves ? launch2(k_bwd_w2<128, true>) : launch2(k_bwd_w2<128, false>);
+            case 256: return halves ? launch2(k_bwd_w2<256, true>) : launch2(k_bwd_w2<256, false>);
             default: break;
         }
     }

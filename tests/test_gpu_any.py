@@ -51,3 +51,89 @@ def test_bwd_x(shape, beta):
     hs.haste_bwd_x(desc, idx, W, dY, dX, beta, ws)
     ref = dY.double() @ Wd + beta
     assert rel_err(dX.cpu(), ref.cpu()) < SUM_TOL
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("beta", [0, 1])
+def test_bwd_w(shape, beta):
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    say("bwd_w", shape, beta)
+    X, idx, W, dY, sup, Wd = layer(shape, 1)
+    desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_BF16)
+    need = hs.haste_workspace_bytes(desc, hs.HASTE_OP_BWD_W)
+    ws = hs.workspace(need)
+    if ws is not None:
+        ws.fill_(0xff)
+    dW, db = torch.ones((L, F_in), device="cuda"), torch.ones(L, device="cuda")
+    hs.haste_bwd_w(desc, X, idx, dY, dW, db, beta, ws)
+    ref = (dY.double().t() @ X.double()).gather(1, sup) + beta
+    assert rel_err(dW.cpu(), ref.cpu()) < SUM_TOL
+    assert rel_err(db.cpu(), (dY.double().sum(0) + beta).cpu()) < SUM_TOL
+
+
+def ref_positives(pos, L):
+    import torch
+    T = torch.zeros((pos.shape[0], L), dtype=torch.float64, device="cuda")
+    rows = torch.arange(pos.shape[0], device="cuda")[:, None].expand_as(pos)
+    ok = (pos >= 0) & (pos < L)
+    T[rows[ok], pos[ok].long()] = 1.0
+    return T
+
+
+def close_bf16(a, ref, scale):
+    """Within one rounding to bf16 of the 64-bit value (half an ulp, 2^-8 of it, and as much again where
+    the fp32 sum lies at the tie), beside the fp32 sum's own error."""
+    return bool(((a.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + SUM_TOL * scale).all())
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("bias", [False, True])
+def test_fwd(shape, bias):
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    say("fwd", shape, bias)
+    X, idx, W, _, sup, Wd = layer(shape, 2)
+    b = torch.randn(L, device="cuda") if bias else None
+    desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_BF16)
+    Y = torch.full((B, L), 7.0, dtype=torch.bfloat16, device="cuda")
+    hs.haste_fwd(desc, X, idx, W, b, Y)
+    ref = X.double() @ Wd.t() + (b.double() if bias else 0.0)
+    assert close_bf16(Y, ref, float(ref.abs().max()))
+    # the loss gradient: that of the rounded logits, bit for bit, and backward-weight on it
+    pos = torch.randint(-2, L + 2, (B, 9), dtype=torch.int32, device="cuda")
+    dY, dY2, dW = torch.empty_like(Y), torch.empty_like(Y), torch.empty((L, F_in), device="cuda")
+    ws = hs.workspace(hs.haste_workspace_bytes(desc, hs.HASTE_OP_FWD_BCE))
+    if ws is not None:
+        ws.fill_(0xff)
+    hs.haste_fwd_bce(desc, X, idx, W, b, pos, dY, dW, None, 0, ws)
+    T = ref_positives(pos, L)
+    if G % 16 or F_in not in (32, 64, 128):       # the fused kernel's gradient is that of the fp32 logits
+        hs.haste_bce_grad(B, L, synth.DT_BF16, Y, pos, dY2)
+        assert torch.equal(dY.view(torch.int16), dY2.view(torch.int16))
+    assert rel_err(dY.cpu().float(), (torch.sigmoid(ref) - T).cpu()) < 2e-2
+    refw = (dY.double().t() @ X.double()).gather(1, sup)
+    assert rel_err(dW.cpu(), refw.cpu()) < SUM_TOL
+
+
+@pytest.mark.parametrize("shape", [(33, 768, 1027, 1, 63), (77, 500, 24 * 131, 24, 48), (130, 768, 1050, 35, 181)])
+def test_fwd_not_finite(shape):
+    """An infinity or a NaN in X reaches the labels whose support holds its feature, and no others."""
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    say("fwd_not_finite", shape)
+    X, idx, W, _, sup, Wd = layer(shape, 3)
+    X[B - 1, 5] = float("inf")
+    X[B // 2, F_s - 1] = float("nan")
+    desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_BF16)
+    Y = torch.empty((B, L), dtype=torch.bfloat16, device="cuda")
+    hs.haste_fwd(desc, X, idx, W, None, Y)
+    touched = torch.zeros((B, L), dtype=torch.bool, device="cuda")
+    touched[B - 1] |= (sup == 5).any(1)
+    touched[B // 2] |= (sup == F_s - 1).any(1)
+    assert torch.equal(~torch.isfinite(Y), touched)
+    ref = torch.where(torch.isfinite(X), X, 0).double() @ Wd.t()
+    assert close_bf16(torch.where(touched, 0, Y.double()), torch.where(touched, 0, ref), float(ref.abs().max()))
