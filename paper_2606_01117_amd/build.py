@@ -14,7 +14,8 @@ OBJDIR = os.path.join(ROOT, "_build", "haste")
 LIB = os.path.join(PKG, "libhaste.so")
 
 SOURCES = ["abi.hip", "tail_mfma.hip", "tail_valu.hip", "head.hip", "util.hip", "rewire.hip", "group.hip", "static_ws.hip", "tail_sg.hip", "tail_dense.hip", "tail_any.hip",
-           "tail_any_4_8.hip", "tail_any_2_12.hip", "tail_any_fwd_48.hip", "tail_any_fwd_32.hip"]
+           "tail_any_4_8.hip", "tail_any_2_12.hip", "tail_any_fwd_48.hip", "tail_any_fwd_32.hip",
+           "tail_f32.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

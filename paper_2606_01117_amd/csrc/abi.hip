@@ -98,10 +98,11 @@ hipError_t fwd_run(const haste::TailArgs &a, const void *X, const int32_t *idx, 
     if (haste::fwd_dn_supported(a)) return haste::fwd_dn(a, X, idx, W, bias, Y, s);
     if (haste::fwd_sg_supported(a)) return haste::fwd_sg(a, X, idx, W, bias, Y, s);
     if (haste::fwd_mfma_supported(a)) return haste::fwd_mfma(a, X, idx, W, bias, Y, s);
+    if (haste::fwd_f32_preferred(a)) return haste::fwd_f32(a, X, idx, W, bias, Y, s);
     return haste::fwd_valu(a, X, idx, W, bias, Y, s);
 }
 
-// backward-feature beside the any-group kernel: small-group kernels, else the general matrix-core
+// backward-feature beside the any-group and fp32 kernels: small-group kernels, else the general matrix-core
 // kernel, else the VALU kernel
 size_t bwd_x_other_ws(const haste::TailArgs &a) {
     if (haste::bwd_x_dn_supported(a)) return haste::bwd_x_dn_ws(a);
@@ -110,7 +111,9 @@ size_t bwd_x_other_ws(const haste::TailArgs &a) {
 }
 
 size_t bwd_x_ws(const haste::TailArgs &a) {
-    return haste::bwd_x_any_preferred(a) ? haste::bwd_x_any_ws(a) : bwd_x_other_ws(a);
+    return haste::bwd_x_any_preferred(a)   ? haste::bwd_x_any_ws(a)
+           : haste::bwd_x_f32_preferred(a) ? haste::bwd_x_f32_ws(a)
+                                           : bwd_x_other_ws(a);
 }
 
 // the backward-weight kernel for a layer: small groups (G = 1, 2, 4, 8) and larger ones on the matrix
@@ -136,6 +139,7 @@ hipError_t bwd_w_run(const haste::TailArgs &a, const void *X, const int32_t *idx
     if (haste::bwd_w_mfma_supported(a)) return haste::bwd_w_mfma(a, X, idx, dY, dW, dbias, beta, ws, s);
     if (bwd_w_takes_xt(a) && ws && aligned16(ws) && ws_bytes >= haste::bwd_w_mfma_ws(a))
         return haste::bwd_w_mfma(a, X, idx, dY, dW, dbias, beta, ws, s);
+    if (haste::bwd_w_f32_preferred(a)) return haste::bwd_w_f32(a, X, idx, dY, dW, dbias, beta, s);
     return haste::bwd_w_valu(a, X, idx, dY, dW, dbias, beta, s);
 }
 
@@ -271,11 +275,13 @@ int haste_bwd_x(const haste_desc_t *d, const int32_t *idx, const void *W, const 
         return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
     // a workspace of less than the queried size that another kernel can do with is still taken
     const bool any = haste::bwd_x_any_preferred(a) && ws_bytes >= haste::bwd_x_any_ws(a);
-    const size_t need = any ? haste::bwd_x_any_ws(a) : bwd_x_other_ws(a);
+    const bool f32 = haste::bwd_x_f32_preferred(a) && ws_bytes >= haste::bwd_x_f32_ws(a);
+    const size_t need = any || f32 ? bwd_x_ws(a) : bwd_x_other_ws(a);
     if (!ws || ws_bytes < need)
         return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", bwd_x_ws(a), ws ? ws_bytes : 0);
     TRY(need_ptr(ws, "ws"));
     if (any) return hip_status(haste::bwd_x_any(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
+    if (f32) return hip_status(haste::bwd_x_f32(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_dn_supported(a)) return hip_status(haste::bwd_x_dn(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_sg_supported(a)) return hip_status(haste::bwd_x_sg(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_mfma_supported(a)) return hip_status(haste::bwd_x_mfma(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");

@@ -339,6 +339,18 @@ hipError_t sort_positives(int64_t B, int64_t N, const int32_t *pos, int P, int32
 hipError_t bce_grad(int64_t B, int64_t N, int32_t dtype, const void *Y, const int32_t *pos, int P, void *dY,
                     hipStream_t s);
 
+// tail, fp32 on the matrix cores; preferred: where faster than the vector ALUs
+bool fwd_f32_preferred(const TailArgs &a);
+hipError_t fwd_f32(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
+                   hipStream_t s);
+bool bwd_w_f32_preferred(const TailArgs &a);
+hipError_t bwd_w_f32(const TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW, float *dbias,
+                     int beta, hipStream_t s);
+bool bwd_x_f32_preferred(const TailArgs &a);
+size_t bwd_x_f32_ws(const TailArgs &a);
+hipError_t bwd_x_f32(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
+                     hipStream_t s);
+
 // tail, VALU (fp32 and bf16, any G including per-label fixed fan-in)
 bool valu_supported(const TailArgs &a);
 hipError_t fwd_valu(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias,

@@ -1,9 +1,9 @@
 // Group-shared fixed fan-in tail on the vector ALUs (fp32 FMA), for any G including G = 1.
 //
-// Used for fp32 layers (the paper's logit definition, Section 3.1, evaluated with true fp32
-// products: gfx950 has no reduced-precision fp32 matrix path to fall into) and as the standard
-// per-label fixed fan-in comparator (G = 1, Section 3.1 / Fig. 2(c)): every label gathers its own
-// F_in features, so there is no shared tile and the work is thin dot products.
+// Used for fp32 layers of one or two labels per group (standard per-label fixed fan-in, Section 3.1 /
+// Fig. 2(c): every label gathers its own F_in features, so there is no shared tile and the work is thin
+// dot products) and for the layers that no matrix-core kernel takes (more than 256 slots, wide inputs
+// with odd shapes, very large batches).
 //
 // A batch tile of TB rows of X is kept transposed in LDS as fp32 (xs[f][b], row stride TB+4
 // floats so 16-byte reads stay aligned).  One thread owns one label.

@@ -8,7 +8,8 @@ __global__ void k_fill(float *__restrict__ p, int64_t n, float v) {
         p[i] = v;
 }
 
-// dX[b, f] = beta dX[b, f] + sum_{k < S} part[k][f][b], summed in ascending k.  A workgroup takes
+// dX[b, f] = beta dX[b, f] + sum_{k < S} part[k][f][b], in a fixed order: eight partials in pairs, the
+// eights in ascending k.  A workgroup takes
 // 8 features x 128 rows: each thread reads 4 consecutive rows (16 bytes, 512 contiguous bytes per
 // feature and wave) of every partial, with the loads of 8 partials in flight, and the tile is
 // transposed through LDS so that dX is written 16 bytes per thread.
@@ -27,13 +28,20 @@ __global__ __launch_bounds__(256) void k_reduce_fmajor(const float *__restrict__
             float4 v[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(k + j) * ks];
+            // the eight in pairs, then onto the running sum, whose roundings are the largest
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                acc.x += v[j].x;
-                acc.y += v[j].y;
-                acc.z += v[j].z;
-                acc.w += v[j].w;
-            }
+            for (int d = 1; d < 8; d *= 2)
+#pragma unroll
+                for (int j = 0; j < 8; j += 2 * d) {
+                    v[j].x += v[j + d].x;
+                    v[j].y += v[j + d].y;
+                    v[j].z += v[j + d].z;
+                    v[j].w += v[j + d].w;
+                }
+            acc.x += v[0].x;
+            acc.y += v[0].y;
+            acc.z += v[0].z;
+            acc.w += v[0].w;
         }
         for (; k < S; ++k) {
             const float4 v = p[(int64_t)k * ks];
@@ -154,33 +162,54 @@ unsigned grid_for(int64_t n) {
 
 // BCE gradient of stored logits (Section 3.3 objective): dY[b, n] = sigmoid(Y[b, n]) - T[b, n], with
 // T[b, n] = 1 where n occurs in pos[b, 0..P-1].  A workgroup takes 2048 columns of one row and a
-// thread 8 consecutive columns; the row's positives are workgroup-uniform reads.  Y and dY may be
-// the same buffer (each element is read before it is written, by the same thread).
+// thread 8 of them; the row's positives are workgroup-uniform reads.  Y and dY may be the same buffer
+// (each element is read before it is written, by the same thread).
+// Which 8 columns a thread takes: 8 consecutive bf16 (16 bytes), two runs of 4 consecutive fp32 (16 bytes
+// each, 1024 columns apart), or, where rows are not whole 16-byte groups, 8 single columns 256 apart, so
+// that every access of a wave is one contiguous run.  (Eight consecutive columns one by one touched each
+// line eight times: 131K fp32 columns, 128 rows: 73 us, 21 so.)
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_bce_grad(const T *Y, const int32_t *__restrict__ pos, int P, T *dY,
                                                   int64_t N, int64_t nchunk) {
+    constexpr int RUN = VEC ? 16 / (int)sizeof(T) : 1;   // consecutive columns
     const int64_t b = blockIdx.x / nchunk;
-    const int64_t c0 = (blockIdx.x - b * nchunk) * 2048 + 8 * (int64_t)threadIdx.x;
-    if (c0 >= N) return;
-    uint32_t t = 0;
+    const int64_t c0 = (blockIdx.x - b * nchunk) * 2048;
+    const int tid = threadIdx.x;
+    uint32_t t = 0;                               // bit RUN i + e: column c0 + 256 RUN i + RUN tid + e
     for (int p = 0; p < P; ++p) {
         const int64_t d = (int64_t)pos[b * P + p] - c0;
-        if (d >= 0 && d < 8) t |= 1u << d;
+        if (d < 0 || d >= 2048) continue;         // workgroup-uniform
+        const int i = (int)d / (256 * RUN), e = (int)d % (256 * RUN) - RUN * tid;
+        if (e >= 0 && e < RUN) t |= 1u << (RUN * i + e);
     }
-    const T *y = Y + b * N + c0;
-    T *o = dY + b * N + c0;
-    if constexpr (VEC && sizeof(T) == 2) {   // bf16, whole 16-byte groups
-        const uint4 v = *reinterpret_cast<const uint4 *>(y);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        uint32_t r[4];
+    const T *y = Y + b * N;
+    T *o = dY + b * N;
+    if constexpr (VEC) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            r[i] = pack_bf16(bce_grad_f32(__uint_as_float(w[i] << 16), (t >> (2 * i)) & 1),
-                             bce_grad_f32(__uint_as_float(w[i] & 0xffff0000u), (t >> (2 * i + 1)) & 1));
-        *reinterpret_cast<uint4 *>(o) = make_uint4(r[0], r[1], r[2], r[3]);
+        for (int i = 0; i < 8 / RUN; ++i) {
+            const int64_t c = c0 + 256 * RUN * i + RUN * tid;
+            if (c >= N) continue;
+            const uint4 v = *reinterpret_cast<const uint4 *>(y + c);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            uint32_t r[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                r[k] = sizeof(T) == 2 ? bce_pair(w[k], t >> (2 * k))
+                                      : __float_as_uint(bce_grad_f32(__uint_as_float(w[k]), (t >> (RUN * i + k)) & 1));
+            *reinterpret_cast<uint4 *>(o + c) = make_uint4(r[0], r[1], r[2], r[3]);
+        }
     } else {
-        const int n = N - c0 < 8 ? (int)(N - c0) : 8;
-        for (int i = 0; i < n; ++i) store_out(o, i, bce_grad_f32(load_f32(y, i), (t >> i) & 1));
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t c = c0 + 256 * i + tid;
+            v[i] = c < N ? load_f32(y, c) : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int64_t c = c0 + 256 * i + tid;
+            if (c < N) store_out(o, c, bce_grad_f32(v[i], (t >> i) & 1));
+        }
     }
 }
 
@@ -296,14 +325,18 @@ hipError_t bce_grad(int64_t B, int64_t N, int32_t dtype, const void *Y, const in
                     hipStream_t s) {
     const int64_t nchunk = cdiv(N, 2048);
     const dim3 grid((unsigned)(B * nchunk)), block(256);
-    const bool vec = (N % 8) == 0 && ((reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(dY)) & 15) == 0;
+    const bool vec = N % (dtype == HASTE_DTYPE_BF16 ? 8 : 4) == 0 &&
+                     ((reinterpret_cast<uintptr_t>(Y) | reinterpret_cast<uintptr_t>(dY)) & 15) == 0;
     if (dtype == HASTE_DTYPE_BF16) {
         if (vec)
             hipLaunchKernelGGL((k_bce_grad<bf16_t, true>), grid, block, 0, s, (const bf16_t *)Y, pos, P, (bf16_t *)dY, N, nchunk);
         else
             hipLaunchKernelGGL((k_bce_grad<bf16_t, false>), grid, block, 0, s, (const bf16_t *)Y, pos, P, (bf16_t *)dY, N, nchunk);
     } else {
-        hipLaunchKernelGGL((k_bce_grad<float, false>), grid, block, 0, s, (const float *)Y, pos, P, (float *)dY, N, nchunk);
+        if (vec)
+            hipLaunchKernelGGL((k_bce_grad<float, true>), grid, block, 0, s, (const float *)Y, pos, P, (float *)dY, N, nchunk);
+        else
+            hipLaunchKernelGGL((k_bce_grad<float, false>), grid, block, 0, s, (const float *)Y, pos, P, (float *)dY, N, nchunk);
     }
     return hipGetLastError();
 }

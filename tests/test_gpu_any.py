@@ -137,3 +137,72 @@ def test_fwd_not_finite(shape):
     assert torch.equal(~torch.isfinite(Y), touched)
     ref = torch.where(torch.isfinite(X), X, 0).double() @ Wd.t()
     assert close_bf16(torch.where(touched, 0, Y.double()), torch.where(touched, 0, ref), float(ref.abs().max()))
+
+
+# fp32: one unit, part of one, several per group; 64-slot chunks, part of one and four; F_s past 512 and
+# 768; aligned and odd labels and supports; batches of part of a row tile, and of several slabs
+SHAPES_F32 = [
+    (32, 256, 4096, 8, 32), (128, 768, 2048, 16, 64), (33, 768, 1027, 1, 63), (65, 513, 516, 4, 256), (77, 500, 24 * 131, 24, 48),
+    (130, 896, 35 * 30, 35, 181), (40, 640, 333, 3, 1), (300, 384, 2048, 64, 128), (1, 65, 1, 1, 2), (17, 905, 602, 14, 100),
+    (64, 768, 260, 260, 33), (16, 768, 16 * 300, 16, 65),
+]
+
+
+def layer_f32(shape, seed):
+    import torch
+    B, F_s, L, G, F_in = shape
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    r = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    idx = torch.rand((L // G, F_s), device="cuda", generator=gen).argsort(1)[:, :F_in].sort(1).values.int().contiguous()
+    sup = idx.long().repeat_interleave(G, 0)
+    return r(B, F_s), idx, r(L, F_in) / F_in ** 0.5, r(B, L), r(L), sup
+
+
+@pytest.mark.parametrize("shape", SHAPES_F32)
+@pytest.mark.parametrize("beta", [0, 1])
+def test_f32(shape, beta):
+    """fp32 sums of fp32 products: n terms, each product and partial sum rounded to 2^-24 of itself; random
+    signs keep the error within 3 sqrt(n) 2^-24 of a term's size, under 1e-5 of the largest entry."""
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    say("f32", shape, beta)
+    X, idx, W, dY, bias, sup = layer_f32(shape, 4)
+    desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_F32)
+    dense = torch.zeros((L, F_s), dtype=torch.float64, device="cuda").scatter_(1, sup, W.double())
+    Y = torch.empty((B, L), device="cuda")
+    for b in (None, bias):
+        hs.haste_fwd(desc, X, idx, W, b, Y)
+        assert rel_err(Y.cpu(), (X.double() @ dense.t() + (0 if b is None else b.double())).cpu()) < 1e-5
+    dW, db = torch.ones((L, F_in), device="cuda"), torch.ones(L, device="cuda")
+    hs.haste_bwd_w(desc, X, idx, dY, dW, db, beta, hs.workspace(hs.haste_workspace_bytes(desc, hs.HASTE_OP_BWD_W)))
+    assert rel_err(dW.cpu(), ((dY.double().t() @ X.double()).gather(1, sup) + beta).cpu()) < 1e-5
+    assert rel_err(db.cpu(), (dY.double().sum(0) + beta).cpu()) < 1e-5
+    ws = hs.workspace(hs.haste_workspace_bytes(desc, hs.HASTE_OP_BWD_X))
+    ws.fill_(0xff)
+    dX = torch.ones((B, F_s), device="cuda")
+    hs.haste_bwd_x(desc, idx, W, dY, dX, beta, ws)
+    assert rel_err(dX.cpu(), (dY.double() @ dense + beta).cpu()) < 1e-5
+
+
+def test_f32_not_finite():
+    """An infinity in X or dY reaches the outputs the definition names, and no others."""
+    import torch
+    import paper_2606_01117_amd as hs
+    shape = B, F_s, L, G, F_in = (33, 300, 24 * 40, 24, 50)
+    X, idx, W, dY, _, sup = layer_f32(shape, 5)
+    desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_F32)
+    Xi, Yi = X.clone(), dY.clone()
+    Xi[7, 11] = float("inf")
+    Yi[5, 100] = float("inf")
+    Y, dW, dX = torch.empty((B, L), device="cuda"), torch.empty((L, F_in), device="cuda"), torch.empty((B, F_s), device="cuda")
+    hs.haste_fwd(desc, Xi, idx, W, None, Y)
+    bad = torch.zeros((B, L), dtype=torch.bool, device="cuda")
+    bad[7] = (sup == 11).any(1)
+    assert torch.equal(~torch.isfinite(Y), bad)
+    hs.haste_bwd_w(desc, Xi, idx, dY, dW, None, 0, None)
+    assert torch.equal(~torch.isfinite(dW), sup == 11)
+    hs.haste_bwd_x(desc, idx, W, Yi, dX, 0, hs.workspace(hs.haste_workspace_bytes(desc, hs.HASTE_OP_BWD_X)))
+    bad = torch.zeros((B, F_s), dtype=torch.bool, device="cuda")
+    bad[5, sup[100]] = True
+    assert torch.equal(~torch.isfinite(dX), bad)
