@@ -44,6 +44,24 @@ __global__ void k_gl_shuffle(int32_t *__restrict__ a, int64_t N, int64_t C, uint
     }
 }
 
+// The same entries without the swaps' chain of memory accesses: before step i, position p holds p, or, if
+// the last earlier step k with partner p exists, what position k held before step k.  One workgroup; every
+// thread follows its entries' chains through the partners in LDS (C <= kGlShuffleMax).  C = 256: 129 us
+// swap by swap, 5 us.
+constexpr int kGlShuffleMax = 8192;
+__global__ __launch_bounds__(1024) void k_gl_draw(int32_t *__restrict__ a, int64_t N, int C, uint64_t seed) {
+    extern __shared__ int32_t partner[];          // [C]
+    for (int i = threadIdx.x; i < C; i += blockDim.x)
+        partner[i] = i + (int32_t)(splitmix64_at(seed, (uint64_t)i) % (uint64_t)(N - i));
+    __syncthreads();
+    for (int i = threadIdx.x; i < C; i += blockDim.x) {
+        int32_t p = partner[i];
+        for (int k = i - 1; k >= 0; --k)
+            if (partner[k] == p) p = k;           // from here, position k before step k
+        a[i] = p;
+    }
+}
+
 // Centre c is the direction of the int32 vector s_c (a label's embedding at the start, then the
 // sum of its members).  The assignment reads it as digit planes cp[p][c][D] (s_c = sum_p 256^p
 // cp[p][c]), the number of planes it needs cnp[c] (higher planes are zero), and its norm cn[c].
@@ -123,94 +141,131 @@ __global__ __launch_bounds__(kGlThreads) void k_gl_pick_centres(const int8_t *__
     gl_store_centre(sum, D, C, c, cs, cp, cn, cnp);
 }
 
-// cl[l] = argmax_c (E[l].s_c) / |s_c| (ties: the lower c).  A wave takes 16 labels, a workgroup of
-// 8 waves 128; centres pass through LDS 16 at a time, as many digit planes as the 16 need.
-// v_mfma_i32_16x16x64_i8, M = 16 labels, N = 16 centres, K = 64 dimensions: both operands hold,
-// per lane, 16 consecutive dimensions (16 q .. 16 q + 15 of the 64-chunk) of their row, so each
-// lane group contracts the same dimensions; result lane (centre l16, q) holds labels 4q .. 4q+3.
+// cl[l] = argmax_c (E[l].s_c) / |s_c| (ties: the lower c).  A wave takes 32 labels, a workgroup of
+// 8 waves 256; centres pass through LDS 16 at a time, as many digit planes as the 16 need, and the next
+// 16 wait in registers.  v_mfma_i32_16x16x64_i8, M = 16 labels, N = 16 centres, K = 64 dimensions: both
+// operands hold, per lane, 16 consecutive dimensions (16 q .. 16 q + 15 of the 64-chunk) of their row, so
+// each lane group contracts the same dimensions; result lane (centre l16, q) holds labels 4q .. 4q+3.
+// Rows of the tile are 16 bytes longer than whole 64-chunks, so that the 16 lanes of a read meet 64
+// different banks (1 KiB rows put them all on one).
+// The quotient is compared through dot * (1 / |s_c|), which lies within 2^-51 of it: only scores closer
+// than 2^-48 of the best are divided.  131K labels, 256 centres, 768 dimensions, three planes: 530 us with
+// 16 labels a wave, 1 KiB rows and a division per score, 110 us.
+template <int NK>
 __global__ __launch_bounds__(64 * kGlWaves) void k_gl_assign(const int8_t *__restrict__ E, int64_t N, int D,
                                                              const int8_t *__restrict__ cp,
                                                              const double *__restrict__ cn,
                                                              const int32_t *__restrict__ cnp, int64_t C,
                                                              int32_t *__restrict__ cl) {
-    __shared__ __align__(16) int8_t tile[kGlPlanes][16 * kGlMaxD];
+    constexpr int RS = 64 * NK + 16;              // bytes of a tile row
+    constexpr int SL = kGlPlanes * 16 * 4 * NK / (64 * kGlWaves) > 0 ? kGlPlanes * 16 * 4 * NK / (64 * kGlWaves) : 1;
+    __shared__ __align__(16) int8_t tile[kGlPlanes * 16 * RS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, q = lane >> 4;
-    const int64_t l0 = (int64_t)blockIdx.x * (16 * kGlWaves) + 16 * wave;
-    const int nk = (D + 63) / 64;
-    // this lane's A rows: label l0 + l16, dims 64 kk + 16 q .. +15 (zero past D or past N)
+    const int64_t l0 = (int64_t)blockIdx.x * (32 * kGlWaves) + 32 * wave;
+    // this lane's A rows: label l0 + 16 m + l16, dims 64 kk + 16 q .. +15 (zero past D or past N)
     const Buf eb(E, (uint32_t)(N * D));
-    i32x4_t a[kGlMaxD / 64];
+    i32x4_t a[2][NK];
 #pragma unroll
-    for (int kk = 0; kk < kGlMaxD / 64; ++kk) {
-        const int d0 = 64 * kk + 16 * q;
-        const bool ok = kk < nk && d0 < D && l0 + l16 < N;
-        a[kk] = __builtin_bit_cast(i32x4_t, eb.ld16(ok ? (uint32_t)((l0 + l16) * D + d0) : kOob));
-    }
-    double bv[4];
-    int bi[4];
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bv[i] = -DBL_MAX;
-        bi[i] = INT_MAX;
-    }
+        for (int kk = 0; kk < NK; ++kk) {
+            const int d0 = 64 * kk + 16 * q;
+            const int64_t l = l0 + 16 * m + l16;
+            a[m][kk] = __builtin_bit_cast(i32x4_t, eb.ld16(d0 < D && l < N ? (uint32_t)(l * D + d0) : kOob));
+        }
+    // best so far per label: the score's stand-in, the exact product and the centre
+    double bv[2][4], bd[2][4];
+    int bi[2][4];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            bv[m][i] = bd[m][i] = 0.0;
+            bi[m][i] = INT_MAX;
+        }
+    // 16-byte piece e of a tile: plane e / (64 NK), centre, chunk (zero past D and past C)
     const Buf cb(cp, (uint32_t)(kGlPlanes * C * D));
+    uint4 st[SL];
+    auto load = [&](int64_t c0) {
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            const int e = threadIdx.x + 64 * kGlWaves * i, p = e / (64 * NK), r = (e / (4 * NK)) & 15, ch = e % (4 * NK);
+            st[i] = cb.ld16(p < kGlPlanes && c0 + r < C && 16 * ch < D ? (uint32_t)(((int64_t)p * C + c0 + r) * D + 16 * ch) : kOob);
+        }
+    };
+    auto planes = [&](int64_t c0) -> int {        // of the 16 centres (wave-uniform)
+        const int v = c0 + l16 < C ? cnp[c0 + l16] : 1;
+        return __ballot(v > 3) ? 4 : __ballot(v > 2) ? 3 : __ballot(v > 1) ? 2 : 1;
+    };
+    load(0);
+    int npn = planes(0);
     for (int64_t c0 = 0; c0 < C; c0 += 16) {
-        int npt = 1;   // planes of the 16 centres (workgroup-uniform)
-        for (int r = 0; r < 16 && c0 + r < C; ++r) npt = cnp[c0 + r] > npt ? cnp[c0 + r] : npt;
-        __syncthreads();   // the previous tile is no longer read
-        for (int p = 0; p < npt; ++p)
-            for (int e = threadIdx.x; e < 16 * (D / 16); e += 64 * kGlWaves) {
-                const int r = e / (D / 16), ch = e - r * (D / 16);
-                const uint4 v = cb.ld16(c0 + r < C ? (uint32_t)(((int64_t)p * C + c0 + r) * D + 16 * ch) : kOob);
-                *reinterpret_cast<uint4 *>(&tile[p][r * kGlMaxD + 16 * ch]) = v;
-            }
+        const int npt = npn;
+        __syncthreads();                          // the previous tile is no longer read
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            const int e = threadIdx.x + 64 * kGlWaves * i, r = e / (4 * NK), ch = e % (4 * NK);   // row: plane 16 + centre
+            if (r < 16 * kGlPlanes) *reinterpret_cast<uint4 *>(&tile[r * RS + 16 * ch]) = st[i];
+        }
         __syncthreads();
-        i32x4_t acc[kGlPlanes];
+        if (c0 + 16 < C) {
+            load(c0 + 16);
+            npn = planes(c0 + 16);
+        }
+        i32x4_t acc[kGlPlanes][2];
 #pragma unroll
         for (int p = 0; p < kGlPlanes; ++p) {
-            acc[p] = i32x4_t{0, 0, 0, 0};
+            acc[p][0] = acc[p][1] = i32x4_t{0, 0, 0, 0};
             if (p >= npt) continue;
 #pragma unroll
-            for (int kk = 0; kk < kGlMaxD / 64; ++kk) {
-                if (kk >= nk) break;
-                const int d0 = 64 * kk + 16 * q;
-                const i32x4_t b = d0 < D ? *reinterpret_cast<const i32x4_t *>(&tile[p][l16 * kGlMaxD + d0])
-                                         : i32x4_t{0, 0, 0, 0};
-                acc[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[kk], b, acc[p], 0, 0, 0);
+            for (int kk = 0; kk < NK; ++kk) {
+                const i32x4_t b = *reinterpret_cast<const i32x4_t *>(&tile[(16 * p + l16) * RS + 64 * kk + 16 * q]);
+                acc[p][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[0][kk], b, acc[p][0], 0, 0, 0);
+                acc[p][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[1][kk], b, acc[p][1], 0, 0, 0);
             }
         }
         const int c = (int)(c0 + l16);
         if (c < C) {
-            const double nc = cn[c];
+            const double nc = cn[c], inv = 1.0 / nc;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t dot = (int64_t)acc[0][i] + (int64_t)acc[1][i] * 256 + (int64_t)acc[2][i] * 65536 +
-                                    (int64_t)acc[3][i] * 16777216;
-                const double v = (double)dot / nc;
-                // centres ascend per lane: ties keep the lower one; a lane's first centre is always
-                // taken, so a label always gets a valid centre (even from NaN scores of zero rows)
-                if (v > bv[i] || bi[i] == INT_MAX) {
-                    bv[i] = v;
-                    bi[i] = c;
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // exact: |dot| < 2^31 127 1024 < 2^53
+                    const double dot = fma((double)acc[3][m][i], 16777216.0,
+                                           fma((double)acc[2][m][i], 65536.0, fma((double)acc[1][m][i], 256.0, (double)acc[0][m][i])));
+                    const double v = dot * inv, t = fabs(bv[m][i]) * 0x1p-48, d = v - bv[m][i];
+                    // centres ascend per lane: ties keep the lower one; a lane's first centre is always
+                    // taken, so a label always gets a valid centre (even from NaN scores of zero rows)
+                    bool take = d > t || bi[m][i] == INT_MAX;
+                    if (!take && d >= -t) take = dot / nc > bd[m][i] / cn[bi[m][i]];
+                    if (take) {
+                        bv[m][i] = v;
+                        bd[m][i] = dot;
+                        bi[m][i] = c;
+                    }
                 }
-            }
         }
     }
     // best over the 16 lanes of each row group: larger value, then lower centre
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        for (int off = 1; off < 16; off <<= 1) {
-            const double ov = __shfl_xor(bv[i], off, 64);
-            const int oi = __shfl_xor(bi[i], off, 64);
-            if (oi != INT_MAX && (bi[i] == INT_MAX || ov > bv[i] || (ov == bv[i] && oi < bi[i]))) {
-                bv[i] = ov;
-                bi[i] = oi;
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double v = bi[m][i] != INT_MAX ? bd[m][i] / cn[bi[m][i]] : 0.0;
+            int bc = bi[m][i];
+            for (int off = 1; off < 16; off <<= 1) {
+                const double ov = __shfl_xor(v, off, 64);
+                const int oi = __shfl_xor(bc, off, 64);
+                if (oi != INT_MAX && (bc == INT_MAX || ov > v || (ov == v && oi < bc))) {
+                    v = ov;
+                    bc = oi;
+                }
             }
+            const int64_t l = l0 + 16 * m + 4 * q + i;
+            if (l16 == 0 && l < N) cl[l] = bc;
         }
-        const int64_t l = l0 + 4 * q + i;
-        if (l16 == 0 && l < N) cl[l] = bi[i];
-    }
 }
 
 __global__ void k_gl_zero(int32_t *__restrict__ p, int64_t n) {
@@ -287,44 +342,318 @@ __global__ __launch_bounds__(256) void k_gl_collect(const int32_t *__restrict__ 
     }
 }
 
-// s_c = the sum of the cluster's members, exactly (one workgroup per cluster; an empty cluster, or
-// one whose members sum to zero, keeps its centre)
-__global__ __launch_bounds__(kGlThreads) void k_gl_centroid(const int8_t *__restrict__ E, int D, int64_t C,
-                                                            const int32_t *__restrict__ members,
-                                                            const int32_t *__restrict__ start,
+// The same lists as a stable counting sort over tiles of TL labels, one wave per tile, where the clusters'
+// counters fit the LDS (C <= kGlSortMax): counts per (tile, cluster), their exclusive sums over the tiles,
+// and then every tile writes its labels behind them.  131K labels, 256 clusters: 600 us for the three
+// kernels above (each cluster scanned all labels), 31 us.
+constexpr int kGlSortMax = 16384;
+constexpr int kGlScanSegs = 16;
+
+__global__ __launch_bounds__(64) void k_gl_hist(const int32_t *__restrict__ cl, int64_t N, int64_t TL, int C,
+                                                int32_t *__restrict__ hist) {
+    extern __shared__ int32_t hc[];               // [C]
+    for (int c = threadIdx.x; c < C; c += 64) hc[c] = 0;
+    __syncthreads();
+    const int64_t l0 = blockIdx.x * TL, l1 = l0 + TL < N ? l0 + TL : N;
+    for (int64_t l = l0 + threadIdx.x; l < l1; l += 64) atomicAdd(&hc[cl[l]], 1);
+    __syncthreads();
+    for (int c = threadIdx.x; c < C; c += 64) hist[(int64_t)blockIdx.x * C + c] = hc[c];
+}
+
+// hist[t][c] becomes the sum over earlier tiles; cnt[c] the total.  64 clusters x 16 runs of tiles.
+__global__ __launch_bounds__(64 * kGlScanSegs) void k_gl_scan(int32_t *__restrict__ hist, int nt, int C,
+                                                              int32_t *__restrict__ cnt) {
+    __shared__ int32_t part[kGlScanSegs][64];
+    const int c = blockIdx.x * 64 + (threadIdx.x & 63), sg = threadIdx.x >> 6;
+    const int per = (nt + kGlScanSegs - 1) / kGlScanSegs, t0 = sg * per, t1 = t0 + per < nt ? t0 + per : nt;
+    int32_t sum = 0;
+    if (c < C) {
+#pragma unroll 8
+        for (int t = t0; t < t1; ++t) sum += hist[(int64_t)t * C + c];
+    }
+    part[sg][threadIdx.x & 63] = sum;
+    __syncthreads();
+    if (c >= C) return;
+    int32_t run = 0;
+    for (int j = 0; j < sg; ++j) run += part[j][threadIdx.x & 63];
+#pragma unroll 8
+    for (int t = t0; t < t1; ++t) {
+        const int32_t v = hist[(int64_t)t * C + c];
+        hist[(int64_t)t * C + c] = run;
+        run += v;
+    }
+    if (sg == kGlScanSegs - 1) cnt[c] = run;
+}
+
+__global__ __launch_bounds__(64) void k_gl_fill(const int32_t *__restrict__ cl, int64_t N, int64_t TL, int C,
+                                                const int32_t *__restrict__ hist, const int32_t *__restrict__ start,
+                                                int32_t *__restrict__ members) {
+    extern __shared__ int32_t hc[];               // [C]: where the tile's next label of the cluster goes
+    for (int c = threadIdx.x; c < C; c += 64) hc[c] = start[c] + hist[(int64_t)blockIdx.x * C + c];
+    __syncthreads();
+    const int64_t l0 = blockIdx.x * TL, l1 = l0 + TL < N ? l0 + TL : N;
+    const uint64_t lt = __lanemask_lt();
+    for (int64_t base = l0; base < l1; base += 64) {
+        const int64_t l = base + threadIdx.x;
+        const int c = l < l1 ? cl[l] : -1;
+        uint64_t left = __ballot(c >= 0);
+        int rank = 0, same = 0;                   // labels of this lane's cluster before it, and in all
+        while (left) {                            // cluster by cluster (wave-uniform)
+            const int cc = __builtin_amdgcn_readlane(c, (int)__builtin_ctzll(left));
+            const uint64_t m = __ballot(c == cc);
+            if (c == cc) {
+                rank = __popcll(m & lt);
+                same = __popcll(m);
+            }
+            left &= ~m;
+        }
+        if (c >= 0) members[hc[c] + rank] = (int32_t)l;
+        __syncthreads();
+        if (c >= 0 && rank == same - 1) hc[c] += same;
+        __syncthreads();
+    }
+}
+
+// cs[c] += the sums of the clusters' member rows (cs zeroed before): a workgroup takes kGlSumRows
+// consecutive places of the member lists, run by run of one cluster; its 8 waves take every eighth member,
+// a lane 16 dimensions, and the waves' sums meet in LDS before they are added (whole numbers: any order
+// gives the same sum).  131K x 768: one workgroup per cluster reading single bytes 785 us, 22 us (and 5 for the centres).
+constexpr int kGlSumRows = 256;
+__global__ __launch_bounds__(512) void k_gl_sum(const int8_t *__restrict__ E, int64_t N, int D,
+                                                const int32_t *__restrict__ members, const int32_t *__restrict__ cl,
+                                                const int32_t *__restrict__ start, int32_t *__restrict__ cs) {
+    __shared__ int32_t wsum[8 * kGlMaxD];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t p0 = (int64_t)blockIdx.x * kGlSumRows, p1 = p0 + kGlSumRows < N ? p0 + kGlSumRows : N;
+    const bool own = 16 * lane < D;
+    for (int64_t q0 = p0; q0 < p1;) {             // workgroup-uniform
+        const int c = cl[members[q0]];
+        const int64_t q1 = start[c + 1] < p1 ? start[c + 1] : p1;
+        int32_t acc[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc[k] = 0;
+        for (int64_t m0 = q0 + wave; m0 < q1; m0 += 64) {   // 8 members of this wave
+            uint4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool ok = own && m0 + 8 * j < q1;
+                v[j] = ok ? *reinterpret_cast<const uint4 *>(E + (int64_t)members[m0 + 8 * j] * D + 16 * lane) : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+                for (int k = 0; k < 16; ++k)      // a dot product with one 1 adds one signed byte
+                    acc[k] = __builtin_amdgcn_sdot4((int)w[k >> 2], 1 << (8 * (k & 3)), acc[k], false);
+            }
+        }
+        if (own) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) wsum[wave * kGlMaxD + 16 * lane + k] = acc[k];
+        }
+        __syncthreads();
+        for (int d = threadIdx.x; d < D; d += 512) {
+            int32_t t = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) t += wsum[w * kGlMaxD + d];
+            if (t != 0) atomicAdd(&cs[(int64_t)c * D + d], t);
+        }
+        __syncthreads();
+        q0 = q1;
+    }
+}
+
+// centre c from the sum in cs (one workgroup per cluster; an empty cluster, or one whose members sum to
+// zero, keeps its centre)
+__global__ __launch_bounds__(kGlThreads) void k_gl_centroid(int D, int64_t C, const int32_t *__restrict__ start,
                                                             int32_t *__restrict__ cs, int8_t *__restrict__ cp,
                                                             double *__restrict__ cn, int32_t *__restrict__ cnp) {
     const int c = blockIdx.x;
-    const int32_t m0 = start[c], m1 = start[c + 1];
-    if (m1 == m0) return;   // workgroup-uniform
+    if (start[c + 1] == start[c]) return;   // workgroup-uniform
     int32_t sum[kGlMaxD / kGlThreads];
 #pragma unroll
-    for (int t = 0; t < kGlMaxD / kGlThreads; ++t) sum[t] = 0;
-    for (int32_t m = m0; m < m1; ++m) {
-        const int8_t *e = E + (int64_t)members[m] * D;
-#pragma unroll
-        for (int t = 0; t < kGlMaxD / kGlThreads; ++t) {
-            const int d = threadIdx.x + kGlThreads * t;
-            if (d < D) sum[t] += e[d];
-        }
+    for (int t = 0; t < kGlMaxD / kGlThreads; ++t) {
+        const int d = threadIdx.x + kGlThreads * t;
+        sum[t] = d < D ? cs[(int64_t)c * D + d] : 0;
     }
     gl_store_centre(sum, D, C, c, cs, cp, cn, cnp);
 }
 
-// |e|^2 of every label (exact integers below 2^24)
-__global__ void k_gl_norms(const int8_t *__restrict__ E, int64_t N, int D, int32_t *__restrict__ nrm) {
-    const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= N) return;
-    const int8_t *e = E + l * D;
+// |e|^2 of every label (exact integers below 2^24), 16 lanes per label
+__global__ __launch_bounds__(256) void k_gl_norms(const int8_t *__restrict__ E, int64_t N, int D, int32_t *__restrict__ nrm) {
+    const int64_t l = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int l16 = threadIdx.x & 15;
     int32_t acc = 0;
-    for (int d = 0; d < D; d += 4) {
-        const int32_t w = *reinterpret_cast<const int32_t *>(e + d);
-        acc = __builtin_amdgcn_sdot4(w, w, acc, false);
+    if (l < N) {
+        for (int d = 16 * l16; d < D; d += 256) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(E + l * D + d);
+            acc = __builtin_amdgcn_sdot4((int)v.x, (int)v.x, acc, false);
+            acc = __builtin_amdgcn_sdot4((int)v.y, (int)v.y, acc, false);
+            acc = __builtin_amdgcn_sdot4((int)v.z, (int)v.z, acc, false);
+            acc = __builtin_amdgcn_sdot4((int)v.w, (int)v.w, acc, false);
+        }
     }
-    nrm[l] = acc;
+    for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
+    if (l < N && l16 == 0) nrm[l] = acc;
 }
 
-// Greedy groups inside each cluster (one workgroup per cluster): the seed is the (out(N + c N + t)
+// Greedy groups of clusters of up to kGlSmall members (one workgroup per cluster; the larger ones take
+// the kernel below).  The unassigned members' places stay compact and ascending in LDS, so the seed
+// is read directly; 16 lanes form one member's product with the seed's row; and instead of k - 1 passes
+// of a workgroup maximum, a radix selection over the upper halves of the similarities finds the value
+// that the group's other members lie above, and only those at it are compared in full.  131K labels, 256
+// clusters (the largest of about 2000): 6.4 ms with the kernel below, 0.48 ms.
+constexpr int kGlSmall = 2048;
+constexpr int kGlSmallThreads = 1024;
+__global__ __launch_bounds__(kGlSmallThreads) void k_gl_greedy_small(
+    const int8_t *__restrict__ E, int64_t N, int D, const int32_t *__restrict__ members, const int32_t *__restrict__ start,
+    const int32_t *__restrict__ gstart, int64_t G, uint64_t seed, const int32_t *__restrict__ nrm, int32_t *__restrict__ order,
+    int32_t *__restrict__ gsize) {
+    constexpr int T = kGlSmallThreads, PT = kGlSmall / T;   // members per thread
+    constexpr int RU = 4;                         // rows in flight per 16 lanes
+    __shared__ int32_t un[2][kGlSmall];           // places of the unassigned members, ascending
+    __shared__ int32_t lab[kGlSmall];             // their labels
+    __shared__ int32_t dot[kGlSmall];
+    __shared__ uint2 eq[kGlSmall];                // members at the threshold: lower half, place
+    __shared__ int32_t hist[256], wcnt[2][T / 64];
+    __shared__ int32_t s_bin, s_above, s_eq;
+    const int c = blockIdx.x;
+    const int32_t m0 = start[c], n = start[c + 1] - m0;
+    if (n > kGlSmall) return;                     // workgroup-uniform
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15;
+    int32_t g = gstart[c], pos = m0;
+    for (int i = tid; i < n; i += T) un[0][i] = i;
+    __syncthreads();
+    int cur = 0;
+    for (int64_t t = 0, nu = n; nu > 0; ++t, cur ^= 1) {
+        const int u = (int)nu, k = u < (int)G ? u : (int)G;
+        const int r = (int)(splitmix64_at(seed, (uint64_t)(N + (int64_t)c * N + t)) % (uint64_t)nu);
+        for (int i = tid; i < u; i += T) lab[i] = members[m0 + un[cur][i]];
+        if (tid == 0) s_eq = 0;
+        __syncthreads();
+        int need = k - 1;                         // members to choose beside the seed
+        uint32_t thr = 0;                         // those whose upper half lies above it, and `need` of those at it
+        uint64_t key[PT];                         // ordered as the similarities
+#pragma unroll
+        for (int j = 0; j < PT; ++j) key[j] = 0;
+        if (need > 0 && need < u - 1) {           // workgroup-uniform; else none or all of them
+            const int8_t *es = E + (int64_t)lab[r] * D;
+            uint4 sv[kGlMaxD / 256];
+#pragma unroll
+            for (int q = 0; q < kGlMaxD / 256; ++q)
+                sv[q] = 16 * l16 + 256 * q < D ? *reinterpret_cast<const uint4 *>(es + 16 * l16 + 256 * q) : make_uint4(0, 0, 0, 0);
+            for (int i0 = tid >> 4; i0 < u; i0 += RU * (T / 16)) {
+                int32_t acc[RU];
+#pragma unroll
+                for (int x = 0; x < RU; ++x) {
+                    const int i = i0 + x * (T / 16);
+                    const int8_t *e = E + (int64_t)lab[i < u ? i : i0] * D + 16 * l16;
+                    acc[x] = 0;
+#pragma unroll
+                    for (int q = 0; q < kGlMaxD / 256; ++q) {
+                        if (16 * l16 + 256 * q >= D) continue;
+                        const uint4 v = *reinterpret_cast<const uint4 *>(e + 256 * q);
+                        acc[x] = __builtin_amdgcn_sdot4((int)v.x, (int)sv[q].x, acc[x], false);
+                        acc[x] = __builtin_amdgcn_sdot4((int)v.y, (int)sv[q].y, acc[x], false);
+                        acc[x] = __builtin_amdgcn_sdot4((int)v.z, (int)sv[q].z, acc[x], false);
+                        acc[x] = __builtin_amdgcn_sdot4((int)v.w, (int)sv[q].w, acc[x], false);
+                    }
+                }
+#pragma unroll
+                for (int x = 0; x < RU; ++x) {
+                    const int i = i0 + x * (T / 16);
+                    for (int off = 8; off > 0; off >>= 1) acc[x] += __shfl_xor(acc[x], off, 16);
+                    if (l16 == 0 && i < u) dot[i] = acc[x];
+                }
+            }
+            __syncthreads();
+            const int64_t ns = nrm[lab[r]];
+#pragma unroll
+            for (int j = 0; j < PT; ++j) {
+                const int i = tid + T * j;
+                if (i >= u) continue;
+                const uint64_t b = __builtin_bit_cast(uint64_t, (double)dot[i] / sqrt((double)((int64_t)nrm[lab[i]] * ns)));
+                key[j] = b >> 63 ? ~b : b | (uint64_t)1 << 63;
+            }
+            for (int sh = 24; sh >= 0; sh -= 8) {
+                for (int i = tid; i < 256; i += T) hist[i] = 0;
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < PT; ++j) {
+                    const int i = tid + T * j;
+                    const uint32_t hi = (uint32_t)(key[j] >> 32);
+                    if (i < u && i != r && (sh == 24 || hi >> (sh + 8) == thr >> (sh + 8))) atomicAdd(&hist[(hi >> sh) & 255], 1);
+                }
+                __syncthreads();
+                if (wave == 0) {                  // the bin that holds the need-th from above: lane -> 4 bins downward
+                    int32_t cnt[4], sum = 0;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) sum += cnt[x] = hist[255 - 4 * lane - x];
+                    int32_t incl = sum;
+                    for (int off = 1; off < 64; off <<= 1) {
+                        const int32_t o = __shfl_up(incl, off);
+                        if (lane >= off) incl += o;
+                    }
+                    int32_t above = incl - sum;
+                    if (above < need && incl >= need) {
+                        int x = 0;
+                        while (above + cnt[x] < need) above += cnt[x++];
+                        s_bin = 255 - 4 * lane - x;
+                        s_above = above;
+                    }
+                }
+                __syncthreads();
+                thr |= (uint32_t)s_bin << sh;
+                need -= s_above;
+            }
+#pragma unroll
+            for (int j = 0; j < PT; ++j) {
+                const int i = tid + T * j;
+                if (i < u && i != r && (uint32_t)(key[j] >> 32) == thr) eq[atomicAdd(&s_eq, 1)] = make_uint2((uint32_t)key[j], (uint32_t)i);
+            }
+            __syncthreads();
+        }
+        // the group in ascending order, and the rest: T places at a time
+        const bool all_in = k == u;
+        int gone = 0;                             // chosen members before this run of T
+#pragma unroll
+        for (int j = 0; j < PT; ++j) {
+            if (T * j >= u) break;                // workgroup-uniform
+            const int i = tid + T * j;
+            bool in = i < u && (all_in || i == r);
+            if (i < u && i != r && !all_in && k > 1) {
+                const uint32_t hi = (uint32_t)(key[j] >> 32), lo = (uint32_t)key[j];
+                in = hi > thr;
+                if (hi == thr) {                  // larger similarity first, then the lower place
+                    int rank = 0;
+                    for (int x = 0; x < s_eq; ++x) rank += eq[x].x > lo || (eq[x].x == lo && (int)eq[x].y < i);
+                    in = rank < need;
+                }
+            }
+            const uint64_t m = __ballot(in);
+            if (lane == 0) wcnt[j & 1][wave] = __popcll(m);
+            __syncthreads();
+            int before = gone, all = gone;
+            for (int w = 0; w < T / 64; ++w) {
+                before += w < wave ? wcnt[j & 1][w] : 0;
+                all += wcnt[j & 1][w];
+            }
+            before += __popcll(m & __lanemask_lt());
+            if (i < u) {
+                if (in) order[pos + before] = lab[i];
+                else un[cur ^ 1][i - before] = un[cur][i];
+            }
+            gone = all;
+        }
+        if (tid == 0) gsize[g] = k;
+        __syncthreads();
+        pos += k;
+        ++g;
+        nu -= k;
+    }
+}
+
+// Greedy groups inside each cluster of more than kGlSmall members (one workgroup per cluster): the seed is the (out(N + c N + t)
 // mod nu)-th unassigned member in ascending order; the group is the seed and its top-(k - 1)
 // unassigned members by cosine to it (k = min(G, nu), ties to the lower label), listed in ascending
 // label order.
@@ -342,6 +671,7 @@ __global__ __launch_bounds__(kGlThreads) void k_gl_greedy(const int8_t *__restri
     __shared__ int32_t bpos;
     const int c = blockIdx.x;
     const int32_t m0 = start[c], n = start[c + 1] - m0;
+    if (n <= kGlSmall) return;                    // workgroup-uniform
     int32_t g = gstart[c], pos = m0;
     for (int32_t i = threadIdx.x; i < n; i += kGlThreads) taken[m0 + i] = 0;
     __syncthreads();
@@ -488,12 +818,41 @@ hipError_t group_labels(int64_t N, int64_t D, const int8_t *E, int64_t G, int64_
     int32_t *start = reinterpret_cast<int32_t *>(take((C + 1) * 4));
     int32_t *gstart = reinterpret_cast<int32_t *>(take((C + 1) * 4));
     const int Di = (int)D;
-    hipLaunchKernelGGL(k_gl_iota, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, s, a, N);
-    hipLaunchKernelGGL(k_gl_shuffle, dim3(1), dim3(64), 0, s, a, N, C, seed);
+    if (C <= kGlShuffleMax) {
+        hipLaunchKernelGGL(k_gl_draw, dim3(1), dim3(1024), (size_t)C * 4, s, a, N, (int)C, seed);
+    } else {
+        hipLaunchKernelGGL(k_gl_iota, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, s, a, N);
+        hipLaunchKernelGGL(k_gl_shuffle, dim3(1), dim3(64), 0, s, a, N, C, seed);
+    }
     hipLaunchKernelGGL(k_gl_pick_centres, dim3((unsigned)C), dim3(kGlThreads), 0, s, E, a, C, Di, cs, cp, cn, cnp);
-    const dim3 ga((unsigned)cdiv(N, 16 * kGlWaves));
+    const dim3 ga((unsigned)cdiv(N, 32 * kGlWaves));
+    auto assign = [&](auto kern) { hipLaunchKernelGGL(kern, ga, dim3(64 * kGlWaves), 0, s, E, N, Di, cp, cn, cnp, C, cl); };
+    // tiles of the counting sort: about 512, and few enough that their counts fit the similarities' space
+    // (8 N bytes; those come later)
+    int64_t TL = cdiv(N, 512) > 256 ? cdiv(N, 512) : 256;
+    if (TL < cdiv(C, 2)) TL = cdiv(C, 2);
+    const int nt = (int)cdiv(N, TL);
+    const bool sorted = C <= kGlSortMax && (int64_t)nt * C * 4 <= N * 8;
+    int32_t *hist = reinterpret_cast<int32_t *>(sims);
+    hipError_t e = hipSuccess;
+    if (sorted) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_gl_hist), hipFuncAttributeMaxDynamicSharedMemorySize, (int)C * 4);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_gl_fill), hipFuncAttributeMaxDynamicSharedMemorySize, (int)C * 4);
+        if (e != hipSuccess) return e;
+    }
     auto assign_and_collect = [&]() {
-        hipLaunchKernelGGL(k_gl_assign, ga, dim3(64 * kGlWaves), 0, s, E, N, Di, cp, cn, cnp, C, cl);
+        if (D <= 256) assign(k_gl_assign<4>);
+        else if (D <= 512) assign(k_gl_assign<8>);
+        else if (D <= 768) assign(k_gl_assign<12>);
+        else assign(k_gl_assign<16>);
+        if (sorted) {
+            hipLaunchKernelGGL(k_gl_hist, dim3((unsigned)nt), dim3(64), (size_t)C * 4, s, cl, N, TL, (int)C, hist);
+            hipLaunchKernelGGL(k_gl_scan, dim3((unsigned)cdiv(C, 64)), dim3(64 * kGlScanSegs), 0, s, hist, nt, (int)C, cnt);
+            hipLaunchKernelGGL(k_gl_starts, dim3(1), dim3(256), 0, s, cnt, C, G, start, gstart, n_groups);
+            hipLaunchKernelGGL(k_gl_fill, dim3((unsigned)nt), dim3(64), (size_t)C * 4, s, cl, N, TL, (int)C, hist, start, members);
+            return;
+        }
         hipLaunchKernelGGL(k_gl_zero, dim3((unsigned)cdiv(C, 256)), dim3(256), 0, s, cnt, C);
         hipLaunchKernelGGL(k_gl_count, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, s, cl, N, cnt);
         hipLaunchKernelGGL(k_gl_starts, dim3(1), dim3(256), 0, s, cnt, C, G, start, gstart, n_groups);
@@ -501,11 +860,14 @@ hipError_t group_labels(int64_t N, int64_t D, const int8_t *E, int64_t G, int64_
     };
     for (int64_t it = 0; it < iters; ++it) {
         assign_and_collect();
-        hipLaunchKernelGGL(k_gl_centroid, dim3((unsigned)C), dim3(kGlThreads), 0, s, E, Di, C, members, start, cs, cp,
-                           cn, cnp);
+        hipLaunchKernelGGL(k_gl_zero, dim3((unsigned)cdiv(C * D, 256)), dim3(256), 0, s, cs, C * D);
+        hipLaunchKernelGGL(k_gl_sum, dim3((unsigned)cdiv(N, kGlSumRows)), dim3(512), 0, s, E, N, Di, members, cl, start, cs);
+        hipLaunchKernelGGL(k_gl_centroid, dim3((unsigned)C), dim3(kGlThreads), 0, s, Di, C, start, cs, cp, cn, cnp);
     }
     assign_and_collect();
-    hipLaunchKernelGGL(k_gl_norms, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, s, E, N, Di, nrm);
+    hipLaunchKernelGGL(k_gl_norms, dim3((unsigned)cdiv(N, 16)), dim3(256), 0, s, E, N, Di, nrm);
+    hipLaunchKernelGGL(k_gl_greedy_small, dim3((unsigned)C), dim3(kGlSmallThreads), 0, s, E, N, Di, members, start, gstart,
+                       G, seed, nrm, order, gsize);
     hipLaunchKernelGGL(k_gl_greedy, dim3((unsigned)C), dim3(kGlThreads), 0, s, E, N, Di, members, start, gstart, G,
                        seed, nrm, taken, sims, order, gsize);
     return hipGetLastError();
