@@ -622,6 +622,145 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float *__restrict__ A, i
         }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Small or unaligned bf16 products.  A workgroup forms one 32 x 32 output tile; its 4 waves share K (wave w
+// takes every fourth 16-step), read both operands straight from memory into the matrix-core layout, two
+// steps ahead, and meet in LDS at the end, each storing a quarter of the tile.  Against the 128 x 128
+// kernel, whose few tiles leave most CUs idle and whose every step waits for its loads, this has 16
+// times the workgroups and no barrier in the loop (77 x 1003 x 500: forward 60 us there, 8 here, dX 30 and 7, dW
+// 13 and 6; 8 x 16384 x 768 against the 256-row tiles: 12.4 and 7.2); with many tiles its operand loads (each element read once per 32 outputs) are what costs.
+// ---------------------------------------------------------------------------------------------
+constexpr int kDirT = 32;
+
+// how a fragment of 8 consecutive k is read: 16 bytes (rows of whole 16-byte groups), dwords, or halves
+enum { DIR16 = 0, DIR4 = 1, DIR2 = 2 };
+
+// K contiguous: elements k .. k + 7 of row r (row stride ld), zero from klim on
+template <int RD>
+__device__ __forceinline__ bf16x8_t dir_load_k(const Buf &b, int64_t r, int64_t ld, int64_t k, int64_t klim, bool ok) {
+    const uint32_t o = (uint32_t)((r * ld + k) * 2);
+    if constexpr (RD == DIR16) return as_bf16x8(b.ld16(ok && k < klim ? o : kOob));
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (RD == DIR4)
+            v[i] = b.ld4(ok && k + 2 * i < klim ? o + 4 * i : kOob);
+        else
+            v[i] = (uint32_t)b.ld2(ok && k + 2 * i < klim ? o + 4 * i : kOob) |
+                   ((uint32_t)b.ld2(ok && k + 2 * i + 1 < klim ? o + 4 * i + 2 : kOob) << 16);
+    }
+    return as_bf16x8(make_uint4(v[0], v[1], v[2], v[3]));
+}
+
+// rows contiguous: elements k .. k + 7 of row r at (k + e) ld + r
+__device__ __forceinline__ bf16x8_t dir_load_r(const Buf &b, int64_t r, int64_t ld, int64_t k, int64_t klim, bool ok) {
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t lo = b.ld2(ok && k + 2 * i < klim ? (uint32_t)(((k + 2 * i) * ld + r) * 2) : kOob);
+        const uint32_t hi = b.ld2(ok && k + 2 * i + 1 < klim ? (uint32_t)(((k + 2 * i + 1) * ld + r) * 2) : kOob);
+        v[i] = lo | hi << 16;
+    }
+    return as_bf16x8(make_uint4(v[0], v[1], v[2], v[3]));
+}
+
+// A(m, k): AK ? m lda + k : k lda + m;  B(k, n): BK ? n ldb + k : k ldb + n.  EPI_BF16_BCE: the gradient of
+// the logits rounded to bf16.  gridDim: (n tiles, m tiles, chunks of K)
+template <bool AK, bool BK, int EPI, int RD>
+__global__ __launch_bounds__(256) void k_gemm_dir(const bf16_t *__restrict__ A, int64_t lda, uint32_t a_bytes,
+                                                  const bf16_t *__restrict__ Bm, int64_t ldb, uint32_t b_bytes,
+                                                  void *__restrict__ C, int64_t ldc, const float *__restrict__ bias,
+                                                  int64_t M, int64_t N, int64_t K, int64_t kchunk,
+                                                  const int32_t *__restrict__ pos, int P) {
+    __shared__ float red[4][4][64][4];            // quarter of the tile, wave, lane
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ln = lane & 31, hh = lane >> 5;
+    const int64_t n0 = (int64_t)blockIdx.x * kDirT, m0 = (int64_t)blockIdx.y * kDirT;
+    const int64_t kb = (int64_t)blockIdx.z * kchunk, ke = kb + kchunk < K ? kb + kchunk : K;
+    const Buf ab(A, a_bytes), bb(Bm, b_bytes);
+    const int64_t m = m0 + ln, n = n0 + ln;
+    auto load = [&](int64_t k, bf16x8_t &a, bf16x8_t &b) {
+        const int64_t kk = k + 8 * hh;
+        if constexpr (AK) a = dir_load_k<RD>(ab, m, lda, kk, ke, m < M);
+        else a = dir_load_r(ab, m, lda, kk, ke, m < M);
+        if constexpr (BK) b = dir_load_k<RD>(bb, n, ldb, kk, ke, n < N);
+        else b = dir_load_r(bb, n, ldb, kk, ke, n < N);
+    };
+    f32x16_t acc = f32x16_t{0};
+    bf16x8_t a[3], b[3];
+    const int64_t k0 = kb + 16 * wave;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) load(k0 + 64 * i, a[i], b[i]);   // past the chunk: zeros
+    for (int64_t k = k0; k < ke; k += 3 * 64) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            load(k + 64 * (i + 2), a[(i + 2) % 3], b[(i + 2) % 3]);
+            acc = mfma32x32x16(a[i], b[i], acc);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4 *>(red[i][wave][lane]) = make_float4(acc[4 * i], acc[4 * i + 1], acc[4 * i + 2], acc[4 * i + 3]);
+    __syncthreads();
+    // wave w: rows 8 w + 4 hh + j of column ln, the four waves' sums in order
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float4 x = *reinterpret_cast<const float4 *>(red[wave][w][lane]);
+        v[0] += x.x;
+        v[1] += x.y;
+        v[2] += x.z;
+        v[3] += x.w;
+    }
+    if (n >= N) return;
+    const float bv = (EPI == EPI_BF16_BIAS || EPI == EPI_BF16_BCE) && bias ? bias[n] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int64_t mr = m0 + 8 * wave + 4 * hh + j;
+        if (mr >= M) continue;
+        if (EPI == EPI_BF16_BIAS) {
+            reinterpret_cast<bf16_t *>(C)[mr * ldc + n] = f32_to_bf16(v[j] + bv);
+        } else if (EPI == EPI_BF16_BCE) {
+            bool hit = false;
+            for (int p = 0; p < P; ++p) hit |= pos[mr * P + p] == (int32_t)n;
+            reinterpret_cast<bf16_t *>(C)[mr * ldc + n] = f32_to_bf16(bce_grad_f32(bf16_to_f32(f32_to_bf16(v[j] + bv)), hit));
+        } else if (EPI == EPI_F32) {
+            reinterpret_cast<float *>(C)[mr * ldc + n] = v[j];
+        } else {
+            reinterpret_cast<float *>(C)[(int64_t)blockIdx.z * M * N + mr * N + n] = v[j];
+        }
+    }
+}
+
+// The direct kernel where the 128 x 128 tiles would leave half of the CUs idle, and operands within the
+// 31-bit range of a buffer offset (the steps past a chunk's end included).
+bool dir_ok(int64_t M, int64_t N, int64_t K, int64_t Z) {
+    const int64_t lim = ((int64_t)1 << 31) - 1, Kp = K + 512;
+    return haste::cdiv(M, TM) * haste::cdiv(N, TN) * Z <= kXcds * kCusPerXcd / 2 && M * Kp * 2 < lim && N * Kp * 2 < lim &&
+           haste::cdiv(M, kDirT) < 65536;
+}
+
+template <bool AK, bool BK, int EPI>
+hipError_t launch_dir(hipStream_t s, const bf16_t *A, int64_t lda, const bf16_t *Bm, int64_t ldb, void *C, int64_t ldc,
+                      const float *bias, int64_t M, int64_t N, int64_t K, int64_t kchunk, int64_t Z,
+                      const int32_t *pos = nullptr, int P = 0) {
+    const dim3 grid((unsigned)haste::cdiv(N, kDirT), (unsigned)haste::cdiv(M, kDirT), (unsigned)Z);
+    // the K-contiguous operands' rows
+    uint64_t al = 0;
+    if (AK) al |= reinterpret_cast<uintptr_t>(A) | (uint64_t)(lda * 2);
+    if (BK) al |= reinterpret_cast<uintptr_t>(Bm) | (uint64_t)(ldb * 2);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, A, lda, (uint32_t)(M * K * 2), Bm, ldb, (uint32_t)(N * K * 2), C, ldc,
+                           bias, M, N, K, kchunk, pos, P);
+        return hipGetLastError();
+    };
+    if constexpr (AK || BK) {
+        if ((al & 15) == 0) return go(k_gemm_dir<AK, BK, EPI, DIR16>);
+        if ((al & 3) == 0) return go(k_gemm_dir<AK, BK, EPI, DIR4>);
+    }
+    return go(k_gemm_dir<AK, BK, EPI, DIR2>);
+}
+
 // split of the H contraction of dX for output tiles of tm x tn: enough workgroups to cover the
 // chip (about `target`), never below 256 head labels per chunk.  at_most: never more than
 // `target` workgroups, for the 256x256 kernel, which holds a whole CU (its LDS allows one
@@ -713,7 +852,12 @@ hipError_t head_fwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
                     const float *bias_h, void *Yh, hipStream_t s) {
     // M = B, N = H, K = F_s;  A(m,k) = X[m*F_s + k];  B(k,n) = Wh[n*F_s + k]
     if (dtype == HASTE_DTYPE_BF16) {
-        if (gemm4_ok(B, F_s, H, {X, Wh, Yh, bias_h}))
+        const bool big = gemm4_ok(B, F_s, H, {X, Wh, Yh, bias_h});
+        // (32 rows or fewer would fill an eighth of the 256-row tiles)
+        if ((!big || B <= 32) && dir_ok(B, H, F_s, 1))
+            return launch_dir<true, true, EPI_BF16_BIAS>(s, (const bf16_t *)X, F_s, (const bf16_t *)Wh, F_s, Yh, H, bias_h, B,
+                                                         H, F_s, F_s, 1);
+        if (big)
             return launch_gemm4<true, true, EPI_BF16_BIAS>(s, (const bf16_t *)X, F_s, B * F_s, (const bf16_t *)Wh, F_s,
                                                            H * F_s, Yh, H, bias_h, B, H, F_s, F_s, 1);
         const dim3 grid((unsigned)cdiv(H, TN), (unsigned)cdiv(B, TM), 1);
@@ -739,6 +883,9 @@ hipError_t head_fwd_bce(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const 
     if (dtype == HASTE_DTYPE_BF16 && gemm4_ok(B, F_s, H, {X, Wh, dYh, bias_h}))
         return launch_gemm4<true, true, EPI_BF16_BCE>(s, (const bf16_t *)X, F_s, B * F_s, (const bf16_t *)Wh, F_s,
                                                       H * F_s, dYh, H, bias_h, B, H, F_s, F_s, 1, pos, P);
+    if (dtype == HASTE_DTYPE_BF16 && dir_ok(B, H, F_s, 1))
+        return launch_dir<true, true, EPI_BF16_BCE>(s, (const bf16_t *)X, F_s, (const bf16_t *)Wh, F_s, dYh, H, bias_h, B, H,
+                                                    F_s, F_s, 1, pos, P);
     const hipError_t e = head_fwd(B, F_s, H, dtype, X, Wh, bias_h, dYh, s);
     if (e != hipSuccess) return e;
     return bce_grad(B, H, dtype, dYh, pos, P, dYh, s);
@@ -753,6 +900,10 @@ hipError_t head_bwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
             // A(m, k) = dYh[k][m] (k-rows of H), B(k, n) = X[k][n] (k-rows of F_s)
             hipError_t e = launch_gemm4<false, false, EPI_F32>(s, (const bf16_t *)dYh, H, B * H, (const bf16_t *)X, F_s,
                                                                B * F_s, (void *)dWh, F_s, nullptr, H, F_s, B, B, 1);
+            if (e != hipSuccess) return e;
+        } else if (bf && dir_ok(H, F_s, B, 1)) {
+            hipError_t e = launch_dir<false, false, EPI_F32>(s, (const bf16_t *)dYh, H, (const bf16_t *)X, F_s, (void *)dWh,
+                                                             F_s, nullptr, H, F_s, B, B, 1);
             if (e != hipSuccess) return e;
         } else if (bf) {
             const dim3 grid((unsigned)cdiv(F_s, TN), (unsigned)cdiv(H, TM), 1);
@@ -787,6 +938,11 @@ hipError_t head_bwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
             hipError_t e = launch_gemm4<true, false, EPI_F32_PART>(s, (const bf16_t *)dYh, H, B * H, (const bf16_t *)Wh,
                                                                    F_s, H * F_s, (void *)part, F_s, nullptr, B, F_s, H,
                                                                    kchunk, (int)Sx);
+            if (e != hipSuccess) return e;
+        } else if (bf && dir_ok(B, F_s, H, 1)) {
+            // (the direct kernel's tiles are a sixteenth of those the split was made for)
+            hipError_t e = launch_dir<true, false, EPI_F32_PART>(s, (const bf16_t *)dYh, H, (const bf16_t *)Wh, F_s,
+                                                                 (void *)part, F_s, nullptr, B, F_s, H, kchunk, Sx);
             if (e != hipSuccess) return e;
         } else if (bf) {
             const dim3 grid((unsigned)cdiv(F_s, TN), (unsigned)cdiv(B, TM), (unsigned)Sx);

@@ -428,11 +428,13 @@ void k_fwd_any(const bf16_t *__restrict__ X, const int32_t *__restrict__ idx, co
             uint4 v;
             if ((F_s & 7) == 0) {                 // kernel-uniform
                 v = xr.ld16(nv > 0 ? o : kOob);
+            } else if ((F_s & 3) == 0) {
+                const uint2 lo = xr.ld8(nv > 0 ? o : kOob), hi = xr.ld8(nv > 4 ? o + 8 : kOob);
+                v = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            } else if ((F_s & 1) == 0) {
+                v = __builtin_bit_cast(uint4, load_row8<kRead4>(xr, o, nv));
             } else {
-                uint32_t e[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) e[k] = xr.ld2(nv > k ? o + 2 * k : kOob);
-                v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+                v = __builtin_bit_cast(uint4, load_row8<kRead2>(xr, o, nv));
             }
             const uint32_t d[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
