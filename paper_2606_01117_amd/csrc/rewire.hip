@@ -20,56 +20,135 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t s, uint64_t i) {
 }
 
 // Selection state of the radix select: the prefix of the threshold's key found so far, the bits it
-// covers, and the rank of the wanted key among the keys that share the prefix.
+// covers, the rank of the wanted key among the keys that share the prefix, the number of blocks that
+// have added their counts, and whether every key equal to the threshold is pruned.
 struct RwState {
     uint32_t prefix, pmask;
     uint64_t rank;
+    uint32_t done, all;
 };
-
-// keys[k F + j] = bits of the fp32 sum over the group's labels of |W[l, j]| (non-negative, so the
-// bit patterns order as the values)
-template <typename T>
-__global__ __launch_bounds__(256) void k_rw_scores(const T *__restrict__ W, int64_t K, int G, int F,
-                                                   uint32_t *__restrict__ keys) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= K * F) return;
-    const int64_t k = i / F;
-    const int j = (int)(i - k * F);
-    // the labels' weights 8 at a time, all 8 loads in flight before they are summed in order
-    float s = 0.0f;
-    const T *w = W + k * G * F + j;
-    int g = 0;
-    for (; g + 8 <= G; g += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = load_f32(w, (int64_t)(g + u) * F);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += fabsf(v[u]);
-    }
-    for (; g < G; ++g) s += fabsf(load_f32(w, (int64_t)g * F));
-    keys[i] = __float_as_uint(s);
-}
 
 __global__ void k_rw_init(uint32_t *__restrict__ hist, RwState *__restrict__ st, uint64_t rank) {
     const int t = threadIdx.x;
     if (t < 256) hist[t] = 0u;
-    if (t == 0) *st = RwState{0u, 0u, rank};
+    if (t == 0) *st = RwState{0u, 0u, rank, 0u, 0u};
+}
+
+// Digit counts of one workgroup in LDS: 16 copies, by lane, at an odd stride, because the keys of
+// trained weights share one or two values of their leading digit and a wave's 64 additions to one
+// counter are served one after the other.
+constexpr int kRwRep = 16, kRwRepStride = 257;
+
+__device__ __forceinline__ void rw_clear(uint32_t *h) {
+    for (int i = threadIdx.x; i < kRwRep * kRwRepStride; i += blockDim.x) h[i] = 0u;
+    __syncthreads();
+}
+
+// Adds the workgroup's counts to the digit's histogram; the last workgroup to do so picks the digit
+// whose cumulative count passes the wanted rank and clears the histogram for the next pass.  What
+// crosses workgroups goes through device-scope atomics alone, each done (its old value is back)
+// before the workgroup's barrier and so before its addition to st->done: no fence, which would write
+// back the L2 with the keys just stored (one per workgroup: 690 us for the score pass).
+__device__ void rw_pick(const uint32_t *h, uint32_t *hist, RwState *st, int shift) {
+    __shared__ uint32_t scan[256];
+    __shared__ bool last;
+    const int t = threadIdx.x;   // 256 threads or more
+    __syncthreads();
+    uint32_t own = 0u;
+    if (t < 256)
+        for (int r = 0; r < kRwRep; ++r) own += h[r * kRwRepStride + t];
+    const uint32_t old = own ? __hip_atomic_fetch_add(&hist[t], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (__syncthreads_or(old == 0xFFFFFFFFu)) return;   // waits for old; never taken (fewer than 2^31 keys)
+    if (t == 0)
+        last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;   // workgroup-uniform
+    uint32_t n = 0u;
+    if (t < 256) {
+        n = __hip_atomic_load(&hist[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&hist[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        scan[t] = n;
+    }
+    __syncthreads();
+    for (int off = 1; off < 256; off <<= 1) {
+        const uint32_t a = t >= off && t < 256 ? scan[t - off] : 0u;
+        __syncthreads();
+        if (t < 256) scan[t] += a;
+        __syncthreads();
+    }
+    const uint64_t rank = st->rank, upto = t < 256 ? scan[t] : 0u, before = upto - n;   // (fewer than 2^31 keys)
+    __syncthreads();
+    if (before <= rank && rank < upto) {   // one thread
+        st->prefix |= (uint32_t)t << shift;
+        st->pmask |= 255u << shift;
+        st->rank = rank - before;
+        st->all = rank - before + 1 == n ? 1u : 0u;
+        st->done = 0u;
+    }
+}
+
+// keys[k F + j] = bits of the fp32 sum over the group's labels of |W[l, j]| (non-negative, so the
+// bit patterns order as the values), and the count of their leading digit.  NE neighbouring slots
+// per thread, read together (NE divides F and W is 16-byte aligned): the pass is
+// bound by memory (2.9M x 64: 101 to 118 us with 2 bytes, 8 bytes or 16 a load, the leading digit's
+// count included; that count took 53 us in a pass of its own, the scores 88).
+template <typename T, int NE>
+__global__ __launch_bounds__(256) void k_rw_scores(const T *__restrict__ W, int64_t K, int G, int F,
+                                                   uint32_t *__restrict__ keys, uint32_t *__restrict__ hist,
+                                                   RwState *__restrict__ st) {
+    typedef T Vec __attribute__((ext_vector_type(NE)));
+    __shared__ uint32_t h[kRwRep * kRwRepStride];
+    rw_clear(h);
+    uint32_t *mine = h + (threadIdx.x & (kRwRep - 1)) * kRwRepStride;
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * NE; i < K * F;
+         i += (int64_t)gridDim.x * blockDim.x * NE) {
+        const int64_t k = (uint32_t)i / (uint32_t)F;   // K F < 2^29
+        const int j = (int)(i - k * F);
+        // the labels' weights 8 at a time, all 8 loads in flight before they are summed in order
+        float s[NE];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) s[e] = 0.0f;
+        const T *w = W + k * G * F + j;
+        auto load = [&](int g) { return *reinterpret_cast<const Vec *>(w + (int64_t)g * F); };
+        auto add = [&](Vec v) {
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const T x = v[e];
+                s[e] += fabsf(load_f32(&x, 0));
+            }
+        };
+        int g = 0;
+        for (; g + 8 <= G; g += 8) {
+            Vec v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = load(g + u);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) add(v[u]);
+        }
+        for (; g < G; ++g) add(load(g));
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const uint32_t key = __float_as_uint(s[e]);
+            keys[i + e] = key;
+            atomicAdd(&mine[key >> 24], 1u);
+        }
+    }
+    rw_pick(h, hist, st, 24);
 }
 
 // histogram of the next 8-bit digit (at `shift`) of the keys that share the current prefix
-__global__ __launch_bounds__(256) void k_rw_hist(const uint32_t *__restrict__ keys, int64_t n,
-                                                 const RwState *__restrict__ st, int shift,
-                                                 uint32_t *__restrict__ hist) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0u;
-    __syncthreads();
+__global__ __launch_bounds__(1024) void k_rw_hist(const uint32_t *__restrict__ keys, int64_t n,
+                                                 RwState *__restrict__ st, int shift, uint32_t *__restrict__ hist) {
+    __shared__ uint32_t h[kRwRep * kRwRepStride];
+    rw_clear(h);
+    uint32_t *mine = h + (threadIdx.x & (kRwRep - 1)) * kRwRepStride;
     const uint32_t prefix = st->prefix, pmask = st->pmask;
     // four keys per 16-byte load, four loads in flight per thread (the keys array is 256-byte
     // aligned); the last n mod 4 keys one by one
     const uint4 *k4 = reinterpret_cast<const uint4 *>(keys);
     const int64_t n4 = n / 4, stride = (int64_t)gridDim.x * blockDim.x;
     auto count = [&](uint32_t key) {
-        if ((key & pmask) == prefix) atomicAdd(&h[(key >> shift) & 255u], 1u);
+        if ((key & pmask) == prefix) atomicAdd(&mine[(key >> shift) & 255u], 1u);
     };
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += 4 * stride) {
         uint4 v[4];
@@ -89,41 +168,17 @@ __global__ __launch_bounds__(256) void k_rw_hist(const uint32_t *__restrict__ ke
             }
     }
     if (blockIdx.x == 0 && threadIdx.x < n - 4 * n4) count(keys[4 * n4 + threadIdx.x]);
-    __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+    rw_pick(h, hist, st, shift);
 }
 
-// pick the digit whose cumulative count passes the wanted rank; clear the histogram for the next pass
-__global__ void k_rw_pick(uint32_t *__restrict__ hist, RwState *__restrict__ st, int shift) {
-    __shared__ uint32_t h[256];
-    const int t = threadIdx.x;
-    h[t] = hist[t];
-    hist[t] = 0u;
-    __syncthreads();
-    if (t == 0) {
-        RwState s = *st;
-        uint64_t cum = 0;
-        int d = 255;
-        for (int b = 0; b < 256; ++b) {
-            if (cum + h[b] > s.rank) {
-                d = b;
-                break;
-            }
-            cum += h[b];
-        }
-        s.rank -= cum;
-        s.prefix |= (uint32_t)d << shift;
-        s.pmask |= 255u << shift;
-        *st = s;
-    }
-}
+constexpr int kRwBlock = 1024;   // keys per block of the tie count (256 threads x 4)
 
-constexpr int kRwBlock = 1024;   // keys per block of the tie scan (256 threads x 4)
-
-// number of keys equal to the threshold per block of kRwBlock keys
+// number of keys equal to the threshold per block of kRwBlock keys (nothing reads it where every
+// such key is pruned)
 __global__ __launch_bounds__(256) void k_rw_eqcount(const uint32_t *__restrict__ keys, int64_t n,
                                                     const RwState *__restrict__ st, uint32_t *__restrict__ cnt) {
     __shared__ uint32_t tot;
+    if (st->all) return;   // uniform
     if (threadIdx.x == 0) tot = 0u;
     __syncthreads();
     const uint32_t T = st->prefix;
@@ -139,7 +194,9 @@ __global__ __launch_bounds__(256) void k_rw_eqcount(const uint32_t *__restrict__
 // thread sums a contiguous run of counts, one scan of the 1024 run sums, then each thread writes
 // its run's prefixes (integer sums: the same values in any order)
 constexpr int kRwScanThreads = 1024;
-__global__ __launch_bounds__(kRwScanThreads) void k_rw_scan(uint32_t *__restrict__ cnt, int64_t nb) {
+__global__ __launch_bounds__(kRwScanThreads) void k_rw_scan(uint32_t *__restrict__ cnt, int64_t nb,
+                                                            const RwState *__restrict__ st) {
+    if (st->all) return;   // uniform
     __shared__ uint32_t part[kRwScanThreads];
     const int t = threadIdx.x;
     const int64_t per = (nb + kRwScanThreads - 1) / kRwScanThreads;
@@ -163,109 +220,203 @@ __global__ __launch_bounds__(kRwScanThreads) void k_rw_scan(uint32_t *__restrict
     }
 }
 
-// mask[i] = key < T, or key == T and fewer than `need` equal keys precede it
-__global__ __launch_bounds__(256) void k_rw_mark(const uint32_t *__restrict__ keys, int64_t n,
-                                                 const RwState *__restrict__ st, const uint32_t *__restrict__ pre,
-                                                 uint8_t *__restrict__ mask) {
-    __shared__ uint32_t part[256];
-    const uint32_t T = st->prefix;
-    const uint64_t need = st->rank + 1;   // the wanted key is the rank-th (0-based) among those equal to T
-    const int64_t i0 = (int64_t)blockIdx.x * kRwBlock + 4 * threadIdx.x;
-    uint32_t key[4], c = 0;
-    for (int e = 0; e < 4; ++e) {
-        key[e] = i0 + e < n ? keys[i0 + e] : 0xFFFFFFFFu;
-        c += (i0 + e < n && key[e] == T) ? 1u : 0u;
-    }
-    part[threadIdx.x] = c;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const uint32_t a = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += a;
-        __syncthreads();
-    }
-    uint64_t r = (uint64_t)pre[blockIdx.x] + part[threadIdx.x] - c;   // equal keys before this thread's
-    for (int e = 0; e < 4; ++e) {
-        if (i0 + e >= n) break;
-        uint8_t mk = key[e] < T ? 1 : 0;
-        if (key[e] == T) mk = r++ < need ? 1 : 0;
-        mask[i0 + e] = mk;
-    }
-}
-
 // Regrowth, one wave per group with a pruned slot.  F <= 256 slots (up to four per lane), H <= 1024
 // features (one 32-bit word of the wave's used-feature bitmap per lane).
 constexpr int kRwWaves = 4;
-constexpr int kRwMaxF = 256;
+constexpr int kRwChunk = 1024;    // a wave moves up to 1024 weights (or velocities) at a time
+constexpr int kRwMaxRows = 64;
+// LDS words of a chunk: rows of F values at an odd number of words, at least one word apart
+constexpr int kRwChunkWords = kRwChunk + 2 * kRwMaxRows;
 
-// NPL: 64-slot words of a support (F <= 64 NPL)
-template <typename T, int NPL>
+typedef uint32_t rw_word __attribute__((may_alias));
+typedef uint16_t rw_half __attribute__((may_alias));
+template <int BYTES> struct RwVec { typedef uint32_t type __attribute__((ext_vector_type(BYTES / 4))); };
+template <> struct RwVec<4> { typedef uint32_t type; };
+template <> struct RwVec<2> { typedef uint16_t type; };
+
+// A chunk of whole label rows, VB bytes per lane and access (a row is a whole number of them)
+template <typename T, int VB> struct RwRows {
+    typedef typename RwVec<VB>::type V;
+    static constexpr int kVe = VB / (int)sizeof(T), kNv = kRwChunk / (64 * kVe);
+    V v[kNv];
+
+    static __device__ __forceinline__ int stride_words(int F) { return ((F * (int)sizeof(T) + 3) / 4 + 1) | 1; }
+
+    __device__ __forceinline__ void load(const T *p, int n, int lane) {
+#pragma unroll
+        for (int i = 0; i < kNv; ++i) {
+            const int e = kVe * (lane + 64 * i);
+            if (e < n) v[i] = *reinterpret_cast<const V *>(p + e);
+        }
+    }
+    __device__ __forceinline__ void put(uint32_t *lds, int n, int F, uint32_t magic, int lane) const {
+        const int sw = stride_words(F);
+#pragma unroll
+        for (int i = 0; i < kNv; ++i) {
+            const int e = kVe * (lane + 64 * i);
+            if (e >= n) continue;
+            const int row = (int)((uint32_t)e * magic >> 20), pos = e - row * F;
+            if constexpr (VB == 2) {
+                reinterpret_cast<rw_half *>(lds + row * sw)[pos] = v[i];
+            } else if constexpr (VB == 4) {
+                reinterpret_cast<rw_word *>(lds + row * sw)[pos * (int)sizeof(T) / 4] = v[i];
+            } else {
+#pragma unroll
+                for (int u = 0; u < VB / 4; ++u)
+                    reinterpret_cast<rw_word *>(lds + row * sw)[pos * (int)sizeof(T) / 4 + u] = v[i][u];
+            }
+        }
+    }
+    // the value of row `row`, slot j
+    static __device__ __forceinline__ void set(uint32_t *lds, int F, int row, int j, float x) {
+        if constexpr (sizeof(T) == 2) reinterpret_cast<rw_half *>(lds + row * stride_words(F))[j] = f32_to_bf16(x);
+        else reinterpret_cast<rw_word *>(lds + row * stride_words(F))[j] = __float_as_uint(x);
+    }
+    // position p of each row takes slot src[p]
+    static __device__ __forceinline__ void store(const uint32_t *lds, const uint16_t *src, T *p, int n, int F,
+                                                 uint32_t magic, int lane) {
+        const int sw = stride_words(F);
+#pragma unroll
+        for (int i = 0; i < kNv; ++i) {
+            const int e = kVe * (lane + 64 * i);
+            if (e >= n) continue;
+            const int row = (int)((uint32_t)e * magic >> 20), pos = e - row * F;
+            uint32_t x[kVe];
+#pragma unroll
+            for (int u = 0; u < kVe; ++u) {
+                const int j = src[pos + u];
+                if constexpr (sizeof(T) == 2) x[u] = reinterpret_cast<const rw_half *>(lds + row * sw)[j];
+                else x[u] = reinterpret_cast<const rw_word *>(lds + row * sw)[j];
+            }
+            V o;
+            if constexpr (VB == 2) {
+                o = (uint16_t)x[0];
+            } else if constexpr (VB == 4) {
+                if constexpr (sizeof(T) == 2) o = x[0] | x[1] << 16;
+                else o = x[0];
+            } else {
+#pragma unroll
+                for (int u = 0; u < VB / 4; ++u) {
+                    if constexpr (sizeof(T) == 2) o[u] = x[2 * u] | x[2 * u + 1] << 16;
+                    else o[u] = x[u];
+                }
+            }
+            *reinterpret_cast<V *>(p + e) = o;
+        }
+    }
+};
+
+// Bound by memory: the weights and velocities of nearly every group move once.  A group's first
+// chunk of both is requested before the draws, which are a serial chain of about 20 instructions
+// each; whole chunks of rows then pass through LDS in the widest accesses that the rows allow, the
+// pruned slots' new values written there by dense lanes.  (One row at a time, each a load, an LDS
+// write, a gather and a store that waited for each other, and draws of 45 instructions: 727 us at
+// 2.9M labels x 64, rho 0.1, of 2.26 GB moved; 410 here, 5.5 TB/s.)
+//
+// A slot is pruned if its key is below the threshold, or equal to it and among the first need keys
+// that are: cnt holds the equal keys before each block of kRwBlock, and the wave counts those between
+// its block's start and its slots (only where not all of them are pruned).
+//
+// NPL: 64-slot words of a support (F <= 64 NPL); VB, VM: bytes per access of W and of the velocity
+template <typename T, int NPL, int VB, int VM>
 __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict__ idx, T *__restrict__ W,
-                                                             float *__restrict__ mom, const uint8_t *__restrict__ mask,
-                                                             int64_t K, int G, int F, int H, int init_random,
-                                                             uint64_t seed, float scale) {
+                                                             float *__restrict__ mom, const uint32_t *__restrict__ keys,
+                                                             const RwState *__restrict__ st,
+                                                             const uint32_t *__restrict__ cnt, int64_t K, int G, int F,
+                                                             int H, int init_random, uint64_t seed, float scale,
+                                                             uint32_t fmagic) {
     __shared__ uint32_t used_s[kRwWaves][32];
     __shared__ uint32_t upre_s[kRwWaves][32];
-    __shared__ int32_t feat_s[kRwWaves][kRwMaxF];
-    __shared__ int32_t src_s[kRwWaves][kRwMaxF];
-    __shared__ uint8_t mk_s[kRwWaves][kRwMaxF];
-    __shared__ float row_s[kRwWaves][kRwMaxF];
+    __shared__ int32_t feat_s[kRwWaves][64 * NPL];
+    __shared__ __align__(16) uint16_t src_s[kRwWaves][64 * NPL];
+    __shared__ uint16_t pl_s[kRwWaves][64 * NPL];
+    __shared__ uint32_t rows_s[kRwWaves][kRwChunkWords];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t k = (int64_t)blockIdx.x * kRwWaves + wv;
     if (k >= K) return;   // wave-uniform; this kernel has no workgroup barrier
-    uint32_t *used = used_s[wv], *upre = upre_s[wv];
-    int32_t *feat = feat_s[wv], *src = src_s[wv];
-    uint8_t *mk = mk_s[wv];
-    float *row = row_s[wv];
+    uint32_t *used = used_s[wv], *upre = upre_s[wv], *rows = rows_s[wv];
+    int32_t *feat = feat_s[wv];
+    uint16_t *src = src_s[wv], *pl = pl_s[wv];
     const int64_t KF = K * F;
-
-    // the group's slots, their marks (also as one 64-bit ballot per 64 slots), and the features it
-    // keeps
-    used[lane & 31] = 0u;
     constexpr int NPW = NPL;
+
+    // the group's slots and their marks as one 64-bit ballot per 64 slots
+    used[lane & 31] = 0u;
     uint64_t pm[NPW];
+    int32_t ft[NPW];
     int n_pruned = 0;
+    const uint32_t T0 = st->prefix;
+    const bool all = st->all != 0u;
+    const uint64_t need = st->rank + 1;   // the wanted key is the rank-th (0-based) among those equal
+    bool tie = false;
 #pragma unroll
     for (int w = 0; w < NPW; ++w) {
         const int j = lane + 64 * w;
-        uint8_t m = 0;
-        if (j < F) {
-            feat[j] = idx[k * F + j];
-            m = mask[k * F + j];
-            mk[j] = m;
-        }
-        pm[w] = __builtin_amdgcn_ballot_w64(m != 0);
-        n_pruned += __popcll(pm[w]);
+        const uint32_t key = j < F ? keys[k * F + j] : 0xFFFFFFFFu;
+        ft[w] = j < F ? idx[k * F + j] : 0;
+        pm[w] = __builtin_amdgcn_ballot_w64(j < F && (key < T0 || (all && key == T0)));
+        tie |= j < F && key == T0;
     }
+    if (!all && __builtin_amdgcn_ballot_w64(tie) != 0u) {   // wave-uniform
+        const int64_t b0 = k * F / kRwBlock * kRwBlock;
+        uint64_t before = cnt[k * F / kRwBlock];
+        for (int64_t i = b0; i < k * F; i += 64)
+            before += __popcll(__builtin_amdgcn_ballot_w64(i + lane < k * F && keys[i + lane] == T0));
+        // a support may cross into later blocks: the running count goes on over its own slots
+#pragma unroll
+        for (int w = 0; w < NPW; ++w) {
+            const int j = lane + 64 * w;
+            const bool eq = j < F && keys[k * F + j] == T0;
+            const uint64_t em = __builtin_amdgcn_ballot_w64(eq);
+            const uint64_t r = before + __popcll(em & ((1ull << lane) - 1ull));
+            pm[w] |= __builtin_amdgcn_ballot_w64(eq && r < need);
+            before += __popcll(em);
+        }
+    }
+#pragma unroll
+    for (int w = 0; w < NPW; ++w) n_pruned += __popcll(pm[w]);
     if (n_pruned == 0) return;   // wave-uniform
-    for (int j = lane; j < F; j += 64)
-        if (!mk[j]) atomicOr(&used[feat[j] >> 5], 1u << (feat[j] & 31));
 
+    // rows per chunk, at most 1024 values; the first chunk is on its way during the draws
+    int R = (int)((kRwChunk * fmagic) >> 20);   // 1024 / F
+    R = R < kRwMaxRows ? R : kRwMaxRows;
+    R = R < G ? R : G;
+    T *wg = W + k * G * F;
+    float *mg = mom + k * G * F;
+    RwRows<T, VB> wr;
+    RwRows<float, VM> mr;
+    wr.load(wg, R * F, lane);
+    if (mom) mr.load(mg, R * F, lane);
+
+    // the kept features, and the list of pruned slots
+    int d0 = 0;   // pruned slots in earlier words
     // Draws, pruned slots in ascending order: the (r mod n_free)-th free feature, r the slot's
     // SplitMix64 value.  The d-th draw has n_free = H - (F - n_pruned) - d, so every draw's
     // r mod n_free is computed at once, on the lane of its slot; only the selection is sequential.
     // In 32-bit steps (n_free <= H <= 1024, so every product fits):
     //   r mod n = ((r_hi mod n) (2^32 mod n) + r_lo mod n) mod n.
     uint32_t tt[NPW];
-    {
-        int d0 = 0;   // pruned slots in earlier words
 #pragma unroll
-        for (int w = 0; w < NPW; ++w) {
-            const int j = lane + 64 * w;
-            tt[w] = 0u;
-            if ((pm[w] >> lane) & 1u) {
-                const int d = d0 + __popcll(pm[w] & ((1ull << lane) - 1ull));
-                const uint64_t r = splitmix64_at(seed, (uint64_t)(k * F + j));
-                const uint32_t nf = (uint32_t)(H - (F - n_pruned) - d);
-                const uint32_t p32 = (0xFFFFFFFFu % nf + 1u) % nf;   // 2^32 mod nf
-                tt[w] = ((uint32_t)(r >> 32) % nf * p32 % nf + (uint32_t)r % nf) % nf;
-            }
-            d0 += __popcll(pm[w]);
+    for (int w = 0; w < NPW; ++w) {
+        const int j = lane + 64 * w;
+        tt[w] = 0u;
+        if ((pm[w] >> lane) & 1u) {
+            const int d = d0 + __popcll(pm[w] & ((1ull << lane) - 1ull));
+            pl[d] = (uint16_t)j;
+            const uint64_t r = splitmix64_at(seed, (uint64_t)(k * F + j));
+            const uint32_t nf = (uint32_t)(H - (F - n_pruned) - d);
+            const uint32_t p32 = (0xFFFFFFFFu % nf + 1u) % nf;   // 2^32 mod nf
+            tt[w] = ((uint32_t)(r >> 32) % nf * p32 % nf + (uint32_t)r % nf) % nf;
+        } else if (j < F) {
+            atomicOr(&used[ft[w] >> 5], 1u << (ft[w] & 31));
         }
+        d0 += __popcll(pm[w]);
     }
     // Lane w holds the free bits of bitmap word w (words past H have none) and the inclusive
     // prefix of the free counts, scanned once; a draw removes one bit, so the lane that held it
-    // and every later prefix drop by one, with no further scan.
+    // and every later prefix drop by one, with no further scan.  The holder is the first lane whose
+    // prefix passes t, and its word's wanted bit the set one with as many set bits below it as are
+    // left to pass, which 32 lanes test at once.
     const int nw = (H + 31) >> 5;
     uint32_t freew = 0u, valid = 0u;
     if (lane < nw) {
@@ -273,37 +424,25 @@ __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict
         valid = H - lo >= 32 ? 0xFFFFFFFFu : ((1u << (H - lo)) - 1u);
         freew = ~used[lane] & valid;
     }
-    uint32_t c = __popc(freew), inc = c;
+    uint32_t inc = __popc(freew);
     for (int off = 1; off < 64; off <<= 1) {
         const uint32_t a = __shfl_up(inc, off, 64);
         if (lane >= off) inc += a;
     }
+    const uint32_t lanebit = lane < 32 ? 1u << lane : 0u;
 #pragma unroll
     for (int w = 0; w < NPW; ++w)
         for (uint64_t rem = pm[w]; rem != 0u; rem &= rem - 1u) {
             const int sl = (int)__builtin_ctzll(rem);
             const uint32_t t = __builtin_amdgcn_readlane(tt[w], sl);
-            const uint32_t before = inc - c;
-            const bool mine = before <= t && t < inc;
-            // the holder's (t - before)-th free bit: a binary search on popcounts of halves
-            uint32_t sel = mine ? t - before : 0u;
-            int pos = 0;
-#pragma unroll
-            for (int half = 16; half > 0; half >>= 1) {
-                const uint32_t cnt = __popc((freew >> pos) & ((1u << half) - 1u));
-                if (sel >= cnt) {
-                    sel -= cnt;
-                    pos += half;
-                }
-            }
-            const int holder = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(mine));
-            const int f = __builtin_amdgcn_readlane(32 * lane + pos, holder);
-            if (lane == holder) {
-                freew &= ~(1u << (f & 31));
-                --c;
-            }
+            const int holder = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(t < inc));
+            const uint32_t fw = __builtin_amdgcn_readlane(freew, holder);
+            const uint32_t left = t - (__builtin_amdgcn_readlane(inc, holder) - __popc(fw));
+            const int pos = (int)__builtin_ctzll(
+                __builtin_amdgcn_ballot_w64((fw & lanebit) != 0u && __builtin_amdgcn_mbcnt_lo(fw, 0u) == left));
+            if (lane == holder) freew &= ~(1u << pos);
             if (lane >= holder) --inc;
-            if (lane == 0) feat[64 * w + sl] = f;
+            if (lane == sl) ft[w] = 32 * holder + pos;
         }
 
     // new positions: the rank of each slot's feature among the row's features, from the final
@@ -322,33 +461,42 @@ __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict
             upre[lane] = ui - uc;
         }
     }
-    for (int j = lane; j < F; j += 64) {
-        const int f = feat[j];
+#pragma unroll
+    for (int w = 0; w < NPW; ++w) {
+        const int j = lane + 64 * w;
+        if (j >= F) continue;
+        const int f = ft[w];
         const int p = (int)(upre[f >> 5] + __popc(used[f >> 5] & ((1u << (f & 31)) - 1u)));
-        src[p] = j;
+        src[p] = (uint16_t)j;
+        feat[p] = f;
     }
-    for (int p = lane; p < F; p += 64) idx[k * F + p] = feat[src[p]];
+    for (int p = lane; p < F; p += 64) idx[k * F + p] = feat[p];
 
     // each label's weights (and velocity) follow their slots; pruned slots are reinitialised
-    for (int g = 0; g < G; ++g) {
-        const int64_t l = k * G + g;
-        for (int j = lane; j < F; j += 64) row[j] = load_f32(W, l * F + j);
-        for (int p = lane; p < F; p += 64) {
-            const int j = src[p];
-            float v = row[j];
-            if (mk[j]) {
-                v = 0.0f;
-                if (init_random) {
-                    const uint64_t n = splitmix64_at(seed, (uint64_t)(KF + l * F + j)) >> 40;
-                    v = (float)((int32_t)(2 * n) - (1 << 24)) * scale;
-                }
+    const uint32_t pmagic = ((1u << 20) + (uint32_t)n_pruned - 1u) / (uint32_t)n_pruned;
+    for (int g0 = 0; g0 < G; g0 += R) {
+        const int nr = G - g0 < R ? G - g0 : R, n = nr * F;
+        const int nx = G - g0 - nr < R ? (G - g0 - nr) * F : R * F;   // values of the next chunk
+        wr.put(rows, n, F, fmagic, lane);
+        if (nx > 0) wr.load(wg + (int64_t)(g0 + nr) * F, nx, lane);
+        for (int e = lane; e < nr * n_pruned; e += 64) {
+            const int row = (int)((uint32_t)e * pmagic >> 20), j = pl[e - row * n_pruned];
+            float v = 0.0f;
+            if (init_random) {
+                const uint64_t r = splitmix64_at(seed, (uint64_t)(KF + (k * G + g0 + row) * F + j)) >> 40;
+                v = (float)((int32_t)(2 * r) - (1 << 24)) * scale;
             }
-            store_out(W, l * F + p, v);
+            RwRows<T, VB>::set(rows, F, row, j, v);
         }
-        if (mom) {
-            for (int j = lane; j < F; j += 64) row[j] = mom[l * F + j];
-            for (int p = lane; p < F; p += 64) mom[l * F + p] = mk[src[p]] ? 0.0f : row[src[p]];
+        RwRows<T, VB>::store(rows, src, wg + (int64_t)g0 * F, n, F, fmagic, lane);
+        if (!mom) continue;   // uniform
+        mr.put(rows, n, F, fmagic, lane);
+        if (nx > 0) mr.load(mg + (int64_t)(g0 + nr) * F, nx, lane);
+        for (int e = lane; e < nr * n_pruned; e += 64) {
+            const int row = (int)((uint32_t)e * pmagic >> 20);
+            RwRows<float, VM>::set(rows, F, row, pl[e - row * n_pruned], 0.0f);
         }
+        RwRows<float, VM>::store(rows, src, mg + (int64_t)g0 * F, n, F, fmagic, lane);
     }
 }
 
@@ -356,9 +504,9 @@ __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict
 
 namespace haste {
 
-// the regrowth addresses a group's weights (and velocity) with 32-bit offsets within its block
+// 256 slots: four per lane of the regrowth; it addresses a group's weights (and velocity) with 32-bit offsets within its block
 bool rewire_supported(const TailArgs &a) {
-    return a.F_in <= kRwMaxF && a.F_s <= kMaxFs && a.G * a.F_in * 4 < ((int64_t)1 << 31);
+    return a.F_in <= 256 && a.F_s <= kMaxFs && a.G * a.F_in * 4 < ((int64_t)1 << 31);
 }
 
 static int64_t rw_blocks(const TailArgs &a) { return cdiv((a.L / a.G) * a.F_in, kRwBlock); }
@@ -374,43 +522,65 @@ hipError_t rewire(const TailArgs &a, int32_t *idx, void *W, float *m, int64_t n_
     const int64_t K = a.L / a.G, KF = K * a.F_in;
     char *p = static_cast<char *>(ws);
     uint32_t *keys = reinterpret_cast<uint32_t *>(p);
-    p += round_up(KF * 4, 256);
-    uint8_t *mask = reinterpret_cast<uint8_t *>(p);
-    p += round_up(KF, 256);
+    p += round_up(KF * 4, 256) + round_up(KF, 256);   // (the KF bytes after the keys are not used)
     uint32_t *cnt = reinterpret_cast<uint32_t *>(p);
     p += round_up(rw_blocks(a) * 4, 256);
     uint32_t *hist = reinterpret_cast<uint32_t *>(p);
     RwState *st = reinterpret_cast<RwState *>(p + 256 * 4);
     const bool bf = a.dtype == HASTE_DTYPE_BF16;
-    const dim3 g1((unsigned)cdiv(KF, 256));
-    if (bf)
-        hipLaunchKernelGGL((k_rw_scores<bf16_t>), g1, dim3(256), 0, s, (const bf16_t *)W, K, (int)a.G, (int)a.F_in, keys);
-    else
-        hipLaunchKernelGGL((k_rw_scores<float>), g1, dim3(256), 0, s, (const float *)W, K, (int)a.G, (int)a.F_in, keys);
+    const int F = (int)a.F_in;
     hipLaunchKernelGGL(k_rw_init, dim3(1), dim3(256), 0, s, hist, st, (uint64_t)(n_prune - 1));
-    const int64_t hb = cdiv(KF, 1024) < 1024 ? (cdiv(KF, 1024) < 1 ? 1 : cdiv(KF, 1024)) : 1024;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_rw_hist, dim3((unsigned)hb), dim3(256), 0, s, keys, KF, st, shift, hist);
-        hipLaunchKernelGGL(k_rw_pick, dim3(1), dim3(256), 0, s, hist, st, shift);
+    // every workgroup adds to the same few counters, one addition after the other (2.9M x 64: digits 24 us a
+    // pass with 1024 workgroups of 256 threads, 11 with 256 of 1024; scores with 2 bytes a load 300 with one
+    // workgroup per 256 slots, 120 with 1024)
+    auto blocks = [](int64_t want, int64_t most) { return want < most ? want : most; };
+    auto scores = [&](auto tag, auto ne) {
+        using T = decltype(tag);
+        constexpr int NE = decltype(ne)::value;
+        hipLaunchKernelGGL((k_rw_scores<T, NE>), dim3((unsigned)blocks(cdiv(KF / NE, 256), 1024)), dim3(256), 0, s,
+                           (const T *)W, K,
+                           (int)a.G, F, keys, hist, st);
+    };
+    if (bf) {
+        if (F % 4 == 0) scores(bf16_t{}, std::integral_constant<int, 4>{});
+        else if (F % 2 == 0) scores(bf16_t{}, std::integral_constant<int, 2>{});
+        else scores(bf16_t{}, std::integral_constant<int, 1>{});
+    } else {
+        if (F % 4 == 0) scores(float{}, std::integral_constant<int, 4>{});
+        else scores(float{}, std::integral_constant<int, 1>{});
     }
+    for (int shift = 16; shift >= 0; shift -= 8)
+        hipLaunchKernelGGL(k_rw_hist, dim3((unsigned)blocks(cdiv(KF, 4096), 256)), dim3(1024), 0, s, keys, KF, st,
+                           shift, hist);
     const int64_t nb = rw_blocks(a);
     hipLaunchKernelGGL(k_rw_eqcount, dim3((unsigned)nb), dim3(256), 0, s, keys, KF, st, cnt);
-    hipLaunchKernelGGL(k_rw_scan, dim3(1), dim3(kRwScanThreads), 0, s, cnt, nb);
-    hipLaunchKernelGGL(k_rw_mark, dim3((unsigned)nb), dim3(256), 0, s, keys, KF, st, cnt, mask);
+    hipLaunchKernelGGL(k_rw_scan, dim3(1), dim3(kRwScanThreads), 0, s, cnt, nb, st);
     const float scale = (float)(1.0 / sqrt((double)a.F_in)) * 5.9604644775390625e-08f;   // a 2^-24, exact
+    const uint32_t fmagic = ((1u << 20) + (uint32_t)F - 1u) / (uint32_t)F;   // e / F = e fmagic >> 20, e <= 1024
     const dim3 g2((unsigned)cdiv(K, kRwWaves));
-    auto regrow = [&](auto tag, auto npl) {
+    auto regrow = [&](auto tag, auto npl, auto vb, auto vm) {
         using T = decltype(tag);
-        hipLaunchKernelGGL((k_rw_regrow<T, decltype(npl)::value>), g2, dim3(64 * kRwWaves), 0, s, idx, (T *)W, m,
-                           mask, K, (int)a.G, (int)a.F_in, (int)a.F_s, init_random, seed, scale);
+        hipLaunchKernelGGL((k_rw_regrow<T, decltype(npl)::value, decltype(vb)::value, decltype(vm)::value>), g2,
+                           dim3(64 * kRwWaves), 0, s, idx, (T *)W, m, keys, st, cnt, K, (int)a.G, F, (int)a.F_s,
+                           init_random, seed, scale, fmagic);
     };
-    auto by_words = [&](auto tag) {
-        if (a.F_in <= 64) regrow(tag, std::integral_constant<int, 1>{});
-        else if (a.F_in <= 128) regrow(tag, std::integral_constant<int, 2>{});
-        else regrow(tag, std::integral_constant<int, 4>{});
+    // accesses that divide a row: 16 bytes where every row is aligned to them, else 4, else one value
+    using c16 = std::integral_constant<int, 16>;
+    using c4 = std::integral_constant<int, 4>;
+    using c2 = std::integral_constant<int, 2>;
+    auto by_access = [&](auto npl) {
+        if (bf) {
+            if (F % 8 == 0) regrow(bf16_t{}, npl, c16{}, c16{});
+            else if (F % 2 == 0) regrow(bf16_t{}, npl, c4{}, c4{});
+            else regrow(bf16_t{}, npl, c2{}, c4{});
+        } else {
+            if (F % 4 == 0) regrow(float{}, npl, c16{}, c16{});
+            else regrow(float{}, npl, c4{}, c4{});
+        }
     };
-    if (bf) by_words(bf16_t{});
-    else by_words(float{});
+    if (F <= 64) by_access(std::integral_constant<int, 1>{});
+    else if (F <= 128) by_access(std::integral_constant<int, 2>{});
+    else by_access(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 
