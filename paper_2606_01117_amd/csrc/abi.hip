@@ -143,6 +143,38 @@ hipError_t bwd_w_run(const haste::TailArgs &a, const void *X, const int32_t *idx
     return haste::bwd_w_valu(a, X, idx, dY, dW, dbias, beta, s);
 }
 
+// A call also takes the workspace that the kernels of less scratch need, and then runs those (or fewer
+// segments): programs that keep a size from before the faster kernels go on.  haste_fwd_bce's part:
+size_t bce_least_ws(const haste::TailArgs &a) {
+    if (haste::fwd_bce_mfma_supported(a, haste::kFusedPosWs)) return haste::fwd_bce_mfma_ws(a, haste::kFusedPosWs);
+    const size_t xws = bwd_w_uses_xt(a) ? haste::bwd_w_mfma_ws(a) : 0;
+    if (!haste::fwd_dn_supported(a) && !haste::fwd_sg_supported(a)) return xws;
+    return (size_t)haste::round_up((int64_t)xws, 256) + (size_t)haste::round_up(a.B * haste::kSortPosMax * 4, 256);
+}
+
+// the composed optimizer form's, without the dW behind it
+size_t sgd_least_at(const haste::TailArgs &a) { return (size_t)haste::round_up((int64_t)bce_least_ws(a), 256); }
+
+size_t sgd_least_ws(const haste::TailArgs &a) {
+    if (haste::fwd_bce_mfma_supported(a, haste::kFusedPosWs)) return bce_least_ws(a);
+    return sgd_least_at(a) + (size_t)haste::round_up(a.L * a.F_in * 4, 256);
+}
+
+// and backward-feature's: the other kernels', or what the scattered tiles of their shapes took, which holds
+// the any-group kernel's partials of fewer segments
+size_t bwd_x_least_ws(const haste::TailArgs &a) {
+    const size_t dn = haste::bwd_x_dn_shape_ws(a);
+    return dn ? dn : bwd_x_other_ws(a);
+}
+
+// A tail step's workspace: bytes of backward-feature's part, haste_fwd_bce's (or the optimizer form's,
+// which can do with `least`) behind it; -1: too small
+int64_t tail_split(const haste::TailArgs &a, size_t bytes, size_t need, size_t least) {
+    if (bytes >= need) return a.B == 0 || a.L == 0 ? 0 : haste::round_up((int64_t)bwd_x_ws(a), 256);
+    const int64_t at = haste::round_up((int64_t)bwd_x_least_ws(a), 256);
+    return bytes >= (size_t)at + least ? at : -1;
+}
+
 #define TRY(x)                      \
     do {                            \
         int _rc = (x);              \
@@ -273,14 +305,16 @@ int haste_bwd_x(const haste_desc_t *d, const int32_t *idx, const void *W, const 
     if (!haste::bwd_x_dn_supported(a) && !haste::bwd_x_sg_supported(a) && !haste::bwd_x_mfma_supported(a) &&
         !haste::valu_supported(a))
         return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
-    // a workspace of less than the queried size that another kernel can do with is still taken
-    const bool any = haste::bwd_x_any_preferred(a) && ws_bytes >= haste::bwd_x_any_ws(a);
-    const bool f32 = haste::bwd_x_f32_preferred(a) && ws_bytes >= haste::bwd_x_f32_ws(a);
-    const size_t need = any || f32 ? bwd_x_ws(a) : bwd_x_other_ws(a);
-    if (!ws || ws_bytes < need)
+    if (!ws || (ws_bytes < bwd_x_ws(a) && ws_bytes < bwd_x_least_ws(a)))
         return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", bwd_x_ws(a), ws ? ws_bytes : 0);
     TRY(need_ptr(ws, "ws"));
-    if (any) return hip_status(haste::bwd_x_any(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
+    // with less than the queried size: the other kernel, where it can do with it
+    const bool any = haste::bwd_x_any_preferred(a) &&
+                     (ws_bytes >= haste::bwd_x_any_ws(a) || ws_bytes < bwd_x_other_ws(a));
+    const bool f32 = haste::bwd_x_f32_preferred(a) && ws_bytes >= haste::bwd_x_f32_ws(a);
+    if (any ? !haste::bwd_x_any_fits(a, ws_bytes) : !f32 && ws_bytes < bwd_x_other_ws(a))
+        return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", bwd_x_ws(a), ws_bytes);
+    if (any) return hip_status(haste::bwd_x_any(a, idx, W, dY, dX, beta, ws, ws_bytes, s), "haste_bwd_x");
     if (f32) return hip_status(haste::bwd_x_f32(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_dn_supported(a)) return hip_status(haste::bwd_x_dn(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
     if (haste::bwd_x_sg_supported(a)) return hip_status(haste::bwd_x_sg(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
@@ -297,9 +331,10 @@ int haste_tail_step(const haste_desc_t *d, const void *X, const int32_t *idx, co
     if (P < 0) return fail(HASTE_ERR_INVALID, "P must be >= 0");
     const haste::TailArgs a = targs(d);
     const size_t need = haste_workspace_bytes(d, HASTE_OP_TAIL_STEP);
-    if (need && (!ws || ws_bytes < need))
+    const int64_t split = need ? tail_split(a, ws ? ws_bytes : 0, need, bce_least_ws(a)) : 0;
+    if (split < 0)
         return fail(HASTE_ERR_WORKSPACE, "haste_tail_step needs %zu workspace bytes, got %zu", need, ws ? ws_bytes : 0);
-    const size_t xoff = (size_t)haste::round_up((int64_t)haste_workspace_bytes(d, HASTE_OP_BWD_X), 256);
+    const size_t xoff = (size_t)split;
     if (a.L > 0 && a.B > 0 && dW && dX && haste::tail_step_fused(a, P) && ws_bytes >= haste::tail_step_ws(a, P)) {
         TRY(need_ptr(X, "X"));
         TRY(need_ptr(idx, "idx"));
@@ -364,7 +399,7 @@ int haste_fwd_bce(const haste_desc_t *d, const void *X, const int32_t *idx, cons
     // separate gradient pass computes), given each row's positives sorted after the X^T copy
     const size_t spos_at = (size_t)haste::round_up((int64_t)need, 256);
     hipError_t e = hipSuccess;
-    if (fwd_small_bce(a, P) && ws && ws_bytes >= spos_at + (size_t)a.B * P * 4) {
+    if (fwd_small_bce(a, P) && ws && aligned16(ws) && ws_bytes >= spos_at + (size_t)a.B * P * 4) {
         int32_t *spos = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + spos_at);
         if (P > 0) e = haste::sort_positives(a.B, a.L, pos, P, spos, s);
         // with no positives the kernels never read the list, but need a non-null one to form the gradient
@@ -435,8 +470,10 @@ int haste_fwd_bce_sgd(const haste_desc_t *d, const void *X, const int32_t *idx, 
     // 64); others keep dW in the workspace too
     const bool fused_shape = haste::fwd_bce_mfma_supported(a, P);
     // composed: haste_fwd_bce's region (the X^T copy and sorted positives), then dW
-    const size_t xws = (size_t)haste::round_up((int64_t)haste_workspace_bytes(d, HASTE_OP_FWD_BCE), 256);
-    const size_t need = fused_shape ? haste::fwd_bce_mfma_ws(a, P) : xws + (size_t)haste::round_up(a.L * a.F_in * 4, 256);
+    const size_t dws = (size_t)haste::round_up(a.L * a.F_in * 4, 256);
+    size_t xws = (size_t)haste::round_up((int64_t)haste_workspace_bytes(d, HASTE_OP_FWD_BCE), 256);
+    if (ws_bytes < xws + dws) xws = sgd_least_at(a);
+    const size_t need = fused_shape ? haste::fwd_bce_mfma_ws(a, P) : xws + dws;
     if (a.B == 0) {  // no rows: a zero gradient, the step still decays the velocity and the weights
         if (dbias) TRY(hip_status(haste::fill_f32(dbias, a.L, 0.0f, s), "haste_fwd_bce_sgd"));
         return hip_status(haste::sgd_momentum(a.L * a.F_in, a.dtype, W, nullptr, m, *opt, W_next, s),
@@ -618,10 +655,10 @@ int haste_tail_step_sgd(const haste_desc_t *d, const void *X, const int32_t *idx
     if (P < 0) return fail(HASTE_ERR_INVALID, "P must be >= 0");
     const haste::TailArgs a = targs(d);
     const size_t need = haste_workspace_bytes(d, HASTE_OP_TAIL_STEP_SGD);
-    if (need && (!ws || ws_bytes < need))
-        return fail(HASTE_ERR_WORKSPACE, "haste_tail_step_sgd needs %zu workspace bytes, got %zu", need,
-                    ws ? ws_bytes : 0);
-    const size_t xoff = (size_t)haste::round_up((int64_t)haste_workspace_bytes(d, HASTE_OP_BWD_X), 256);
+    const int64_t split = need ? tail_split(a, ws ? ws_bytes : 0, need, sgd_least_ws(a)) : 0;
+    if (split < 0)
+        return fail(HASTE_ERR_WORKSPACE, "haste_tail_step_sgd needs %zu workspace bytes, got %zu", need, ws ? ws_bytes : 0);
+    const size_t xoff = (size_t)split;
     if (a.L > 0 && a.B > 0 && dX && haste::tail_step_fused(a, P) && ws_bytes >= haste::tail_step_ws(a, P)) {
         TRY(need_ptr(X, "X"));
         TRY(need_ptr(idx, "idx"));

@@ -263,6 +263,7 @@ hipError_t bwd_x_sg(const TailArgs &a, const int32_t *idx, const void *W, const 
 // 32-label step's weights scattered into an LDS tile
 bool bwd_x_dn_supported(const TailArgs &a);
 size_t bwd_x_dn_ws(const TailArgs &a);
+size_t bwd_x_dn_shape_ws(const TailArgs &a);   // also where another kernel is the faster one; 0: not its shapes
 hipError_t bwd_x_dn(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
                     hipStream_t s);
 // the same product for groups of any size and supports of any width, the tiles written by producer
@@ -270,8 +271,9 @@ hipError_t bwd_x_dn(const TailArgs &a, const int32_t *idx, const void *W, const 
 bool bwd_x_any_supported(const TailArgs &a);
 bool bwd_x_any_preferred(const TailArgs &a);
 size_t bwd_x_any_ws(const TailArgs &a);
+bool bwd_x_any_fits(const TailArgs &a, size_t ws_bytes);   // possibly with fewer segments
 hipError_t bwd_x_any(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
-                     hipStream_t s);
+                     size_t ws_bytes, hipStream_t s);
 // forward on the same tiles; spos as in fwd_sg
 bool fwd_any_supported(const TailArgs &a);
 bool fwd_any_preferred(const TailArgs &a);

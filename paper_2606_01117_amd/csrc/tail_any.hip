@@ -4,8 +4,10 @@
 
 namespace haste {
 
-hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s);
-hipError_t bwd_x_any_2_12(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s);
+hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part,
+                           size_t ws_bytes, hipStream_t s);
+hipError_t bwd_x_any_2_12(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part,
+                           size_t ws_bytes, hipStream_t s);
 
 hipError_t fwd_any_48(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
                       const int32_t *spos, int P, hipStream_t s);
@@ -46,9 +48,13 @@ hipError_t fwd_any(const TailArgs &a, const void *X, const int32_t *idx, const v
 // offset (the loads run five steps past a segment's end); the group of a label by multiply-high.
 bool bwd_x_any_supported(const TailArgs &a) {
     if (a.dtype != HASTE_DTYPE_BF16 || a.F_s > kMaxFs || a.L * 128 >= ((int64_t)1 << 31)) return false;
-    const AxGeom g = ax_geom(a);
+    return bwd_x_any_fits(a, SIZE_MAX);
+}
+
+bool bwd_x_any_fits(const TailArgs &a, size_t ws_bytes) {
+    const AxGeom g = ax_geom(a, ws_bytes);
     const int64_t far = g.lps + 256;
-    return g.ni != 0 && far * a.F_in * 4 < ((int64_t)1 << 31) && (far + a.G) * a.G < ((int64_t)1 << 32);
+    return g.ni != 0 && g.nseg != 0 && far * a.F_in * 4 < ((int64_t)1 << 31) && (far + a.G) * a.G < ((int64_t)1 << 32);
 }
 
 // Where another kernel takes the layer too, measured per call at F_s = 768 (us; 328K labels):
@@ -79,11 +85,11 @@ size_t bwd_x_any_ws(const TailArgs &a) {
 }
 
 hipError_t bwd_x_any(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta, void *ws,
-                     hipStream_t s) {
-    const AxGeom g = ax_geom(a);
+                     size_t ws_bytes, hipStream_t s) {
+    const AxGeom g = ax_geom(a, ws_bytes);
     float *part = reinterpret_cast<float *>(ws);
-    const hipError_t e = g.mt == 2    ? bwd_x_any_2_12(a, idx, W, dY, part, s)
-                         : g.nft == 8 ? bwd_x_any_4_8(a, idx, W, dY, part, s)
+    const hipError_t e = g.mt == 2    ? bwd_x_any_2_12(a, idx, W, dY, part, ws_bytes, s)
+                         : g.nft == 8 ? bwd_x_any_4_8(a, idx, W, dY, part, ws_bytes, s)
                                       : AxRun<4, 12>{a, g, idx, W, dY, part, s}.run();
     if (e != hipSuccess) return e;
     return reduce_fmajor(part, (int)g.nseg, g.nbt * 16 * g.mt, a.B, a.F_s, dX, beta, s);

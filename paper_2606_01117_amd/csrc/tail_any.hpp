@@ -624,7 +624,8 @@ struct AxGeom {
     size_t lds;
 };
 
-inline AxGeom ax_geom(const haste::TailArgs &a) {
+// ws_bytes: of the partials; fewer segments where it holds no more (0 segments: not even a few)
+inline AxGeom ax_geom(const haste::TailArgs &a, size_t ws_bytes = SIZE_MAX) {
     AxGeom g;
     g.mt = a.B > 32 ? 4 : 2;
     g.nbt = (int)haste::cdiv(a.B, 16 * g.mt);
@@ -643,7 +644,9 @@ inline AxGeom ax_geom(const haste::TailArgs &a) {
     int64_t nseg = haste::round_up(haste::cdiv(kXcds * kCusPerXcd, g.nbt * g.nsplit), kXcds);
     const int64_t max_seg = haste::round_up(haste::cdiv(a.L, 256), kXcds);
     g.nseg = nseg < max_seg ? nseg : max_seg;
-    g.lps = haste::round_up(haste::cdiv(a.L, g.nseg), 64);
+    const size_t fit = ws_bytes / ((size_t)a.F_s * (size_t)(g.nbt * 16 * g.mt) * 4);
+    if (fit < (size_t)g.nseg) g.nseg = (int64_t)fit / kXcds * kXcds;
+    g.lps = g.nseg ? haste::round_up(haste::cdiv(a.L, g.nseg), 64) : 0;
     g.lds = (size_t)ax_lds(16 * kAxCons * g.nft, g.mt);
     return g;
 }

@@ -3,8 +3,9 @@
 
 namespace haste {
 
-hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part, hipStream_t s) {
-    const AxGeom g = ax_geom(a);
+hipError_t bwd_x_any_4_8(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *part,
+                           size_t ws_bytes, hipStream_t s) {
+    const AxGeom g = ax_geom(a, ws_bytes);
     return AxRun<4, 8>{a, g, idx, W, dY, part, s}.run();
 }
 

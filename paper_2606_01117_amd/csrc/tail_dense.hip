@@ -932,12 +932,20 @@ namespace haste {
 // fill the LDS); dY rows dword-aligned (L even) and a workgroup's rows within the 31-bit range of a buffer offset;
 // a segment's weight and support offsets within that range too.
 bool bwd_x_dn_supported(const TailArgs &a) {
-    if (a.dtype != HASTE_DTYPE_BF16 || a.G != 1) return false;
-    if (!(a.F_in == 32 || a.F_in == 64 || (a.F_in == 128 && a.B <= 32))) return false;
+    return a.G == 1 && (a.F_in != 128 || a.B <= 32) && bwd_x_dn_shape_ws(a) != 0;
+}
+
+// partials of the shapes for which the tiles were the kernel of groups of up to 8 labels: a workspace of
+// this size is enough for the faster kernel as well
+static bool dn_shape(const TailArgs &a) {
+    if (a.dtype != HASTE_DTYPE_BF16 || !(a.G == 1 || a.G == 2 || a.G == 4 || a.G == 8)) return false;
+    if (!(a.F_in == 32 || a.F_in == 64 || a.F_in == 128)) return false;
     if (a.F_s <= 0 || a.L % 2 != 0 || a.L * 64 * 2 >= ((int64_t)1 << 31)) return false;
     const DnGeom g = dn_geom(a);
     return g.nft != 0 && g.lds <= 160 * 1024 && (g.lps + 1024) * a.F_in * 4 < ((int64_t)1 << 31);
 }
+
+size_t bwd_x_dn_shape_ws(const TailArgs &a) { return dn_shape(a) ? bwd_x_dn_ws(a) : 0; }
 
 size_t bwd_x_dn_ws(const TailArgs &a) {
     const DnGeom g = dn_geom(a);

@@ -206,3 +206,59 @@ def test_f32_not_finite():
     bad = torch.zeros((B, F_s), dtype=torch.bool, device="cuda")
     bad[5, sup[100]] = True
     assert torch.equal(~torch.isfinite(dX), bad)
+
+
+# layers whose queried workspace grew with these kernels: shape, dtype, and the bytes that the calls
+# (haste_bwd_x, haste_tail_step, haste_tail_step_sgd) took before, which they still take
+SCRATCH = [
+    ((128, 512, 55848, 8, 128), synth.DT_BF16, (16777216, 17039616, 45633792)),
+    ((64, 384, 36396, 4, 128), synth.DT_BF16, (12582912, 12697856, 31332608)),
+    ((33, 768, 114792, 8, 15), synth.DT_BF16, (50331904, 50331904, 57219584)),
+    ((256, 256, 24880, 2, 256), synth.DT_BF16, (16777472, 16777472, 42254592)),
+    ((128, 298, 60816, 16, 256), synth.DT_BF16, (19529984, 19529984, 81805568)),
+    ((1, 384, 436416, 32, 128), synth.DT_F32, (25166080, 25166080, 248611072)),
+]
+
+
+@pytest.mark.parametrize("shape,dtype,least", SCRATCH)
+def test_scratch_limits(shape, dtype, least):
+    """With the smaller workspace: the results of the queried one (in another order of the fp32 sums, by another
+    kernel or with fewer segments), and not a byte written behind it."""
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    f32 = dtype == synth.DT_F32
+    say("scratch", shape, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    r = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    cast = (lambda t: t) if f32 else (lambda t: t.bfloat16())
+    idx = torch.rand((L // G, F_s), device="cuda", generator=gen).argsort(1)[:, :F_in].sort(1).values.int().contiguous()
+    X, W, dY0, m0 = cast(r(B, F_s)), cast(r(L, F_in) / F_in ** 0.5), cast(r(B, L)), r(L, F_in)
+    pos = torch.randint(0, L, (B, 5), device="cuda", generator=gen).int()
+    desc = hs.make_desc(B, F_s, L, G, F_in, dtype)
+    opt = hs.sgd_opts(0.1, 0.9, 1e-4)
+
+    def bwd_x(ws):
+        dX = torch.ones((B, F_s), device="cuda")
+        hs.haste_bwd_x(desc, idx, W, dY0, dX, 1, ws)
+        return [dX]
+
+    def step(ws):
+        dY, dW, dX = torch.empty_like(dY0), torch.empty_like(m0), torch.empty((B, F_s), device="cuda")
+        hs.haste_tail_step(desc, X, idx, W, None, pos, dY, dW, None, 0, dX, 0, ws)
+        return [dY.float(), dW, dX]
+
+    def sgd(ws):
+        dY, m, dX, Wn = torch.empty_like(dY0), m0.clone(), torch.empty((B, F_s), device="cuda"), torch.empty_like(W)
+        hs.haste_tail_step_sgd(desc, X, idx, W, None, pos, dY, None, opt, m, Wn, dX, 0, ws)
+        return [dY.float(), m, dX]
+
+    for call, op, n in zip((bwd_x, step, sgd), (hs.HASTE_OP_BWD_X, hs.HASTE_OP_TAIL_STEP, hs.HASTE_OP_TAIL_STEP_SGD), least):
+        ref = call(hs.workspace(hs.haste_workspace_bytes(desc, op)))
+        room = torch.full((n + 4096,), 0xa5, dtype=torch.uint8, device="cuda")
+        got = call(room[:n])
+        assert bool((room[n:] == 0xa5).all())
+        for a, b in zip(got, ref):
+            assert rel_err(a.cpu(), b.cpu()) < (1e-5 if f32 else SUM_TOL)
+        with pytest.raises(Exception):
+            call(room[:256])
