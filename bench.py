@@ -57,13 +57,14 @@ CALL_KERNELS = {
     "head_bce": ["k_bce_grad"],
     "bwd_w": ["k_transpose_x", "k_bwd_w"],
     "bwd_x": ["k_transpose_w", "k_bwd_x", "k_reduce_fmajor"],
-    # the head's GEMM kernels by operand layout and epilogue (three tile sizes: 256, 128, fallback)
-    "head_fwd": [r"k_gemm4<\d+, true, true, 0>", "k_gemm2<true, true, 0>", "k_gemm_bf16<true, true, 0>"],
+    # the head's GEMM kernels by operand layout and epilogue (256, 128 and 32 tiles, and the fallback)
+    "head_fwd": [r"k_gemm4<\d+, true, true, 0>", "k_gemm2<true, true, 0>", "k_gemm_bf16<true, true, 0>",
+                 "k_gemm_dir<true, true, 0,"],
     # the large-tile kernel with the loss gradient in its epilogue (other shapes run head_fwd's kernels)
-    "head_fwd_bce": [r"k_gemm4<\d+, true, true, 3>"],
+    "head_fwd_bce": [r"k_gemm4<\d+, true, true, 3>", "k_gemm_dir<true, true, 3,"],
     "head_bwd": [r"k_gemm4<\d+, false, false, 1>", r"k_gemm4<\d+, true, false, 2>", "k_gemm2<false, false, 1>",
                  "k_gemm2<true, false, 2>", "k_gemm_bf16<false, false, 1>", "k_gemm_bf16<true, false, 2>",
-                 "k_reduce_rmajor"],
+                 "k_gemm_dir<false, false, 1,", "k_gemm_dir<true, false, 2,", "k_reduce_rmajor"],
 }
 
 
@@ -136,7 +137,9 @@ CALL_FILES = {
 
 # a tail call runs, depending on the layer's shape, kernels of any of the tail files, and the
 # fixed-order reductions of util.hip
-TAIL_FILES = ["tail_mfma.hip", "tail_sg.hip", "tail_dense.hip", "tail_valu.hip", "util.hip"]
+TAIL_FILES = ["tail_mfma.hip", "tail_sg.hip", "tail_dense.hip", "tail_valu.hip", "tail_f32.hip", "tail_any.hpp",
+              "tail_any.hip", "tail_any_4_8.hip", "tail_any_2_12.hip", "tail_any_fwd_48.hip", "tail_any_fwd_32.hip",
+              "util.hip"]
 
 
 def kernel_source_hash(call=None):
