@@ -42,9 +42,11 @@ constexpr int kAxStageRow = 80;                   // bytes per staged dY row: 32
 // and their step is long enough to cover a load's latency)
 __host__ __device__ constexpr int ax_ring(int ni) { return ni <= 8 ? 3 : 1; }
 
-// three tiles of 64-byte rows, three staged dY steps, and a spare cell for writes of no slot (cheaper
-// than lane masks around the writes: 196 against 201 us on 655K labels in groups of 4)
+// three tiles of 64-byte rows, three staged dY steps, and 64 bytes: a spare cell for writes of no slot
+// (cheaper than lane masks around the writes: 196 against 201 us on 655K labels in groups of 4), and at
+// kAxBad one bit per row whose dY is not finite somewhere
 __host__ __device__ constexpr int ax_lds(int fr, int mt) { return 3 * fr * 64 + 3 * 16 * mt * kAxStageRow + 64; }
+constexpr int kAxBad = 32;
 
 // How dY rows (8 labels per lane) and weight pairs are read: 16 bytes and a dword where dY's rows
 // are 16-byte aligned (L a multiple of 8) and F_in is even; dwords where L and F_in are even; 2
@@ -198,6 +200,51 @@ struct AxTiles {
     }
 };
 
+// All threads of the workgroup: adds to its stored partial pp[f][row] the products of the elements of dY
+// that are not finite, of the marked rows.  32 rows at a time sum in LDS (the tiles' space); a wave takes
+// every eighth run of 64 labels.
+template <int MT, int FR>
+__device__ __forceinline__ void ax_add_not_finite(const int32_t *idx, const bf16_t *W, const bf16_t *dY, float *pp, char *lds,
+                                                  int b0, int Bp, int nf, int f0, int64_t L, int G, int F_in,
+                                                  int64_t l_begin, int64_t l_end, const uint32_t *bad) {
+    float *sum = reinterpret_cast<float *>(lds);   // [32 rows][FR]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int r0 = 0; r0 < 16 * MT; r0 += 32) {
+        const uint32_t mask = bad[r0 >> 5];
+        if (mask == 0u) continue;                 // workgroup-uniform
+        for (int e = tid; e < 32 * FR; e += kAxThreads) sum[e] = 0.0f;
+        __syncthreads();
+        for (uint32_t m = mask; m != 0u; m &= m - 1u) {
+            const int r = __builtin_ctz(m);
+            const bf16_t *y = dY + (int64_t)(b0 + r0 + r) * L;
+            for (int64_t l0 = l_begin + 64 * wave; l0 < l_end; l0 += kAxThreads) {
+                const bf16_t v = l0 + lane < l_end ? y[l0 + lane] : (bf16_t)0;
+                for (uint64_t at = __ballot((v & 0x7f80) == 0x7f80); at != 0u; at &= at - 1u) {
+                    const int j = (int)__builtin_ctzll(at);
+                    const int64_t l = l0 + j;
+                    const float yv = bf16_to_f32((bf16_t)__builtin_amdgcn_readlane((int)v, j));
+                    for (int t = lane; t < F_in; t += 64) {
+                        const int f = idx[l / G * F_in + t] - f0;
+                        if (f >= 0 && f < nf) atomicAdd(&sum[r * FR + f], yv * bf16_to_f32(W[l * F_in + t]));
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        for (int e = tid; e < 32 * nf; e += kAxThreads) {
+            const int r = e & 31, f = e >> 5;
+            if ((mask >> r) & 1u) pp[(size_t)f * Bp + r0 + r] += sum[r * FR + f];
+        }
+        __syncthreads();
+    }
+}
+
+// An empty cell of the tile contributes dY times zero, which is zero only for finite dY.  So an infinity
+// or a NaN of dY is staged as zero and its row marked, and in a workgroup with marked rows all waves go
+// over those rows of dY once more and add each such element's own products, feature by feature.  What
+// they sum to is an infinity or a NaN in any order.  (The test costs a producer lane 11 instructions a
+// step.)
+//
 // MT: 16-row tiles per workgroup.  NFT: 16-feature tiles per consumer wave (tiles w, w + 4, ...).
 // PK: labels per tile write.  NI: slot pairs per producer lane and step (32 / PK packs of
 // ceil(F_in / 2) pairs over 256 lanes).  READ: as above.  The workgroup covers features f0 .. f0 +
@@ -233,7 +280,10 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
     const uint32_t lbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)ax;
     const uint32_t sbase = lbase + 3 * TB;
     for (int e = tid; e < 3 * TB / 16; e += kAxThreads) *(lds_u32x4_t *)(uintptr_t)(lbase + 16 * e) = u32x4_t{0u, 0u, 0u, 0u};
+    uint32_t *bad = reinterpret_cast<uint32_t *>(ax + 3 * TB + 3 * SB + kAxBad);   // [2]: one bit per row
+    if (tid < 2) bad[tid] = 0u;
     __syncthreads();                              // tiles zeroed
+    const int rows = B - b0 < RW ? B - b0 : RW;
 
     if (wave >= kAxCons) {
         // ---- producers ----
@@ -241,7 +291,6 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
         using Tiles = AxTiles<PK, NI, READ, FR, true>;
         const Tiles tl(idx, W, l_begin, l_end, G, gmul, F_in, f0, lbase, lbase + 3 * TB + 3 * SB, pt);
         // dY: lane -> row pt / 4 of 64 (MT = 2: row pt / 4 of 32, lanes past them none), 8 labels
-        const int rows = B - b0 < RW ? B - b0 : RW;
         const int dr = pt >> 2, dp = pt & 3;
         const bool ylane = dr < RW;
         const Buf dseg(dY + (int64_t)b0 * L, (uint32_t)((int64_t)rows * L * 2));
@@ -260,7 +309,19 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
         };
         uint32_t ca[3][NI];                       // cells written, to be cleared three steps later
         auto stage_y = [&](const Slot &r, int sb) __attribute__((always_inline)) {
-            if (ylane) *(lds_u32x4_t *)(uintptr_t)(yst + (uint32_t)(sb * SB)) = r.y;
+            u32x4_t v = r.y;
+            uint32_t top = 0u;                    // bit 15 or 31 of a dword: that half's exponent is all ones
+#pragma unroll
+            for (int k = 0; k < 4; ++k) top |= (v[k] & 0x7fff7fffu) + 0x00800080u;
+            if (top & 0x80008000u) {              // (rows past the batch are zero)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t t = ((v[k] & 0x7fff7fffu) + 0x00800080u) & 0x80008000u;
+                    v[k] &= ~((t >> 15) * 0xffffu);
+                }
+                atomicOr(&bad[dr >> 5], 1u << (dr & 31));
+            }
+            if (ylane) *(lds_u32x4_t *)(uintptr_t)(yst + (uint32_t)(sb * SB)) = v;
         };
 #pragma unroll
         for (int k = 0; k < 3; ++k) tl.no_cells(ca[k]);
@@ -293,72 +354,74 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
             if (t + 2 >= n) break;
             interval(t + 2, std::integral_constant<int, 2>{});
         }
-        return;
-    }
-
-    // ---- consumers ----
-    __builtin_amdgcn_s_setprio(2);
-    f32x4_t acc[MT][NFT];
+    } else {
+        // ---- consumers ----
+        __builtin_amdgcn_s_setprio(2);
+        f32x4_t acc[MT][NFT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+        for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int i = 0; i < NFT; ++i) acc[m][i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    // A rows 16 m + l16, labels 8q .. 8q + 7 of the step; B rows 16 (wave + 4 i) + l16, chunk q
-    const uint32_t aoff = sbase + (uint32_t)(l16 * kAxStageRow + 16 * q);
-    const uint32_t boff = lbase + (uint32_t)(wave * 1024 + l16 * 64 + ((q ^ ((l16 >> 2) & 3)) << 4));
-    constexpr int PD = 3, SC = 1024 * kAxCons;    // feature tiles read ahead; bytes from one to the next
-    static_assert(NFT >= PD && 2 * NFT % 4 == 0, "ring of four operands over two steps");
-    bf16x8_t oa[2][MT], ob[4];
-    auto read_a = [&](uint32_t a, bf16x8_t (&o)[MT]) __attribute__((always_inline)) {
+            for (int i = 0; i < NFT; ++i) acc[m][i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        // A rows 16 m + l16, labels 8q .. 8q + 7 of the step; B rows 16 (wave + 4 i) + l16, chunk q
+        const uint32_t aoff = sbase + (uint32_t)(l16 * kAxStageRow + 16 * q);
+        const uint32_t boff = lbase + (uint32_t)(wave * 1024 + l16 * 64 + ((q ^ ((l16 >> 2) & 3)) << 4));
+        constexpr int PD = 3, SC = 1024 * kAxCons;    // feature tiles read ahead; bytes from one to the next
+        static_assert(NFT >= PD && 2 * NFT % 4 == 0, "ring of four operands over two steps");
+        bf16x8_t oa[2][MT], ob[4];
+        auto read_a = [&](uint32_t a, bf16x8_t (&o)[MT]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int m = 0; m < MT; ++m) o[m] = *(lds_bf16x8_t *)(uintptr_t)(a + 16 * m * kAxStageRow);
-    };
-    int sl3 = 0;                                  // the step's tile and stage
-    __syncthreads();                              // step 0 in its tile
-    read_a(aoff, oa[0]);
+            for (int m = 0; m < MT; ++m) o[m] = *(lds_bf16x8_t *)(uintptr_t)(a + 16 * m * kAxStageRow);
+        };
+        int sl3 = 0;                                  // the step's tile and stage
+        __syncthreads();                              // step 0 in its tile
+        read_a(aoff, oa[0]);
 #pragma unroll
-    for (int i = 0; i < PD; ++i) ob[i] = *(lds_bf16x8_t *)(uintptr_t)(boff + SC * i);
-    auto step = [&](auto pc) __attribute__((always_inline)) {
-        constexpr int P = decltype(pc)::value;
-        const uint32_t bcur = boff + (uint32_t)(sl3 * TB);
-        const int nx = sl3 == 2 ? 0 : sl3 + 1;
-        const uint32_t bnext = boff + (uint32_t)(nx * TB);
+        for (int i = 0; i < PD; ++i) ob[i] = *(lds_bf16x8_t *)(uintptr_t)(boff + SC * i);
+        auto step = [&](auto pc) __attribute__((always_inline)) {
+            constexpr int P = decltype(pc)::value;
+            const uint32_t bcur = boff + (uint32_t)(sl3 * TB);
+            const int nx = sl3 == 2 ? 0 : sl3 + 1;
+            const uint32_t bnext = boff + (uint32_t)(nx * TB);
+#pragma unroll
+            for (int i = 0; i < NFT; ++i) {
+                if (i == NFT - PD) {
+                    // The next step is in its tile.  The reads of this one's need not have returned: its
+                    // tile is written again two barriers on, when its products have been issued.
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    read_a(aoff + (uint32_t)(nx * SB), oa[1 - P]);
+                }
+                ob[(P * NFT + i + PD) & 3] = i + PD < NFT ? *(lds_bf16x8_t *)(uintptr_t)(bcur + SC * (i + PD))
+                                                          : *(lds_bf16x8_t *)(uintptr_t)(bnext + SC * (i + PD - NFT));
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+                    acc[m][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oa[P][m], ob[(P * NFT + i) & 3], acc[m][i], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            sl3 = nx;
+        };
+        for (int t = 0; t < n; t += 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
+        }
+        // partial dX^T of the segment: lane (l16, q) of feature tile ft holds feature 16 ft + l16, rows
+        // 16 m + 4q .. + 3
 #pragma unroll
         for (int i = 0; i < NFT; ++i) {
-            if (i == NFT - PD) {
-                // The next step is in its tile.  The reads of this one's need not have returned: its
-                // tile is written again two barriers on, when its products have been issued.
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                read_a(aoff + (uint32_t)(nx * SB), oa[1 - P]);
+            const int f = 16 * (wave + kAxCons * i) + l16;
+            if (f < nf) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+                    *reinterpret_cast<float4 *>(pp + (size_t)f * Bp + 16 * m + 4 * q) =
+                        make_float4(acc[m][i][0], acc[m][i][1], acc[m][i][2], acc[m][i][3]);
             }
-            ob[(P * NFT + i + PD) & 3] = i + PD < NFT ? *(lds_bf16x8_t *)(uintptr_t)(bcur + SC * (i + PD))
-                                                      : *(lds_bf16x8_t *)(uintptr_t)(bnext + SC * (i + PD - NFT));
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                acc[m][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oa[P][m], ob[(P * NFT + i) & 3], acc[m][i], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        sl3 = nx;
-    };
-    for (int t = 0; t < n; t += 2) {
-        step(std::integral_constant<int, 0>{});
-        step(std::integral_constant<int, 1>{});
-    }
-    // partial dX^T of the segment: lane (l16, q) of feature tile ft holds feature 16 ft + l16, rows
-    // 16 m + 4q .. + 3
-#pragma unroll
-    for (int i = 0; i < NFT; ++i) {
-        const int f = 16 * (wave + kAxCons * i) + l16;
-        if (f < nf) {
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                *reinterpret_cast<float4 *>(pp + (size_t)f * Bp + 16 * m + 4 * q) =
-                    make_float4(acc[m][i][0], acc[m][i][1], acc[m][i][2], acc[m][i][3]);
         }
     }
+    __syncthreads();                              // partial stored, rows marked
+    if ((bad[0] | bad[1]) != 0u)                  // workgroup-uniform
+        ax_add_not_finite<MT, FR>(idx, W, dY, pp, ax, b0, Bp, nf, f0, L, G, F_in, l_begin, l_end, bad);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -139,6 +139,42 @@ def test_fwd_not_finite(shape):
     assert close_bf16(torch.where(touched, 0, Y.double()), torch.where(touched, 0, ref), float(ref.abs().max()))
 
 
+# groups that the accumulator kernel took (16 and 32 labels), any other group, odd widths and labels, two feature
+# shares, and both widths of 64-row tiles; 32- and 64-row tiles, and a segment of more than one step
+@pytest.mark.parametrize("shape", [(64, 768, 32 * 150, 32, 64), (70, 768, 16 * 81, 16, 200), (33, 768, 1027, 1, 63), (20, 300, 24 * 131, 24, 48),
+                                   (130, 896, 35 * 30, 35, 181), (300, 384, 2048, 64, 256), (128, 768, 4096, 4, 64)])
+def test_bwd_x_not_finite(shape):
+    """An infinity or a NaN in dY reaches the features of its label's support, and no others: one element, several
+    of a row in one group and in several, both infinities at once, an infinity that meets a zero weight, the
+    last row and label, and a whole row."""
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    say("bwd_x_not_finite", shape)
+    X, idx, W, dY, sup, Wd = layer(shape, 8)
+    inf, nan = float("inf"), float("nan")
+    W[L // 3, F_in // 2] = 0.0
+    Wd[L // 3, sup[L // 3, F_in // 2]] = 0.0
+    for b, l, v in [(3, 0, inf), (3, 1, inf), (3, L // 2, -inf), (B // 2, L // 3, -inf), (B - 1, L - 1, nan), (B - 1, 5, inf)]:
+        dY[b, l] = v
+    dY[7] = nan
+    desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_BF16)
+    ws = hs.workspace(hs.haste_workspace_bytes(desc, hs.HASTE_OP_BWD_X))
+    ws.fill_(0xff)
+    dX = torch.ones((B, F_s), device="cuda")
+    hs.haste_bwd_x(desc, idx, W, dY, dX, 1, ws)
+    bad = ~torch.isfinite(dY)
+    ref = torch.where(bad, 0, dY).double() @ Wd + 1.0
+    for b, l in bad.nonzero().tolist():
+        if b != 7:
+            ref[b, sup[l]] += dY[b, l].double() * W[l].double()
+    ref[7, sup.unique()] = nan
+    assert torch.equal(torch.isnan(dX), torch.isnan(ref)) and torch.equal(torch.isinf(dX), torch.isinf(ref))
+    assert torch.equal(dX[torch.isinf(ref)] > 0, ref[torch.isinf(ref)] > 0)
+    ok = torch.isfinite(ref)
+    assert rel_err(torch.where(ok, dX, 0).cpu(), torch.where(ok, ref, 0).cpu()) < SUM_TOL
+
+
 # fp32: one unit, part of one, several per group; 64-slot chunks, part of one and four; F_s past 512 and
 # 768; aligned and odd labels and supports; batches of part of a row tile, and of several slabs
 SHAPES_F32 = [
