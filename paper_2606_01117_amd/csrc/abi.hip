@@ -167,12 +167,35 @@ size_t bwd_x_least_ws(const haste::TailArgs &a) {
     return dn ? dn : bwd_x_other_ws(a);
 }
 
+// The backward-feature kernel that runs in ws_bytes of scratch: with less than the queried size another one
+// that can do with it, or the any-group kernel with fewer segments; kBxNone: too little for any
+enum BxKernel { kBxNone, kBxAny, kBxF32, kBxDn, kBxSg, kBxMfma, kBxValu };
+
+BxKernel bwd_x_kernel(const haste::TailArgs &a, size_t ws_bytes) {
+    const size_t other = bwd_x_other_ws(a);
+    if (haste::bwd_x_any_preferred(a) &&
+        (ws_bytes >= haste::bwd_x_any_ws(a) ||
+         (ws_bytes < other && ws_bytes >= bwd_x_least_ws(a) && haste::bwd_x_any_fits(a, ws_bytes))))
+        return kBxAny;
+    if (haste::bwd_x_f32_preferred(a) && ws_bytes >= haste::bwd_x_f32_ws(a)) return kBxF32;
+    if (ws_bytes < other) return kBxNone;
+    if (haste::bwd_x_dn_supported(a)) return kBxDn;
+    if (haste::bwd_x_sg_supported(a)) return kBxSg;
+    return haste::bwd_x_mfma_supported(a) ? kBxMfma : kBxValu;
+}
+
+bool bwd_x_kernel_exists(const haste::TailArgs &a) {
+    return haste::bwd_x_dn_supported(a) || haste::bwd_x_sg_supported(a) || haste::bwd_x_mfma_supported(a) ||
+           haste::valu_supported(a);
+}
+
 // A tail step's workspace: bytes of backward-feature's part, haste_fwd_bce's (or the optimizer form's,
-// which can do with `least`) behind it; -1: too small
+// which can do with `least`) behind it; -1: too small (nothing is launched then, so the backward-feature
+// call, which comes last, must not be the one to find out)
 int64_t tail_split(const haste::TailArgs &a, size_t bytes, size_t need, size_t least) {
     if (bytes >= need) return a.B == 0 || a.L == 0 ? 0 : haste::round_up((int64_t)bwd_x_ws(a), 256);
     const int64_t at = haste::round_up((int64_t)bwd_x_least_ws(a), 256);
-    return bytes >= (size_t)at + least ? at : -1;
+    return bytes >= (size_t)at + least && bwd_x_kernel(a, (size_t)at) != kBxNone ? at : -1;
 }
 
 #define TRY(x)                      \
@@ -302,24 +325,22 @@ int haste_bwd_x(const haste_desc_t *d, const int32_t *idx, const void *W, const 
     TRY(need_ptr(idx, "idx"));
     TRY(need_ptr(W, "W"));
     TRY(need_ptr(dY, "dY"));
-    if (!haste::bwd_x_dn_supported(a) && !haste::bwd_x_sg_supported(a) && !haste::bwd_x_mfma_supported(a) &&
-        !haste::valu_supported(a))
-        return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
-    if (!ws || (ws_bytes < bwd_x_ws(a) && ws_bytes < bwd_x_least_ws(a)))
+    if (!bwd_x_kernel_exists(a)) return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
+    const BxKernel kern = ws ? bwd_x_kernel(a, ws_bytes) : kBxNone;
+    if (kern == kBxNone)
         return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", bwd_x_ws(a), ws ? ws_bytes : 0);
     TRY(need_ptr(ws, "ws"));
-    // with less than the queried size: the other kernel, where it can do with it
-    const bool any = haste::bwd_x_any_preferred(a) &&
-                     (ws_bytes >= haste::bwd_x_any_ws(a) || ws_bytes < bwd_x_other_ws(a));
-    const bool f32 = haste::bwd_x_f32_preferred(a) && ws_bytes >= haste::bwd_x_f32_ws(a);
-    if (any ? !haste::bwd_x_any_fits(a, ws_bytes) : !f32 && ws_bytes < bwd_x_other_ws(a))
-        return fail(HASTE_ERR_WORKSPACE, "haste_bwd_x needs %zu workspace bytes, got %zu", bwd_x_ws(a), ws_bytes);
-    if (any) return hip_status(haste::bwd_x_any(a, idx, W, dY, dX, beta, ws, ws_bytes, s), "haste_bwd_x");
-    if (f32) return hip_status(haste::bwd_x_f32(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
-    if (haste::bwd_x_dn_supported(a)) return hip_status(haste::bwd_x_dn(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
-    if (haste::bwd_x_sg_supported(a)) return hip_status(haste::bwd_x_sg(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
-    if (haste::bwd_x_mfma_supported(a)) return hip_status(haste::bwd_x_mfma(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
-    return hip_status(haste::bwd_x_valu(a, idx, W, dY, dX, beta, ws, s), "haste_bwd_x");
+    hipError_t e = hipErrorInvalidValue;
+    switch (kern) {
+        case kBxNone: break;
+        case kBxAny: e = haste::bwd_x_any(a, idx, W, dY, dX, beta, ws, ws_bytes, s); break;
+        case kBxF32: e = haste::bwd_x_f32(a, idx, W, dY, dX, beta, ws, s); break;
+        case kBxDn: e = haste::bwd_x_dn(a, idx, W, dY, dX, beta, ws, s); break;
+        case kBxSg: e = haste::bwd_x_sg(a, idx, W, dY, dX, beta, ws, s); break;
+        case kBxMfma: e = haste::bwd_x_mfma(a, idx, W, dY, dX, beta, ws, s); break;
+        case kBxValu: e = haste::bwd_x_valu(a, idx, W, dY, dX, beta, ws, s); break;
+    }
+    return hip_status(e, "haste_bwd_x");
 }
 
 int haste_tail_step(const haste_desc_t *d, const void *X, const int32_t *idx, const void *W, const float *bias,
@@ -352,7 +373,12 @@ int haste_tail_step(const haste_desc_t *d, const void *X, const int32_t *idx, co
                                                 beta_dx, ws, as_stream(stream)),
                           "haste_tail_step");
     }
-    // composed: the two calls, each in its own part of the workspace
+    // composed: the two calls, each in its own part of the workspace; what the second would refuse is refused
+    // before the first is launched
+    if (dX && a.B > 0) {
+        TRY(need_ptr(dX, "dX"));
+        if (a.L > 0 && !bwd_x_kernel_exists(a)) return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
+    }
     TRY(haste_fwd_bce(d, X, idx, W, bias, pos, P, dY, dW, dbias, beta, ws ? (char *)ws + xoff : nullptr,
                       ws ? ws_bytes - xoff : 0, stream));
     if (!dX) return ok();
@@ -680,7 +706,12 @@ int haste_tail_step_sgd(const haste_desc_t *d, const void *X, const int32_t *idx
                                                     W_next, dX, beta_dx, ws, ws_bytes - xoff, as_stream(stream)),
                           "haste_tail_step_sgd");
     }
-    // composed: the two calls, each in its own part of the workspace
+    // composed: the two calls, each in its own part of the workspace; what the second would refuse is refused
+    // before the first is launched
+    if (dX && a.B > 0) {
+        TRY(need_ptr(dX, "dX"));
+        if (a.L > 0 && !bwd_x_kernel_exists(a)) return fail(HASTE_ERR_UNSUPPORTED, "no backward-feature kernel for this shape");
+    }
     TRY(haste_fwd_bce_sgd(d, X, idx, W, bias, pos, P, dY, dbias, opt, m, W_next, ws ? (char *)ws + xoff : nullptr,
                           ws ? ws_bytes - xoff : 0, stream));
     if (!dX) return ok();

@@ -253,7 +253,7 @@ template <int MT, int NFT, int PK, int NI, int READ>
 __global__ __attribute__((amdgpu_flat_work_group_size(kAxThreads, kAxThreads), amdgpu_waves_per_eu(2, 2)))
 void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, const bf16_t *__restrict__ dY,
                  float *__restrict__ part, int B, int Bp, int F_s, int64_t L, int G, uint32_t gmul, int F_in, int nbt,
-                 int nsplit, int64_t lps) {
+                 int nsplit, int64_t nseg, int64_t lps) {
     constexpr int FR = 16 * kAxCons * NFT;
     constexpr int TB = FR * 64;                   // bytes of a tile
     constexpr int SB = 16 * MT * kAxStageRow;     // bytes of a staged dY step
@@ -265,6 +265,7 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
     jj /= nbt;
     const int f0 = (jj % nsplit) * FR;
     const int64_t seg = (int64_t)(jj / nsplit) * kXcds + xcd;
+    if (seg >= nseg) return;                      // workgroup-uniform (the grid holds whole rows of 8 segments)
     const int b0 = bt * RW;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
@@ -687,7 +688,7 @@ struct AxGeom {
     size_t lds;
 };
 
-// ws_bytes: of the partials; fewer segments where it holds no more (0 segments: not even a few)
+// ws_bytes: of the partials; fewer segments where it holds no more (0 segments: not even one)
 inline AxGeom ax_geom(const haste::TailArgs &a, size_t ws_bytes = SIZE_MAX) {
     AxGeom g;
     g.mt = a.B > 32 ? 4 : 2;
@@ -708,7 +709,7 @@ inline AxGeom ax_geom(const haste::TailArgs &a, size_t ws_bytes = SIZE_MAX) {
     const int64_t max_seg = haste::round_up(haste::cdiv(a.L, 256), kXcds);
     g.nseg = nseg < max_seg ? nseg : max_seg;
     const size_t fit = ws_bytes / ((size_t)a.F_s * (size_t)(g.nbt * 16 * g.mt) * 4);
-    if (fit < (size_t)g.nseg) g.nseg = (int64_t)fit / kXcds * kXcds;
+    if (fit < (size_t)g.nseg) g.nseg = (int64_t)fit;
     g.lps = g.nseg ? haste::round_up(haste::cdiv(a.L, g.nseg), 64) : 0;
     g.lds = (size_t)ax_lds(16 * kAxCons * g.nft, g.mt);
     return g;
@@ -810,9 +811,9 @@ struct AxRun {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)g.lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(g.nseg * g.nbt * g.nsplit)), dim3(kAxThreads), g.lds, s, idx, (const bf16_t *)W,
-                           (const bf16_t *)dY, part, (int)a.B, g.nbt * 16 * MT, (int)a.F_s, a.L, (int)a.G, div_mul(a.G),
-                           (int)a.F_in, g.nbt, g.nsplit, g.lps);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(haste::round_up(g.nseg, kXcds) * g.nbt * g.nsplit)), dim3(kAxThreads), g.lds, s,
+                           idx, (const bf16_t *)W, (const bf16_t *)dY, part, (int)a.B, g.nbt * 16 * MT, (int)a.F_s, a.L, (int)a.G,
+                           div_mul(a.G), (int)a.F_in, g.nbt, g.nsplit, g.nseg, g.lps);
         return hipGetLastError();
     }
     hipError_t run() const { return ax_pick(a, g.pk, g.ni, ax_wide(dY), *this); }

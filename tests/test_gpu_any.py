@@ -253,6 +253,9 @@ SCRATCH = [
     ((256, 256, 24880, 2, 256), synth.DT_BF16, (16777472, 16777472, 42254592)),
     ((128, 298, 60816, 16, 256), synth.DT_BF16, (19529984, 19529984, 81805568)),
     ((1, 384, 436416, 32, 128), synth.DT_F32, (25166080, 25166080, 248611072)),
+    # an odd number of 32-row tiles, whose partials are then fewer than 8 segments of 64-row tiles
+    ((1030, 768, 65536, 4, 128), synth.DT_BF16, (25952256, 28629248, 62183680)),
+    ((65, 768, 512, 4, 128), synth.DT_BF16, (2359296, 2573568, 2835712)),
 ]
 
 
@@ -298,3 +301,37 @@ def test_scratch_limits(shape, dtype, least):
             assert rel_err(a.cpu(), b.cpu()) < (1e-5 if f32 else SUM_TOL)
         with pytest.raises(Exception):
             call(room[:256])
+
+
+@pytest.mark.parametrize("shape,dtype,least", SCRATCH)
+def test_scratch_refusal(shape, dtype, least):
+    """A tail step whose workspace is too small for one of its products launches none of them."""
+    import torch
+    import paper_2606_01117_amd as hs
+    B, F_s, L, G, F_in = shape
+    say("scratch refusal", shape, dtype)
+    dt = torch.float32 if dtype == synth.DT_F32 else torch.bfloat16
+    idx = torch.arange(F_in, dtype=torch.int32, device="cuda").repeat(L // G, 1)
+    X, W = torch.ones((B, F_s), dtype=dt, device="cuda"), torch.ones((L, F_in), dtype=dt, device="cuda")
+    m, dW, dX = (torch.full(s, 5.0, device="cuda") for s in ((L, F_in), (L, F_in), (B, F_s)))
+    Wn, dY = torch.full((L, F_in), 5.0, dtype=dt, device="cuda"), torch.full((B, L), 5.0, dtype=dt, device="cuda")
+    pos = torch.zeros((B, 1), dtype=torch.int32, device="cuda")
+    desc = hs.make_desc(B, F_s, L, G, F_in, dtype)
+    opt = hs.sgd_opts(0.1, 0.9, 1e-4)
+    room = torch.empty(max(least), dtype=torch.uint8, device="cuda")
+    step = lambda ws: hs.haste_tail_step(desc, X, idx, W, None, pos, dY, dW, None, 0, dX, 0, ws)
+    sgd = lambda ws: hs.haste_tail_step_sgd(desc, X, idx, W, None, pos, dY, None, opt, m, Wn, dX, 0, ws)
+    refused = 0
+    for call, n in ((step, least[1]), (sgd, least[2])):
+        for short in (256, least[0] // 256 * 256 // 8, least[0] // 256 * 256, n // 256 * 256 - 256, n):
+            try:
+                call(room[:n - short])
+            except hs.HasteError as e:
+                assert e.status == 3
+                refused += 1
+                for t in (m, dW, dX, Wn, dY):
+                    assert bool((t == 5.0).all())
+            else:                                 # a size that some kernels can do with
+                for t in (m, dW, dX, Wn, dY):
+                    t.fill_(5.0)
+    assert refused >= 4
