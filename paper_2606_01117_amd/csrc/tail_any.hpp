@@ -240,8 +240,9 @@ __device__ __forceinline__ void ax_add_not_finite(const int32_t *idx, const bf16
 }
 
 // An empty cell of the tile contributes dY times zero, which is zero only for finite dY.  So an infinity
-// or a NaN of dY is staged as zero and its row marked, and in a workgroup with marked rows all waves go
-// over those rows of dY once more and add each such element's own products, feature by feature.  What
+// or a NaN of dY is staged as the smallest normal number of its sign (which leaves zero cells zero, and
+// infinite and NaN weights what they are) and its row marked, and in a workgroup with marked rows all waves
+// go over those rows of dY once more and add each such element's own products, feature by feature.  What
 // they sum to is an infinity or a NaN in any order.  (The test costs a producer lane 11 instructions a
 // step.)
 //
@@ -318,7 +319,8 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const uint32_t t = ((v[k] & 0x7fff7fffu) + 0x00800080u) & 0x80008000u;
-                    v[k] &= ~((t >> 15) * 0xffffu);
+                    const uint32_t m = (t >> 15) * 0xffffu;
+                    v[k] = (v[k] & ~(m & 0x7fff7fffu)) | (m & 0x00800080u);
                 }
                 atomicOr(&bad[dr >> 5], 1u << (dr & 31));
             }

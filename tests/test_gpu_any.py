@@ -145,8 +145,8 @@ def test_fwd_not_finite(shape):
                                    (130, 896, 35 * 30, 35, 181), (300, 384, 2048, 64, 256), (128, 768, 4096, 4, 64)])
 def test_bwd_x_not_finite(shape):
     """An infinity or a NaN in dY reaches the features of its label's support, and no others: one element, several
-    of a row in one group and in several, both infinities at once, an infinity that meets a zero weight, the
-    last row and label, and a whole row."""
+    of a row in one group and in several, both infinities at once, an infinity that meets a zero weight and
+    one that meets infinite weights, the last row and label, and a whole row."""
     import torch
     import paper_2606_01117_amd as hs
     B, F_s, L, G, F_in = shape
@@ -155,7 +155,10 @@ def test_bwd_x_not_finite(shape):
     inf, nan = float("inf"), float("nan")
     W[L // 3, F_in // 2] = 0.0
     Wd[L // 3, sup[L // 3, F_in // 2]] = 0.0
-    for b, l, v in [(3, 0, inf), (3, 1, inf), (3, L // 2, -inf), (B // 2, L // 3, -inf), (B - 1, L - 1, nan), (B - 1, 5, inf)]:
+    li = L // 4
+    W[li, 0], W[li, F_in - 1] = inf, -inf
+    Wd[li] = 0.0                                  # (its products are added below)
+    for b, l, v in [(3, 0, inf), (3, 1, inf), (3, L // 2, -inf), (B // 2, L // 3, -inf), (B - 1, L - 1, nan), (B - 1, 5, inf), (2, li, -inf)]:
         dY[b, l] = v
     dY[7] = nan
     desc = hs.make_desc(B, F_s, L, G, F_in, synth.DT_BF16)
@@ -165,7 +168,8 @@ def test_bwd_x_not_finite(shape):
     hs.haste_bwd_x(desc, idx, W, dY, dX, 1, ws)
     bad = ~torch.isfinite(dY)
     ref = torch.where(bad, 0, dY).double() @ Wd + 1.0
-    for b, l in bad.nonzero().tolist():
+    assert bool((dY[:, li] != 0).all())
+    for b, l in bad.nonzero().tolist() + [(b, li) for b in range(B) if b != 2]:
         if b != 7:
             ref[b, sup[l]] += dY[b, l].double() * W[l].double()
     ref[7, sup.unique()] = nan
