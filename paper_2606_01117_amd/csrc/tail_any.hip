@@ -22,6 +22,16 @@ bool fwd_any_supported(const TailArgs &a) {
     return far * a.F_in * 4 < ((int64_t)1 << 31) && (far + a.G) * a.G < ((int64_t)1 << 32);
 }
 
+// A workgroup clears its tiles and reads X for 128 rows (by 2, 4 or 16 bytes), then takes steps of 32 labels;
+// a step's cost is that of the product over all features, or of the producers' slot pairs
+double fwd_any_us(const TailArgs &a) {
+    const FaGeom g = fa_geom(a);
+    const double R = xcd_rounds(cdiv(a.L, g.lps), g.nbt, 1), S = R * (g.lps / 32);
+    const bool halves = a.F_in % 2 != 0 || a.L % 2 != 0 || (g.pk == 8 && a.L % 8 != 0);
+    return 0.56 + R * (1.3 + g.nc * (0.21 + (a.F_s % 2 ? 0.23 : a.F_s % 8 ? 0.057 : 0.0))) +
+           S * (0.0055 * g.nc + g.ni * (0.07 + 0.024 * g.pk) + (halves ? 0.015 + 0.075 * g.ni * g.pk : 0.0)) + 0.82e-6 * a.B * a.L;
+}
+
 // Where another kernel takes the layer too, measured per call at F_s = 768 (us; 328K labels):
 //   - groups of 1 or 2 labels: the scattered tiles of 32 rows per workgroup are written once per 32 rows
 //     there, once per 128 here (G = 1, 64 slots, 32 / 64 / 128 / 256 rows: 37 / 60 / 111 / 204 there, 51 /
@@ -31,12 +41,17 @@ bool fwd_any_supported(const TailArgs &a) {
 //     104 / 169 against 102 / 104 / 109);
 //   - larger groups share each gather among 16 labels or more (G = 16, 64 slots: 65 there, 104 here);
 //   - everything else (other group sizes and widths) runs on the vector ALUs, 8 times slower.
+// So much for large layers.  Here the cost of a step does not depend on the slots, and a workgroup's
+// prologue takes 8 to 13 us (twice that at odd F_s), so with few slots, rows or features, or few labels per
+// workgroup, the others are faster, and the estimates decide (4 rows, 334K labels, G = 16, 8 slots of 128
+// features: 8 there, 34 here; 1606 rows, 2432 labels, G = 8, 128 slots of 128: 13 against 21; 2600 random
+// layers: 539 more than 6% slower here than there without the estimates, 69 with them).
 bool fwd_any_preferred(const TailArgs &a) {
     if (!fwd_any_supported(a)) return false;
-    if (fwd_dn_supported(a)) return a.B > 32;
+    if (fwd_dn_supported(a)) return a.B > 32 && fwd_any_us(a) < fwd_dn_us(a);
     if (fwd_sg_supported(a))
-        return cdiv(a.B, 32) * (20 + 3 * a.F_in / a.G) * 48 > 177 * cdiv(a.B, 128) * fa_geom(a).nc;
-    return !fwd_mfma_supported(a) && valu_supported(a);
+        return cdiv(a.B, 32) * (20 + 3 * a.F_in / a.G) * 48 > 177 * cdiv(a.B, 128) * fa_geom(a).nc && fwd_any_us(a) < fwd_sg_us(a);
+    return !fwd_mfma_supported(a) && valu_supported(a) && fwd_any_us(a) < fwd_valu_us(a);
 }
 
 hipError_t fwd_any(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,

@@ -978,6 +978,15 @@ bool fwd_dn_supported(const TailArgs &a) {
     return g.lds <= 160 * 1024 && (g.lps + 1024) * a.F_in * 4 < ((int64_t)1 << 31);
 }
 
+// steps of 32 labels, each with the scatter of its weights and the tile's product; narrow tiles leave room for
+// a second workgroup per CU
+double fwd_dn_us(const TailArgs &a) {
+    const FdGeom g = fd_geom(a);
+    const int64_t nseg = cdiv(a.L, g.lps), steps = g.lps / 32;
+    const double R = xcd_rounds(nseg, g.nbt, 1), Rp = xcd_rounds(nseg, g.nbt, 160 * 1024 / (int64_t)g.lds < 2 ? 1 : 2);
+    return 3.0 + 2.5 * Rp + R * (0.006 * a.F_s + steps * 0.004 * a.F_in) + Rp * steps * 0.00024 * a.F_s + 0.36e-6 * a.B * a.L;
+}
+
 hipError_t fwd_dn(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
                   hipStream_t s, const int32_t *spos, int P) {
     const FdGeom g = fd_geom(a);

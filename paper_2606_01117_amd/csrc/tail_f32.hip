@@ -460,26 +460,52 @@ static bool f32_shape(const TailArgs &a) {
            (a.G + 16) * a.F_in * 4 < ((int64_t)1 << 31);
 }
 
+struct F32FwdGeom {
+    int nbt;
+    int64_t nunit, nseg, ups;
+};
+
+static F32FwdGeom f32_fwd_geom(const TailArgs &a) {
+    F32FwdGeom g;
+    g.nbt = (int)cdiv(a.B, 32);
+    g.nunit = f32_units(a);
+    g.nseg = round_up(cdiv(kXcds * kCusPerXcd, g.nbt), kXcds);
+    const int64_t most = round_up(cdiv(g.nunit, kF32Waves), kXcds);
+    if (g.nseg > most) g.nseg = most;
+    g.ups = round_up(cdiv(g.nunit, g.nseg), kF32Waves);
+    return g;
+}
+
+// a workgroup stages its slab of X^T, then every wave takes one unit after the other, chunk by chunk
+double fwd_f32_us(const TailArgs &a) {
+    const F32FwdGeom g = f32_fwd_geom(a);
+    const int64_t nseg = cdiv(g.nunit, g.ups), fit = 160 * 1024 / f32_fwd_lds((int)a.F_s);
+    const double R = xcd_rounds(nseg, g.nbt, 1), Rp = xcd_rounds(nseg, g.nbt, fit < 1 ? 1 : fit > 4 ? 4 : fit);
+    const double S = (double)(g.ups / kF32Waves), ch = (double)cdiv(a.F_in, 64);
+    return 1.7 + Rp * (2.4 + 0.012 * a.F_s + 0.37 * S * ch) +
+           R * S * (0.3 * cdiv(a.F_in, 16) + (a.F_in % 4 ? 0.36 * ch : 0.0) + (a.G % 4 ? 0.27 : 0.0)) + 1.0e-6 * a.B * a.L;
+}
+
 // Groups of 1 or 2 labels leave most of a 16-label unit empty, and the vector ALUs are then as fast
 // (131K labels, 64 slots, 128 rows, us: G = 1 / 2 / 4 / 8 / 16: 357 / 302 / 218 / 211 / 207 on the vector
-// ALUs, 495 / 260 / 143 / 79 / 50 here).
+// ALUs, 495 / 260 / 143 / 79 / 50 here).  Larger ones with few slots (G = 3, 8 slots of 128 features, 194K
+// labels, 168 rows: 47 there, 320 here) or few units per workgroup (1064 rows, 816 labels, 32 slots of
+// 768: 18 and 34) too: the estimates decide (of 1210 random layers 217 more than 6% slower here than there
+// without them, 38 with them).
 bool fwd_f32_preferred(const TailArgs &a) {
-    return a.G > 2 && f32_shape(a) && valu_supported(a) && f32_fwd_lds((int)a.F_s) <= 160 * 1024;
+    return a.G > 2 && f32_shape(a) && valu_supported(a) && f32_fwd_lds((int)a.F_s) <= 160 * 1024 && fwd_f32_us(a) < fwd_valu_us(a);
 }
 
 hipError_t fwd_f32(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
                    hipStream_t s) {
-    const int nbt = (int)cdiv(a.B, 32), lds = f32_fwd_lds((int)a.F_s);
-    const int64_t nunit = f32_units(a);
-    int64_t nseg = round_up(cdiv(kXcds * kCusPerXcd, nbt), kXcds);
-    const int64_t most = round_up(cdiv(nunit, kF32Waves), kXcds);
-    if (nseg > most) nseg = most;
-    const int64_t ups = round_up(cdiv(nunit, nseg), kF32Waves);
+    const int lds = f32_fwd_lds((int)a.F_s);
+    const F32FwdGeom g = f32_fwd_geom(a);
     auto go = [&](auto kern) {
         hipError_t e = lds_limit(kern, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(nseg * nbt)), dim3(512), lds, s, (const float *)X, idx, (const float *)W, bias,
-                           (float *)Y, (int)a.B, (int)a.F_s, a.L, (int)a.G, (int)a.F_in, (int)cdiv(a.G, 16), nunit, ups, nbt);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(g.nseg * g.nbt)), dim3(512), lds, s, (const float *)X, idx, (const float *)W,
+                           bias, (float *)Y, (int)a.B, (int)a.F_s, a.L, (int)a.G, (int)a.F_in, (int)cdiv(a.G, 16), g.nunit, g.ups,
+                           g.nbt);
         return hipGetLastError();
     };
     const bool vst = a.G % 4 == 0;                // L then is too, and every unit starts at a multiple of 4

@@ -884,6 +884,20 @@ hipError_t bwd_x_sg(const TailArgs &a, const int32_t *idx, const void *W, const 
     return reduce_fmajor(part, (int)g.nseg, g.nbt * 32, a.B, a.F_s, dX, beta, s);
 }
 
+// a workgroup stages the slab's X^T, then takes passes of 128 labels, whose gathers are F_in / G per label
+double fwd_sg_us(const TailArgs &a) {
+    const int64_t nbt = cdiv(a.B, kSgRows), npass = cdiv(a.L, kSgPass);
+    int64_t nseg = round_up(cdiv(kXcds * kCusPerXcd, nbt), kXcds);
+    if (nseg > round_up(npass, kXcds)) nseg = round_up(npass, kXcds);
+    const int64_t pps = cdiv(npass, nseg);
+    const int64_t lds = a.F_s * kSgXRow + kSgPass * a.F_in * 2 + kSgPass / a.G * a.F_in * 4 + kSgRows * kSgOutRow;
+    int64_t per = 160 * 1024 / lds;
+    per = per < 1 ? 1 : per > 4 ? 4 : per;
+    const double R = xcd_rounds(cdiv(npass, pps), nbt, 1), Rp = xcd_rounds(cdiv(npass, pps), nbt, per), gathers = (double)a.F_in / a.G;
+    return 4.0 * Rp + R * (0.011 * a.F_s + pps * (0.058 * gathers + 0.0002 * a.F_s)) +
+           1e-6 * nbt * a.L * (0.71 * gathers + 0.017 * a.F_s) + 0.15e-6 * a.B * a.L;
+}
+
 hipError_t fwd_sg(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias, void *Y,
                   hipStream_t s, const int32_t *spos, int P) {
     switch (a.G) {

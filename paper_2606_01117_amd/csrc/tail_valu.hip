@@ -220,6 +220,29 @@ bool valu_supported(const TailArgs &a) {
     return a.F_s <= kMaxFs && (size_t)a.F_s * XS * 4 <= 150 * 1024 && bwd_x_valu_lds(a) <= 160 * 1024;
 }
 
+// workgroups per CU, by the LDS of a batch tile
+static int64_t valu_per_cu(const TailArgs &a) {
+    const int64_t n = 160 * 1024 / (a.F_s * XS * 4);
+    return n < 8 ? n : 8;
+}
+
+// Every workgroup stages a batch tile and then takes tiles of 256 labels, slot by slot.  A thread reads its
+// label's weights and support 2 or 4 bytes at a time, a line or more apart from its neighbours': where the
+// resident threads' lines (ws, about 1 MB per XCD each) are more than the L2 keeps, they are fetched again, the
+// more of them from memory the larger the weights and supports are (1.5 to 7 times the time)
+double fwd_valu_us(const TailArgs &a) {
+    const int64_t nbt = cdiv(a.B, TB), nlt = cdiv(a.L, 256), per = valu_per_cu(a);
+    int64_t gx = 2048 / nbt < 1 ? 1 : 2048 / nbt;
+    if (gx > nlt) gx = nlt;
+    const double R = (double)cdiv(gx * nbt, 256 * per), S = R * cdiv(nlt, gx);
+    const double esz = a.dtype == HASTE_DTYPE_F32 ? 4.0 : 2.0, row = a.F_in * esz;
+    const double lines = (row < 128 ? row / 128 : 1.0) + (a.F_in < 32 ? a.F_in / 32.0 : 1.0) / a.G;
+    const double ws = (double)(cdiv(gx * nbt, 256) < per ? cdiv(gx * nbt, 256) : per) * lines;
+    const double far = 1e-6 * a.L * a.F_in * (esz + 4.0 / a.G) / 16;   // 16 MB of weights and supports
+    const double again = ws > 2.5 ? 0.25 * (ws - 2.5) * (far < 6 ? far : 6.0) : 0.0;
+    return 0.36 + R * (3.9 + 0.0097 * a.F_s) + 0.096 * S * a.F_in + 1e-6 * a.L * a.F_in * nbt * (1.5 + again) + 0.32e-6 * a.B * a.L;
+}
+
 hipError_t fwd_valu(const TailArgs &a, const void *X, const int32_t *idx, const void *W, const float *bias,
                     void *Y, hipStream_t s) {
     const int64_t nbt = cdiv(a.B, TB);

@@ -21,6 +21,8 @@ SHAPES = [
     (40, 640, 333, 3, 1), (16, 65, 8 * 37, 8, 65), (70, 768, 16 * 81, 16, 200), (300, 384, 2048, 64, 256),
     (48, 905, 1001, 7, 255), (1, 256, 1, 1, 2), (64, 768, 260, 260, 33), (33, 768, 602, 14, 129),
     (100, 766, 4100, 4, 31),
+    # as large as the forward's and backward-weight's rules ask for: odd supports in packs of 8, one label, few slots
+    (64, 700, 8 * 137, 8, 65), (64, 768, 1, 1, 255), (300, 766, 4100, 4, 31), (64, 511, 1500, 3, 100),
 ]
 
 
