@@ -122,10 +122,10 @@ bool bwd_w_uses_xt(const haste::TailArgs &a) {
     return haste::bwd_w_dn_supported(a) || haste::bwd_w_sg_supported(a) || haste::bwd_w_mfma_supported(a);
 }
 
-// layers of other groups and supports take the matrix-core kernel where the workspace holds the X^T
-// copy; they never had to bring one, so a smaller workspace takes them to the vector ALUs
+// layers of other groups and supports take the matrix-core kernel where it is the faster one and the workspace
+// holds the X^T copy; they never had to bring one, so a smaller workspace takes them to the vector ALUs
 bool bwd_w_takes_xt(const haste::TailArgs &a) {
-    return !bwd_w_uses_xt(a) && haste::bwd_w_any_supported(a) && haste::valu_supported(a);
+    return !bwd_w_uses_xt(a) && haste::bwd_w_any_preferred(a);
 }
 
 size_t bwd_w_ws(const haste::TailArgs &a) {

@@ -291,6 +291,7 @@ hipError_t bwd_w_dn(const TailArgs &a, const void *X, const int32_t *idx, const 
                     int beta, void *ws, hipStream_t s);
 bool bwd_w_mfma_supported(const TailArgs &a);
 bool bwd_w_any_supported(const TailArgs &a);   // the same kernel for any group and support
+bool bwd_w_any_preferred(const TailArgs &a);
 size_t bwd_w_mfma_ws(const TailArgs &a);
 hipError_t bwd_w_mfma(const TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW,
                       float *dbias, int beta, void *ws, hipStream_t s);
@@ -351,6 +352,9 @@ double fwd_dn_us(const TailArgs &a);
 double fwd_sg_us(const TailArgs &a);
 double fwd_f32_us(const TailArgs &a);
 double fwd_valu_us(const TailArgs &a);
+double bwd_w_any_us(const TailArgs &a);
+double bwd_w_f32_us(const TailArgs &a);
+double bwd_w_valu_us(const TailArgs &a);
 
 // tail, fp32 on the matrix cores; preferred: where faster than the vector ALUs
 bool fwd_f32_preferred(const TailArgs &a);

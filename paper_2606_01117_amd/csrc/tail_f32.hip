@@ -513,10 +513,20 @@ hipError_t fwd_f32(const TailArgs &a, const void *X, const int32_t *idx, const v
     return vst ? go(k_fwd_f32<false, true>) : go(k_fwd_f32<false, false>);
 }
 
+static int f32_bw_nst(const TailArgs &a) { return a.F_in <= 32 ? 2 : a.F_in <= 64 ? 4 : a.F_in <= 128 ? 8 : 16; }
+
+// a workgroup sweeps the batch in slabs of 32 rows for 8 or 16 units
+double bwd_w_f32_us(const TailArgs &a) {
+    const int nst = f32_bw_nst(a), xi = a.F_s <= 512 ? 8 : a.F_s <= 768 ? 12 : 16;
+    const double R = (double)cdiv(cdiv(f32_units(a), kF32Waves * f32_bw_upw(nst)), 256);
+    return 2.5 + R * (1.3 + 0.13 * nst + cdiv(a.B, 32) * (0.88 + 0.18 * nst + 0.21 * xi)) + 0.35e-6 * a.B * a.L + 0.53e-6 * a.L * a.F_in;
+}
+
 // (as above: 444 / 424 / 331 / 405 / 405 on the vector ALUs, about 600 / 345 / 179 / 96 / 55 here; G = 2 with 32
-// slots 182 there, 193 here)
+// slots 182 there, 193 here; G = 3 with 8 slots of 128 features, 194K labels, 168 rows 56 there, 307 here)
 bool bwd_w_f32_preferred(const TailArgs &a) {
-    return (a.G > 2 || (a.G == 2 && a.F_in > 32)) && f32_shape(a) && valu_supported(a) && f32_bw_lds((int)a.F_s) <= 160 * 1024;
+    return (a.G > 2 || (a.G == 2 && a.F_in > 32)) && f32_shape(a) && valu_supported(a) && f32_bw_lds((int)a.F_s) <= 160 * 1024 &&
+           bwd_w_f32_us(a) < bwd_w_valu_us(a);
 }
 
 hipError_t bwd_w_f32(const TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW, float *dbias,
@@ -537,9 +547,11 @@ hipError_t bwd_w_f32(const TailArgs &a, const void *X, const int32_t *idx, const
         if (a.F_s <= 768) return go(k_bwd_w_f32<NST, 12>, f32_bw_upw(NST));
         return go(k_bwd_w_f32<NST, 16>, f32_bw_upw(NST));
     };
-    if (a.F_in <= 32) return wide(std::integral_constant<int, 2>{});
-    if (a.F_in <= 64) return wide(std::integral_constant<int, 4>{});
-    if (a.F_in <= 128) return wide(std::integral_constant<int, 8>{});
+    switch (f32_bw_nst(a)) {
+        case 2: return wide(std::integral_constant<int, 2>{});
+        case 4: return wide(std::integral_constant<int, 4>{});
+        case 8: return wide(std::integral_constant<int, 8>{});
+    }
     return wide(std::integral_constant<int, 16>{});
 }
 

@@ -1497,6 +1497,26 @@ bool bwd_w_any_supported(const TailArgs &a) {
            bwd_w_mfma_ws(a) <= haste_fwd_bce_static_max_bytes() && bw2_lds((int)a.F_s, 256) <= kLdsBudget;
 }
 
+// A workgroup sweeps the batch in slabs of 32 rows for up to 16 units of 32 labels, whose gathers and
+// products do not depend on the labels a unit has (G of them where groups are smaller); supports narrower
+// than the tiles are stored label by label.  The X^T copy comes first.
+double bwd_w_any_us(const TailArgs &a) {
+    const int fin = (int)(a.F_in <= 32 ? 32 : a.F_in <= 64 ? 64 : a.F_in <= 128 ? 128 : 256);
+    const int64_t wgs = cdiv(a.L / a.G * cdiv(a.G, 32), bw2_units(fin)), fit = 160 * 1024 / (int64_t)bw2_lds((int)a.F_s, fin);
+    const double R = (double)cdiv(wgs, 256), Rp = (double)cdiv(wgs, 256 * (fit < 2 ? 1 : 2)), slabs = (double)cdiv(a.B, 32), nst = fin / 16;
+    const double rows = a.F_in != fin ? (double)(a.G < 32 ? a.G : 32) : 0.0;
+    return 5.1 + R * (2.2 + 0.1 * nst + 0.075 * rows + slabs * (1.1 + 0.03 * nst + 0.00036 * a.F_s)) +
+           Rp * (0.07 * rows + (a.L % 2 || a.G % 2 ? 1.2 * slabs : 0.0)) + 0.12e-6 * a.B * a.L + 0.45e-6 * a.L * a.F_in + 5.1e-6 * a.B * a.F_s;
+}
+
+// Against the vector ALUs (98K labels, 768 features, us, 16 / 64 / 256 rows): G = 1, 20 slots 30 / 77 / 364 there,
+// 112 / 184 / 598 here; 48 slots 71 / 182 / 728 against 127 / 207 / 514; 256 slots 337 / 998 / 4080 against 360 /
+// 460 / 890; G = 3, 20 slots 28 / 74 / 325 against 44 / 75 / 240; G = 5 and more here for nearly all.  With 8 slots
+// of 128 features the vector ALUs are up to 13 times faster for G = 1.  The estimates decide.
+bool bwd_w_any_preferred(const TailArgs &a) {
+    return bwd_w_any_supported(a) && valu_supported(a) && bwd_w_any_us(a) < bwd_w_valu_us(a);
+}
+
 // X^T in 32-row batch blocks, [B/32][F_s][32] (rows past B zero), into the workspace
 hipError_t transpose_x(const TailArgs &a, const void *X, void *ws, hipStream_t s) {
     const int Bp = (int)round_up(a.B, 32);

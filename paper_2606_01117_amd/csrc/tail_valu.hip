@@ -264,6 +264,14 @@ hipError_t fwd_valu(const TailArgs &a, const void *X, const int32_t *idx, const 
     return hipGetLastError();
 }
 
+// a workgroup takes 256 labels and, for every 32 slots, stages the whole batch once more
+double bwd_w_valu_us(const TailArgs &a) {
+    const int64_t wgs = cdiv(a.L, 256), slabs = cdiv(a.B, TB);
+    const double R = (double)cdiv(wgs, 256 * valu_per_cu(a)), passes = (double)cdiv(a.F_in, 32);
+    return 2.4 + R * slabs * (passes * (1.1 + 0.014 * a.F_s) + 0.087 * a.F_in) + 0.00021 * wgs * slabs * a.F_in +
+           4.5e-6 * a.L * a.F_in + 0.39e-6 * a.B * a.L;
+}
+
 hipError_t bwd_w_valu(const TailArgs &a, const void *X, const int32_t *idx, const void *dY, float *dW,
                       float *dbias, int beta, hipStream_t s) {
     const size_t lds = (size_t)a.F_s * XS * 4;

@@ -4,9 +4,7 @@ import ctypes
 
 import pytest
 
-from paper_2606_01117_amd import HASTE_DTYPE_BF16 as BF16
-from paper_2606_01117_amd import HASTE_DTYPE_F32 as F32
-from paper_2606_01117_amd import lib
+F32, BF16 = 0, 1
 
 
 class TailArgs(ctypes.Structure):
@@ -14,6 +12,7 @@ class TailArgs(ctypes.Structure):
 
 
 def rule(name, shape, dtype):
+    from paper_2606_01117_amd import lib
     fn = getattr(lib, f"_ZN5haste{len(name)}{name}ERKNS_8TailArgsE")   # haste::name(const TailArgs &)
     fn.restype = ctypes.c_bool
     return fn(ctypes.byref(TailArgs(*shape, dtype)))
@@ -40,7 +39,22 @@ FWD = [
     ("fwd_any_preferred", (1, 256, 187422, 1, 69), BF16, True),
 ]
 
+BWD_W = [
+    # one to three labels a group, few slots or rows: 210 against 16.2 on the vector ALUs, 112 and 29.6, 598 and 364,
+    # 307 and 56.1
+    ("bwd_w_any_preferred", (17, 128, 195575, 1, 8), BF16, False),
+    ("bwd_w_any_preferred", (16, 768, 98304, 1, 20), BF16, False),
+    ("bwd_w_any_preferred", (256, 768, 98304, 1, 20), BF16, False),
+    ("bwd_w_f32_preferred", (168, 128, 194244, 3, 8), F32, False),
+    # 460 against 998, and the large layers
+    ("bwd_w_any_preferred", (64, 768, 98304, 1, 256), BF16, True),
+    ("bwd_w_any_preferred", (256, 768, 131072, 32, 256), BF16, True),
+    ("bwd_w_any_preferred", (77, 500, 65544, 24, 48), BF16, True),
+    ("bwd_w_f32_preferred", (128, 768, 131072, 16, 64), F32, True),
+    ("bwd_w_f32_preferred", (32, 256, 4096, 8, 32), F32, True),
+]
 
-@pytest.mark.parametrize("name,shape,dtype,taken", FWD)
+
+@pytest.mark.parametrize("name,shape,dtype,taken", FWD + BWD_W)
 def test_route(name, shape, dtype, taken):
     assert rule(name, shape, dtype) == taken
