@@ -355,6 +355,10 @@ double fwd_valu_us(const TailArgs &a);
 double bwd_w_any_us(const TailArgs &a);
 double bwd_w_f32_us(const TailArgs &a);
 double bwd_w_valu_us(const TailArgs &a);
+double bwd_x_any_us(const TailArgs &a);
+double bwd_x_mfma_us(const TailArgs &a);
+double bwd_x_f32_us(const TailArgs &a);
+double bwd_x_valu_us(const TailArgs &a);
 
 // tail, fp32 on the matrix cores; preferred: where faster than the vector ALUs
 bool fwd_f32_preferred(const TailArgs &a);

@@ -84,12 +84,27 @@ bool bwd_x_any_fits(const TailArgs &a, size_t ws_bytes) {
 //     / 47; 64 rows 64 slots 52 / 52);
 //   - everything else (other group sizes and widths: vector ALUs, or small groups of wide inputs)
 //     20 times slower there.
+// That is for large layers; between the accumulators and this, for groups of 12 to 32 labels, the estimates decide
+// (440 rows, 51K labels, G = 12, 32 slots of 512: 44 there, 65 here; of 434 random layers of up to 32 labels
+// a group 14 more than 6% slower here than there without them, 2 with them).  Groups of 2, 4 and 8 labels with 32 or 64
+// slots, and of one with 128, once ran on the tiles of k_bwd_x_dn, which are faster for some small layers (4% of
+// 747 random ones by more than 6%, F_s = 128 and 32 slots by up to half) but turn a whole row of dX to NaN
+// where dY is not finite; so they stay here.
+double bwd_x_any_us(const TailArgs &a) {
+    const AxGeom g = ax_geom(a);
+    const double R = xcd_rounds(cdiv(a.L, g.lps), g.nbt * g.nsplit, 1), S = R * (g.lps / 32);
+    const bool halves = a.F_in % 2 != 0 || a.L % 2 != 0 || (g.pk == 8 && a.L % 8 != 0);
+    return 6.2 + R * 0.099 * g.nft * g.mt + S * (0.063 + 0.012 * g.nft + g.ni * (0.16 + 0.013 * g.pk) + (halves ? 0.21 + 0.1 * g.ni * g.pk : 0.0)) +
+           0.36e-6 * bwd_x_any_ws(a);
+}
+
 bool bwd_x_any_preferred(const TailArgs &a) {
     if (!bwd_x_any_supported(a) || bwd_x_dn_supported(a)) return false;
     if (bwd_x_mfma_supported(a)) {
         const AxGeom g = ax_geom(a);
         const int64_t per = a.G < 32 ? a.G : 32;
-        return a.B <= 64 || a.F_in * 768 >= 4 * per * (g.nsplit * 64 * g.nft);
+        return (a.B <= 64 || a.F_in * 768 >= 4 * per * (g.nsplit * 64 * g.nft)) &&
+               (a.G <= 8 || a.G > 32 || bwd_x_any_us(a) < bwd_x_mfma_us(a));
     }
     return bwd_x_sg_supported(a) || valu_supported(a);
 }

@@ -555,9 +555,23 @@ hipError_t bwd_w_f32(const TailArgs &a, const void *X, const int32_t *idx, const
     return wide(std::integral_constant<int, 16>{});
 }
 
-// (as above: 512 / 516 / 517 / 513 / 510 on the vector ALUs, 1032 / 525 / 255 / 141 / 82 here)
+// a one-wave workgroup takes its groups one after the other, 64 slots and 16 labels a step, slower the more
+// waves share its CU
+double bwd_x_f32_us(const TailArgs &a) {
+    const F32BxGeom g = f32_bx_geom(a);
+    const int64_t wgs = g.nseg * g.nbt, fit = 160 * 1024 / f32_bx_lds((int)a.F_s), occ = cdiv(wgs, 256) < fit ? cdiv(wgs, 256) : fit;
+    const double R = (double)cdiv(wgs, 256 * fit), chunks = (double)(g.gps * cdiv(a.F_in, 64)), odd = a.F_in % 4 ? 1.0 : 0.0;
+    return R * (7.6 + 0.0044 * a.F_s + chunks * (0.21 + cdiv(a.G, 16) * (0.26 + 0.067 * odd + (0.086 + 0.052 * odd) * occ))) +
+           0.3e-6 * bwd_x_f32_ws(a);
+}
+
+// (as above: 512 / 516 / 517 / 513 / 510 on the vector ALUs, 1032 / 525 / 255 / 141 / 82 here.)  A segment is
+// at least 8 groups, so layers of few large groups have few workgroups with long chains (275 rows, 952 labels,
+// G = 119, 195 slots of 256: 53 there, 155 here; of 1210 random layers 40 more than 6% slower here than there
+// without the estimates, 11 with them).
 bool bwd_x_f32_preferred(const TailArgs &a) {
-    return a.G > 2 && f32_shape(a) && valu_supported(a) && (a.L * 15 + a.G) * 4 < ((int64_t)1 << 31);
+    return a.G > 2 && f32_shape(a) && valu_supported(a) && (a.L * 15 + a.G) * 4 < ((int64_t)1 << 31) &&
+           bwd_x_f32_us(a) < bwd_x_valu_us(a);
 }
 
 size_t bwd_x_f32_ws(const TailArgs &a) {

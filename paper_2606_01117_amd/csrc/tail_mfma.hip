@@ -1786,6 +1786,15 @@ size_t bwd_x_mfma_ws(const TailArgs &a) {
     return bwd_x_part_bytes(a, g) + bwd_x_wt_bytes(a) + (size_t)round_up(K * a.F_in * 4, 256) + 256;
 }
 
+// the transposition of W, then a workgroup's groups one after the other (one 32-label block each: G <= 32), and
+// the partials' way to memory and back
+double bwd_x_mfma_us(const TailArgs &a) {
+    const BwdXGeom g = bwd_x_geom(a);
+    const double R = xcd_rounds(cdiv(a.L / a.G, g.gps), g.nbt, 1);
+    return 14.0 + R * (1.1 + 0.0046 * a.F_s + 0.0017 * g.gps * a.F_in) + 0.41e-6 * bwd_x_wt_bytes(a) + 0.46e-6 * bwd_x_part_bytes(a, g) +
+           19e-6 * a.L;
+}
+
 template <int F_IN, int NLB>
 static hipError_t launch_bwd_x(const TailArgs &a, const BwdXGeom &g, const int32_t *idx, const bf16_t *WT,
                                const void *dY, float *part, hipStream_t s) {

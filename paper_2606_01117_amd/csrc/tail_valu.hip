@@ -293,6 +293,14 @@ size_t bwd_x_valu_ws(const TailArgs &a) {
     return (size_t)S * (size_t)a.F_s * (size_t)(cdiv(a.B, 32) * 32) * 4 + 256;
 }
 
+// a workgroup takes its labels one after the other, 64 slots at a time, in staged blocks of 4096 slots
+double bwd_x_valu_us(const TailArgs &a) {
+    const int64_t S = bwd_x_valu_segments(a), wgs = S * cdiv(a.B, 32), fit = 160 * 1024 / (int64_t)bwd_x_valu_lds(a);
+    const double lps = (double)cdiv(a.L, S), R = (double)cdiv(wgs, 256), Rp = (double)cdiv(wgs, 256 * (fit < 1 ? 1 : fit > 4 ? 4 : fit));
+    const double runs = lps * cdiv(a.F_in, 64), blocks = (double)cdiv((int64_t)lps, 4096 / a.F_in);
+    return 6.0 + Rp * (0.002 * a.F_s + 0.11 * runs + 0.046 * lps) + R * (0.01 * runs + 3.5 * blocks) + 0.48e-6 * bwd_x_valu_ws(a);
+}
+
 hipError_t bwd_x_valu(const TailArgs &a, const int32_t *idx, const void *W, const void *dY, float *dX, int beta,
                       void *ws, hipStream_t s) {
     const int64_t nbt = cdiv(a.B, 32);

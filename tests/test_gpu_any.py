@@ -187,6 +187,8 @@ SHAPES_F32 = [
     (32, 256, 4096, 8, 32), (128, 768, 2048, 16, 64), (33, 768, 1027, 1, 63), (65, 513, 516, 4, 256), (77, 500, 24 * 131, 24, 48),
     (130, 896, 35 * 30, 35, 181), (40, 640, 333, 3, 1), (300, 384, 2048, 64, 128), (1, 65, 1, 1, 2), (17, 905, 602, 14, 100),
     (64, 768, 260, 260, 33), (16, 768, 16 * 300, 16, 65),
+    # as many groups as backward-feature's rule asks for, three chunks of odd supports
+    (130, 896, 35 * 120, 35, 181),
 ]
 
 

@@ -54,7 +54,23 @@ BWD_W = [
     ("bwd_w_f32_preferred", (32, 256, 4096, 8, 32), F32, True),
 ]
 
+BWD_X = [
+    # few large groups: 155 against 52.6 on the vector ALUs, 119 and 56.0
+    ("bwd_x_f32_preferred", (275, 256, 952, 119, 195), F32, False),
+    ("bwd_x_f32_preferred", (104, 486, 1356, 113, 253), F32, False),
+    # 65.1 against 43.8 in LDS accumulators, 45.8 and 38.1
+    ("bwd_x_any_preferred", (440, 512, 51228, 12, 32), BF16, False),
+    ("bwd_x_any_preferred", (293, 768, 23104, 32, 128), BF16, False),
+    # the large layers
+    ("bwd_x_any_preferred", (256, 768, 655360, 32, 128), BF16, True),
+    ("bwd_x_any_preferred", (128, 768, 131072, 16, 64), BF16, True),
+    ("bwd_x_any_preferred", (256, 768, 131072, 32, 256), BF16, True),
+    ("bwd_x_any_preferred", (512, 768, 2949120, 32, 64), BF16, False),
+    ("bwd_x_f32_preferred", (128, 768, 131072, 16, 64), F32, True),
+    ("bwd_x_f32_preferred", (32, 256, 4096, 8, 32), F32, True),
+]
 
-@pytest.mark.parametrize("name,shape,dtype,taken", FWD + BWD_W)
+
+@pytest.mark.parametrize("name,shape,dtype,taken", FWD + BWD_W + BWD_X)
 def test_route(name, shape, dtype, taken):
     assert rule(name, shape, dtype) == taken
