@@ -734,10 +734,31 @@ __global__ __launch_bounds__(256) void k_gemm_dir(const bf16_t *__restrict__ A, 
 
 // The direct kernel where the 128 x 128 tiles would leave half of the CUs idle, and operands within the
 // 31-bit range of a buffer offset (the steps past a chunk's end included).
-bool dir_ok(int64_t M, int64_t N, int64_t K, int64_t Z) {
+bool dir_ok(int64_t M, int64_t N, int64_t K, int64_t most = kXcds * kCusPerXcd / 2) {
     const int64_t lim = ((int64_t)1 << 31) - 1, Kp = K + 512;
-    return haste::cdiv(M, TM) * haste::cdiv(N, TN) * Z <= kXcds * kCusPerXcd / 2 && M * Kp * 2 < lim && N * Kp * 2 < lim &&
+    return haste::cdiv(M, TM) * haste::cdiv(N, TN) <= most && M * Kp * 2 < lim && N * Kp * 2 < lim &&
            haste::cdiv(M, kDirT) < 65536;
+}
+
+// The three products' limits, from 2180 random unaligned heads (1 to 2048 rows, 16 to 4096 features, 64 to 100K
+// labels; the ratio of the direct kernel's time to the tiles'):
+//   - logits (K = F_s): 0.2 to 0.9 up to 128 tiles, but with 2-byte reads (odd F_s) 1.1 to 1.6 from 96 tiles on;
+//   - dW (K = B): a workgroup's four waves share K, so 32 rows or fewer leave two of them idle: 1.0 up to 64
+//     tiles, 1.2 to 1.5 past them; up to 64 rows 0.84, and 1.2 to 1.3 past 96; from 65 rows on below 0.9;
+//   - dX (K = H, split): the tiles are full only if 128 rows and features are.  Where they are mostly padding (up to a
+//     third of the direct kernel's 32 x 32 tiles) 0.5 to 0.9; else by the work, 32 x 32 tiles x H: 0.5 to 0.9 up
+//     to 0.8 M, 1.0 to 2.3 past it (256 x 768 rows and features, 1K / 4K / 16K / 66K labels: 17 / 31 / 135 / 484 us
+//     direct, 28 / 37 / 70 / 232 in tiles).
+bool dir_fwd_ok(int64_t B, int64_t F_s, int64_t H) {
+    return dir_ok(B, H, F_s, F_s % 2 != 0 && F_s > 256 ? 80 : kXcds * kCusPerXcd / 2);
+}
+bool dir_dw_ok(int64_t B, int64_t F_s, int64_t H) {
+    return dir_ok(H, F_s, B, B <= 32 ? 64 : B <= 64 ? 96 : kXcds * kCusPerXcd / 2);
+}
+bool dir_dx_ok(int64_t B, int64_t F_s, int64_t H) {
+    const int64_t tiles = haste::cdiv(B, kDirT) * haste::cdiv(F_s, kDirT);
+    const int64_t padded = haste::cdiv(B, TM) * haste::cdiv(F_s, TN) * (TM / kDirT) * (TN / kDirT);
+    return dir_ok(B, F_s, H) && (3 * tiles <= padded || tiles * H <= 800000);
 }
 
 template <bool AK, bool BK, int EPI>
@@ -854,7 +875,7 @@ hipError_t head_fwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
     if (dtype == HASTE_DTYPE_BF16) {
         const bool big = gemm4_ok(B, F_s, H, {X, Wh, Yh, bias_h});
         // (32 rows or fewer would fill an eighth of the 256-row tiles)
-        if ((!big || B <= 32) && dir_ok(B, H, F_s, 1))
+        if ((!big || B <= 32) && dir_fwd_ok(B, F_s, H))
             return launch_dir<true, true, EPI_BF16_BIAS>(s, (const bf16_t *)X, F_s, (const bf16_t *)Wh, F_s, Yh, H, bias_h, B,
                                                          H, F_s, F_s, 1);
         if (big)
@@ -883,7 +904,7 @@ hipError_t head_fwd_bce(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const 
     if (dtype == HASTE_DTYPE_BF16 && gemm4_ok(B, F_s, H, {X, Wh, dYh, bias_h}))
         return launch_gemm4<true, true, EPI_BF16_BCE>(s, (const bf16_t *)X, F_s, B * F_s, (const bf16_t *)Wh, F_s,
                                                       H * F_s, dYh, H, bias_h, B, H, F_s, F_s, 1, pos, P);
-    if (dtype == HASTE_DTYPE_BF16 && dir_ok(B, H, F_s, 1))
+    if (dtype == HASTE_DTYPE_BF16 && dir_fwd_ok(B, F_s, H))
         return launch_dir<true, true, EPI_BF16_BCE>(s, (const bf16_t *)X, F_s, (const bf16_t *)Wh, F_s, dYh, H, bias_h, B, H,
                                                     F_s, F_s, 1, pos, P);
     const hipError_t e = head_fwd(B, F_s, H, dtype, X, Wh, bias_h, dYh, s);
@@ -901,7 +922,7 @@ hipError_t head_bwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
             hipError_t e = launch_gemm4<false, false, EPI_F32>(s, (const bf16_t *)dYh, H, B * H, (const bf16_t *)X, F_s,
                                                                B * F_s, (void *)dWh, F_s, nullptr, H, F_s, B, B, 1);
             if (e != hipSuccess) return e;
-        } else if (bf && dir_ok(H, F_s, B, 1)) {
+        } else if (bf && dir_dw_ok(B, F_s, H)) {
             hipError_t e = launch_dir<false, false, EPI_F32>(s, (const bf16_t *)dYh, H, (const bf16_t *)X, F_s, (void *)dWh,
                                                              F_s, nullptr, H, F_s, B, B, 1);
             if (e != hipSuccess) return e;
@@ -939,7 +960,7 @@ hipError_t head_bwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
                                                                    F_s, H * F_s, (void *)part, F_s, nullptr, B, F_s, H,
                                                                    kchunk, (int)Sx);
             if (e != hipSuccess) return e;
-        } else if (bf && dir_ok(B, F_s, H, 1)) {
+        } else if (bf && dir_dx_ok(B, F_s, H)) {
             // (the direct kernel's tiles are a sixteenth of those the split was made for)
             hipError_t e = launch_dir<true, false, EPI_F32_PART>(s, (const bf16_t *)dYh, H, (const bf16_t *)Wh, F_s,
                                                                  (void *)part, F_s, nullptr, B, F_s, H, kchunk, Sx);

@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 # B, F_s, H
 SHAPES = [(1, 1, 1), (77, 500, 1003), (33, 37, 65), (8, 768, 1024), (32, 512, 24), (40, 770, 300), (100, 63, 4001), (5, 16, 31),
-          (300, 384, 1001), (31, 768, 16384)]
+          (300, 384, 1001), (31, 768, 16384),
+          # past the direct kernel's limits: dX by its work, dW of few rows, logits of odd rows
+          (77, 768, 16387), (16, 301, 4098), (900, 559, 1935)]
 
 
 @pytest.mark.parametrize("shape", SHAPES)
