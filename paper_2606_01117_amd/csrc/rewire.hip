@@ -223,10 +223,12 @@ __global__ __launch_bounds__(kRwScanThreads) void k_rw_scan(uint32_t *__restrict
 // Regrowth, one wave per group with a pruned slot.  F <= 256 slots (up to four per lane), H <= 1024
 // features (one 32-bit word of the wave's used-feature bitmap per lane).
 constexpr int kRwWaves = 4;
-constexpr int kRwChunk = 1024;    // a wave moves up to 1024 weights (or velocities) at a time
+// A wave moves up to CH weights (or velocities) at a time: 1024, or 256 where a group has no more, whose
+// registers leave room for more waves (172K groups of one slot: 142 us with 1024, 3 waves per SIMD).
+constexpr int kRwChunk = 1024, kRwChunkSmall = 256;
 constexpr int kRwMaxRows = 64;
 // LDS words of a chunk: rows of F values at an odd number of words, at least one word apart
-constexpr int kRwChunkWords = kRwChunk + 2 * kRwMaxRows;
+constexpr int rw_chunk_words(int ch) { return ch + 2 * kRwMaxRows; }
 
 typedef uint32_t rw_word __attribute__((may_alias));
 typedef uint16_t rw_half __attribute__((may_alias));
@@ -235,9 +237,9 @@ template <> struct RwVec<4> { typedef uint32_t type; };
 template <> struct RwVec<2> { typedef uint16_t type; };
 
 // A chunk of whole label rows, VB bytes per lane and access (a row is a whole number of them)
-template <typename T, int VB> struct RwRows {
+template <typename T, int VB, int CH> struct RwRows {
     typedef typename RwVec<VB>::type V;
-    static constexpr int kVe = VB / (int)sizeof(T), kNv = kRwChunk / (64 * kVe);
+    static constexpr int kVe = VB / (int)sizeof(T), kNv = CH > 64 * kVe ? CH / (64 * kVe) : 1;
     V v[kNv];
 
     static __device__ __forceinline__ int stride_words(int F) { return ((F * (int)sizeof(T) + 3) / 4 + 1) | 1; }
@@ -318,7 +320,7 @@ template <typename T, int VB> struct RwRows {
 // its block's start and its slots (only where not all of them are pruned).
 //
 // NPL: 64-slot words of a support (F <= 64 NPL); VB, VM: bytes per access of W and of the velocity
-template <typename T, int NPL, int VB, int VM>
+template <typename T, int NPL, int VB, int VM, int CH>
 __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict__ idx, T *__restrict__ W,
                                                              float *__restrict__ mom, const uint32_t *__restrict__ keys,
                                                              const RwState *__restrict__ st,
@@ -330,7 +332,7 @@ __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict
     __shared__ int32_t feat_s[kRwWaves][64 * NPL];
     __shared__ __align__(16) uint16_t src_s[kRwWaves][64 * NPL];
     __shared__ uint16_t pl_s[kRwWaves][64 * NPL];
-    __shared__ uint32_t rows_s[kRwWaves][kRwChunkWords];
+    __shared__ uint32_t rows_s[kRwWaves][rw_chunk_words(CH)];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t k = (int64_t)blockIdx.x * kRwWaves + wv;
     if (k >= K) return;   // wave-uniform; this kernel has no workgroup barrier
@@ -377,14 +379,14 @@ __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict
     for (int w = 0; w < NPW; ++w) n_pruned += __popcll(pm[w]);
     if (n_pruned == 0) return;   // wave-uniform
 
-    // rows per chunk, at most 1024 values; the first chunk is on its way during the draws
-    int R = (int)((kRwChunk * fmagic) >> 20);   // 1024 / F
+    // rows per chunk, at most CH values; the first chunk is on its way during the draws
+    int R = (int)((CH * fmagic) >> 20);   // CH / F
     R = R < kRwMaxRows ? R : kRwMaxRows;
     R = R < G ? R : G;
     T *wg = W + k * G * F;
     float *mg = mom + k * G * F;
-    RwRows<T, VB> wr;
-    RwRows<float, VM> mr;
+    RwRows<T, VB, CH> wr;
+    RwRows<float, VM, CH> mr;
     wr.load(wg, R * F, lane);
     if (mom) mr.load(mg, R * F, lane);
 
@@ -486,17 +488,17 @@ __global__ __launch_bounds__(64 * kRwWaves) void k_rw_regrow(int32_t *__restrict
                 const uint64_t r = splitmix64_at(seed, (uint64_t)(KF + (k * G + g0 + row) * F + j)) >> 40;
                 v = (float)((int32_t)(2 * r) - (1 << 24)) * scale;
             }
-            RwRows<T, VB>::set(rows, F, row, j, v);
+            RwRows<T, VB, CH>::set(rows, F, row, j, v);
         }
-        RwRows<T, VB>::store(rows, src, wg + (int64_t)g0 * F, n, F, fmagic, lane);
+        RwRows<T, VB, CH>::store(rows, src, wg + (int64_t)g0 * F, n, F, fmagic, lane);
         if (!mom) continue;   // uniform
         mr.put(rows, n, F, fmagic, lane);
         if (nx > 0) mr.load(mg + (int64_t)(g0 + nr) * F, nx, lane);
         for (int e = lane; e < nr * n_pruned; e += 64) {
             const int row = (int)((uint32_t)e * pmagic >> 20);
-            RwRows<float, VM>::set(rows, F, row, pl[e - row * n_pruned], 0.0f);
+            RwRows<float, VM, CH>::set(rows, F, row, pl[e - row * n_pruned], 0.0f);
         }
-        RwRows<float, VM>::store(rows, src, mg + (int64_t)g0 * F, n, F, fmagic, lane);
+        RwRows<float, VM, CH>::store(rows, src, mg + (int64_t)g0 * F, n, F, fmagic, lane);
     }
 }
 
@@ -560,9 +562,13 @@ hipError_t rewire(const TailArgs &a, int32_t *idx, void *W, float *m, int64_t n_
     const dim3 g2((unsigned)cdiv(K, kRwWaves));
     auto regrow = [&](auto tag, auto npl, auto vb, auto vm) {
         using T = decltype(tag);
-        hipLaunchKernelGGL((k_rw_regrow<T, decltype(npl)::value, decltype(vb)::value, decltype(vm)::value>), g2,
-                           dim3(64 * kRwWaves), 0, s, idx, (T *)W, m, keys, st, cnt, K, (int)a.G, F, (int)a.F_s,
-                           init_random, seed, scale, fmagic);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, g2, dim3(64 * kRwWaves), 0, s, idx, (T *)W, m, keys, st, cnt, K, (int)a.G, F, (int)a.F_s,
+                               init_random, seed, scale, fmagic);
+        };
+        constexpr int NPL = decltype(npl)::value, VB = decltype(vb)::value, VM = decltype(vm)::value;
+        if (a.G * F <= kRwChunkSmall) go(k_rw_regrow<T, NPL, VB, VM, kRwChunkSmall>);
+        else go(k_rw_regrow<T, NPL, VB, VM, kRwChunk>);
     };
     // accesses that divide a row: 16 bytes where every row is aligned to them, else 4, else one value
     using c16 = std::integral_constant<int, 16>;

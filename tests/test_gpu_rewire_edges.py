@@ -1,6 +1,6 @@
 """GPU parity of haste_rewire at the edges of its chunks and of its ties, against the CPU oracle (exact).
 
-A wave moves whole label rows in chunks of up to 1024 values and 64 rows, in accesses of 16, 4 or 2
+A wave moves whole label rows in chunks of up to 1024 (small groups: 256) values and 64 rows, in accesses of 16, 4 or 2
 bytes by what divides a row; a key equal to the threshold is pruned if few enough equal ones precede
 it, counted from the start of its 1024-key block.
 """
@@ -26,6 +26,17 @@ CASES = [
     ("bf16_all_tied", 331, 4, 24, 256, BF16, 0.37, True, 1),
     ("bf16_ties_over_blocks", 257, 2, 200, 400, BF16, 0.45, False, 2),
     ("f32_ties", 1500, 1, 33, 128, F32, 0.31, True, 3),
+    # groups of up to 256 weights (the smaller chunk), by access and 64-slot words, and one past it
+    ("bf16_small", 900, 4, 64, 300, BF16, 0.2, True, 0),
+    ("bf16_small_even", 700, 3, 30, 90, BF16, 0.3, True, 0),
+    ("bf16_small_one", 2000, 1, 1, 9, BF16, 0.3, True, 0),
+    ("bf16_small_odd", 1000, 2, 5, 64, BF16, 0.4, True, 0),
+    ("bf16_small_two_words", 300, 2, 128, 600, BF16, 0.1, True, 0),
+    ("bf16_small_four_words_odd", 300, 1, 255, 700, BF16, 0.2, True, 0),
+    ("bf16_one_past", 60, 257, 1, 30, BF16, 0.3, True, 0),
+    ("f32_small", 500, 4, 64, 256, F32, 0.2, True, 0),
+    ("f32_small_two_words_odd", 400, 3, 77, 200, F32, 0.3, False, 0),
+    ("f32_small_four_words", 200, 1, 256, 900, F32, 0.1, True, 0),
 ]
 
 
