@@ -141,8 +141,10 @@ __global__ __launch_bounds__(kGlThreads) void k_gl_pick_centres(const int8_t *__
     gl_store_centre(sum, D, C, c, cs, cp, cn, cnp);
 }
 
-// cl[l] = argmax_c (E[l].s_c) / |s_c| (ties: the lower c).  A wave takes 32 labels, a workgroup of
-// 8 waves 256; centres pass through LDS 16 at a time, as many digit planes as the 16 need, and the next
+// cl[l] = argmax_c (E[l].s_c) / |s_c| (ties: the lower c).  A wave takes 16 MT labels, a workgroup of
+// 8 waves 256, or 128 where 256 would leave half of the CUs without one, or with up to 256 dimensions (less
+// work per centre) some (60000 labels and centres, 64 dimensions: 9.9 ms with 256, 7.8 the kernel before it;
+// 30000 labels, 512 dimensions, the whole grouping: 1165 us with 256, 1056 with 128; 65536 labels, 768: 1417, 1555); centres pass through LDS 16 at a time, as many digit planes as the 16 need, and the next
 // 16 wait in registers.  v_mfma_i32_16x16x64_i8, M = 16 labels, N = 16 centres, K = 64 dimensions: both
 // operands hold, per lane, 16 consecutive dimensions (16 q .. 16 q + 15 of the 64-chunk) of their row, so
 // each lane group contracts the same dimensions; result lane (centre l16, q) holds labels 4q .. 4q+3.
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(kGlThreads) void k_gl_pick_centres(const int8_t *__
 // The quotient is compared through dot * (1 / |s_c|), which lies within 2^-51 of it: only scores closer
 // than 2^-48 of the best are divided.  131K labels, 256 centres, 768 dimensions, three planes: 530 us with
 // 16 labels a wave, 1 KiB rows and a division per score, 110 us.
-template <int NK>
+template <int NK, int MT>
 __global__ __launch_bounds__(64 * kGlWaves) void k_gl_assign(const int8_t *__restrict__ E, int64_t N, int D,
                                                              const int8_t *__restrict__ cp,
                                                              const double *__restrict__ cn,
@@ -162,12 +164,12 @@ __global__ __launch_bounds__(64 * kGlWaves) void k_gl_assign(const int8_t *__res
     __shared__ __align__(16) int8_t tile[kGlPlanes * 16 * RS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l16 = lane & 15, q = lane >> 4;
-    const int64_t l0 = (int64_t)blockIdx.x * (32 * kGlWaves) + 32 * wave;
+    const int64_t l0 = (int64_t)blockIdx.x * (16 * MT * kGlWaves) + 16 * MT * wave;
     // this lane's A rows: label l0 + 16 m + l16, dims 64 kk + 16 q .. +15 (zero past D or past N)
     const Buf eb(E, (uint32_t)(N * D));
-    i32x4_t a[2][NK];
+    i32x4_t a[MT][NK];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
             const int d0 = 64 * kk + 16 * q;
@@ -175,10 +177,10 @@ __global__ __launch_bounds__(64 * kGlWaves) void k_gl_assign(const int8_t *__res
             a[m][kk] = __builtin_bit_cast(i32x4_t, eb.ld16(d0 < D && l < N ? (uint32_t)(l * D + d0) : kOob));
         }
     // best so far per label: the score's stand-in, the exact product and the centre
-    double bv[2][4], bd[2][4];
-    int bi[2][4];
+    double bv[MT][4], bd[MT][4];
+    int bi[MT][4];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             bv[m][i] = bd[m][i] = 0.0;
@@ -213,23 +215,24 @@ __global__ __launch_bounds__(64 * kGlWaves) void k_gl_assign(const int8_t *__res
             load(c0 + 16);
             npn = planes(c0 + 16);
         }
-        i32x4_t acc[kGlPlanes][2];
+        i32x4_t acc[kGlPlanes][MT];
 #pragma unroll
         for (int p = 0; p < kGlPlanes; ++p) {
-            acc[p][0] = acc[p][1] = i32x4_t{0, 0, 0, 0};
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[p][m] = i32x4_t{0, 0, 0, 0};
             if (p >= npt) continue;
 #pragma unroll
             for (int kk = 0; kk < NK; ++kk) {
                 const i32x4_t b = *reinterpret_cast<const i32x4_t *>(&tile[(16 * p + l16) * RS + 64 * kk + 16 * q]);
-                acc[p][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[0][kk], b, acc[p][0], 0, 0, 0);
-                acc[p][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[1][kk], b, acc[p][1], 0, 0, 0);
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[p][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[m][kk], b, acc[p][m], 0, 0, 0);
             }
         }
         const int c = (int)(c0 + l16);
         if (c < C) {
             const double nc = cn[c], inv = 1.0 / nc;
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
+            for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     // exact: |dot| < 2^31 127 1024 < 2^53
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(64 * kGlWaves) void k_gl_assign(const int8_t *__res
     }
     // best over the 16 lanes of each row group: larger value, then lower centre
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             double v = bi[m][i] != INT_MAX ? bd[m][i] / cn[bi[m][i]] : 0.0;
@@ -414,17 +417,18 @@ __global__ __launch_bounds__(64) void k_gl_fill(const int32_t *__restrict__ cl, 
     }
 }
 
-// cs[c] += the sums of the clusters' member rows (cs zeroed before): a workgroup takes kGlSumRows
+// cs[c] += the sums of the clusters' member rows (cs zeroed before): a workgroup takes `rows`
 // consecutive places of the member lists, run by run of one cluster; its 8 waves take every eighth member,
 // a lane 16 dimensions, and the waves' sums meet in LDS before they are added (whole numbers: any order
 // gives the same sum).  131K x 768: one workgroup per cluster reading single bytes 785 us, 22 us (and 5 for the centres).
-constexpr int kGlSumRows = 256;
+// A run takes about 1.5 us, one after the other, so `rows` holds about four clusters of the average size.
+constexpr int kGlSumRows = 256;                   // at most
 __global__ __launch_bounds__(512) void k_gl_sum(const int8_t *__restrict__ E, int64_t N, int D,
                                                 const int32_t *__restrict__ members, const int32_t *__restrict__ cl,
-                                                const int32_t *__restrict__ start, int32_t *__restrict__ cs) {
+                                                const int32_t *__restrict__ start, int32_t *__restrict__ cs, int rows) {
     __shared__ int32_t wsum[8 * kGlMaxD];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t p0 = (int64_t)blockIdx.x * kGlSumRows, p1 = p0 + kGlSumRows < N ? p0 + kGlSumRows : N;
+    const int64_t p0 = (int64_t)blockIdx.x * rows, p1 = p0 + rows < N ? p0 + rows : N;
     const bool own = 16 * lane < D;
     for (int64_t q0 = p0; q0 < p1;) {             // workgroup-uniform
         const int c = cl[members[q0]];
@@ -825,8 +829,14 @@ hipError_t group_labels(int64_t N, int64_t D, const int8_t *E, int64_t G, int64_
         hipLaunchKernelGGL(k_gl_shuffle, dim3(1), dim3(64), 0, s, a, N, C, seed);
     }
     hipLaunchKernelGGL(k_gl_pick_centres, dim3((unsigned)C), dim3(kGlThreads), 0, s, E, a, C, Di, cs, cp, cn, cnp);
-    const dim3 ga((unsigned)cdiv(N, 32 * kGlWaves));
-    auto assign = [&](auto kern) { hipLaunchKernelGGL(kern, ga, dim3(64 * kGlWaves), 0, s, E, N, Di, cp, cn, cnp, C, cl); };
+    auto assign = [&](auto nk) {
+        constexpr int NK = decltype(nk)::value;
+        auto go = [&](auto kern, int mt) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(N, 16 * mt * kGlWaves)), dim3(64 * kGlWaves), 0, s, E, N, Di, cp, cn, cnp, C, cl);
+        };
+        if (cdiv(N, 32 * kGlWaves) <= (NK == 4 ? kXcds * kCusPerXcd : kXcds * kCusPerXcd / 2)) go(k_gl_assign<NK, 1>, 1);
+        else go(k_gl_assign<NK, 2>, 2);
+    };
     // tiles of the counting sort: about 512, and few enough that their counts fit the similarities' space
     // (8 N bytes; those come later)
     int64_t TL = cdiv(N, 512) > 256 ? cdiv(N, 512) : 256;
@@ -842,10 +852,10 @@ hipError_t group_labels(int64_t N, int64_t D, const int8_t *E, int64_t G, int64_
         if (e != hipSuccess) return e;
     }
     auto assign_and_collect = [&]() {
-        if (D <= 256) assign(k_gl_assign<4>);
-        else if (D <= 512) assign(k_gl_assign<8>);
-        else if (D <= 768) assign(k_gl_assign<12>);
-        else assign(k_gl_assign<16>);
+        if (D <= 256) assign(std::integral_constant<int, 4>{});
+        else if (D <= 512) assign(std::integral_constant<int, 8>{});
+        else if (D <= 768) assign(std::integral_constant<int, 12>{});
+        else assign(std::integral_constant<int, 16>{});
         if (sorted) {
             hipLaunchKernelGGL(k_gl_hist, dim3((unsigned)nt), dim3(64), (size_t)C * 4, s, cl, N, TL, (int)C, hist);
             hipLaunchKernelGGL(k_gl_scan, dim3((unsigned)cdiv(C, 64)), dim3(64 * kGlScanSegs), 0, s, hist, nt, (int)C, cnt);
@@ -858,10 +868,11 @@ hipError_t group_labels(int64_t N, int64_t D, const int8_t *E, int64_t G, int64_
         hipLaunchKernelGGL(k_gl_starts, dim3(1), dim3(256), 0, s, cnt, C, G, start, gstart, n_groups);
         hipLaunchKernelGGL(k_gl_collect, dim3((unsigned)C), dim3(256), 0, s, cl, N, start, members);
     };
+    const int sum_rows = (int)(4 * N / C < kGlSumRows ? 4 * N / C : kGlSumRows);
     for (int64_t it = 0; it < iters; ++it) {
         assign_and_collect();
         hipLaunchKernelGGL(k_gl_zero, dim3((unsigned)cdiv(C * D, 256)), dim3(256), 0, s, cs, C * D);
-        hipLaunchKernelGGL(k_gl_sum, dim3((unsigned)cdiv(N, kGlSumRows)), dim3(512), 0, s, E, N, Di, members, cl, start, cs);
+        hipLaunchKernelGGL(k_gl_sum, dim3((unsigned)cdiv(N, sum_rows)), dim3(512), 0, s, E, N, Di, members, cl, start, cs, sum_rows);
         hipLaunchKernelGGL(k_gl_centroid, dim3((unsigned)C), dim3(kGlThreads), 0, s, Di, C, start, cs, cp, cn, cnp);
     }
     assign_and_collect();
