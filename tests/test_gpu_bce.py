@@ -287,3 +287,27 @@ def test_head_fwd_bce_errors(hs):
     with pytest.raises(hs.HasteError):   # positives named but missing
         hs._check(hs.lib.haste_head_fwd_bce(4, 768, 1024, BF16, hs._ptr(dummy), hs._ptr(dummy), None, None, 3,
                                             hs._ptr(dummy), None))
+
+
+@pytest.mark.parametrize("dt", [synth.DT_BF16, synth.DT_F32])
+@pytest.mark.parametrize("N", [1, 2047, 2048, 2049, 4096, 6001])
+@pytest.mark.parametrize("P", [0, 1, 5, 256, 257, 700])
+def test_bce_grad_positives(dt, N, P):
+    """At logits of zero the gradient is exactly 0.5, less 1 at a positive: each column of the first, a middle and the
+    last workgroup of a row, more positives than threads, repeats, and ids outside the row."""
+    import torch
+    import paper_2606_01117_amd as hs
+    say("bce positives", dt, N, P)
+    B = 3
+    gen = torch.Generator(device="cuda").manual_seed(N * 7 + P)
+    pos = torch.randint(-2, N + 2, (B, P), device="cuda", generator=gen).int()
+    if P > 4:
+        pos[1, :4] = torch.tensor([0, N - 1, min(N - 1, 2047), min(N - 1, 2048)], dtype=torch.int32)
+    Y = torch.zeros((B, N), dtype=torch.bfloat16 if dt == synth.DT_BF16 else torch.float32, device="cuda")
+    dY = torch.empty_like(Y)
+    hs.haste_bce_grad(B, N, dt, Y, pos, dY)
+    ref = torch.full((B, N), 0.5, device="cuda")
+    for b in range(B):
+        p = pos[b][(pos[b] >= 0) & (pos[b] < N)].long()
+        ref[b, p] = -0.5
+    assert torch.equal(dY.float(), ref)
