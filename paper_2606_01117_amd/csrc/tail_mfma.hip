@@ -419,11 +419,13 @@ __global__ __launch_bounds__(512) void k_bwd_w2(const bf16_t *__restrict__ Xb, c
     // cooperative slab loads: X^T block (4 F_s chunks of 16 bytes) and dY (32 rows x 64 chunks: unit
     // part / 4 of the span takes columns 32 (part / 4) .., whatever its labels, so that the operand
     // reads are aligned); this thread's chunk of every row: labels yl .. yl + yn - 1 of the span
+    // (in 32-bit steps from the first unit's group: a lane's own 64-bit division costs 2 to 5% of a short batch)
     const int part = tid & 63;
-    const int64_t yu = u0 + (part >> 2);
-    const bool yok = part >> 2 < UNITS && yu < nunits;
-    const int yl = yok ? (int)(lab_of(yu) - lab0) + 8 * (part & 3) : 0;
-    const int yn = yok ? nlab_of(yu) - 8 * (part & 3) : 0;
+    const int64_t k0 = u0 / ntn;
+    const int yr0 = (int)(u0 - k0 * ntn) + (part >> 2), yk = ntn == 1 ? yr0 : yr0 / ntn, yt = yr0 - yk * ntn;
+    const bool yok = part >> 2 < UNITS && u0 + (part >> 2) < nunits;
+    const int yl = yok ? (int)(k0 * G - lab0) + yk * G + 32 * yt + 8 * (part & 3) : 0;
+    const int yn = yok ? (G - 32 * yt < 32 ? G - 32 * yt : 32) - 8 * (part & 3) : 0;
     const int nxc = 4 * F_s;
     uint4 xr[kBw2MaxXLoads], yr[4];
     auto load = [&](int blk) {
