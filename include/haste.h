@@ -22,8 +22,11 @@
  *     enqueues work on that stream and returns; a kernel fault surfaces at the caller's next
  *     synchronisation.  Calls never synchronise the device.
  *   - "ws" is caller-owned device scratch of ws_bytes bytes; the required size is given by
- *     haste_workspace_bytes / haste_head_workspace_bytes.  Concurrent calls must use distinct
- *     workspaces.
+ *     haste_workspace_bytes / haste_head_workspace_bytes.  Some calls also take less, and then run
+ *     other kernels or fewer partial sums (each says so); a size that no kernel can do with gives
+ *     HASTE_ERR_WORKSPACE.  Which kernel runs, and so the order in which a sum is rounded, depends on
+ *     the layer's sizes and on ws_bytes alone: the same call twice gives the same bits.  Concurrent
+ *     calls must use distinct workspaces.
  *   - Return value: HASTE_OK, or an error code; on error nothing is launched and
  *     haste_last_error() describes the cause (per calling thread).
  *   - 64-bit sizes throughout; B * L may exceed 2^31.
@@ -77,7 +80,11 @@ typedef struct haste_desc {
  * Forward logits of the tail (Section 3.1 logit; Section 3.2 "gather-once and dense MMA"):
  *   Y[b, l] = bias[l] + sum_{t < F_in} X[b, idx[l/G, t]] * W[l, t]
  * X[B, F_s], idx[L/G, F_in] int32, W[L, F_in], bias[L] fp32 or NULL (no bias), Y[B, L] (dtype),
- * overwritten.
+ * overwritten.  ws is not used.
+ * An infinity or a NaN in X[b, f] reaches the labels whose support holds f; on bf16 layers of 1, 2, 4 or
+ * 8 labels per group with 32, 64 or 128 slots it may make other entries of row b NaN too, on other layers
+ * not.  bf16 layers that multiply scattered weight tiles (of small, odd or wide groups, F_s <= 768) take
+ * the 128 rows around such an X on a path without matrix instructions, orders slower.
  */
 int haste_fwd(const haste_desc_t *desc, const void *X, const int32_t *idx, const void *W,
               const float *bias, void *Y, void *ws, size_t ws_bytes, void *stream);
@@ -88,6 +95,9 @@ int haste_fwd(const haste_desc_t *desc, const void *X, const int32_t *idx, const
  *   dW[l, t] = beta * dW[l, t] + sum_b dY[b, l] * X[b, idx[l/G, t]]
  *   dbias[l] = beta * dbias[l] + sum_b dY[b, l]            (skipped when dbias is NULL)
  * dY[B, L] (dtype); dW[L, F_in] fp32; beta is 0 (overwrite) or 1 (accumulate).
+ * ws: haste_workspace_bytes(desc, HASTE_OP_BWD_W) bytes, a copy of X^T.  bf16 layers whose F_in is not 32,
+ * 64 or 128, or whose G is neither 1 nor 2 nor a multiple of 4 (and some of odd F_s or L), also run without
+ * it (ws NULL or smaller) on the vector ALUs, whose sums round in another order.
  */
 int haste_bwd_w(const haste_desc_t *desc, const void *X, const int32_t *idx, const void *dY,
                 float *dW, float *dbias, int beta, void *ws, size_t ws_bytes, void *stream);
@@ -96,9 +106,14 @@ int haste_bwd_w(const haste_desc_t *desc, const void *X, const int32_t *idx, con
  * Backward-feature of the tail (Section 3.2: grad h_{:, I_k} += grad Z_k W_k, reduced over all
  * groups with a split over the label dimension):
  *   dX[b, f] = beta * dX[b, f] + sum_k sum_{t : idx[k,t] = f} sum_{j < G} dY[b, kG+j] * W[kG+j, t]
- * dX[B, F_s] fp32; beta is 0 (overwrite) or 1 (accumulate).  Partial sums over label segments
- * live in ws and are reduced in a fixed segment order; on the bf16 matrix-core path ws also
- * holds a group-transposed copy of W (about L * F_in * 2 bytes), rebuilt by every call.
+ * dX[B, F_s] fp32; beta is 0 (overwrite) or 1 (accumulate).
+ * ws: haste_workspace_bytes(desc, HASTE_OP_BWD_X) bytes.  Partial sums over label segments live there
+ * and are added in a fixed order; where bf16 groups sum in LDS accumulators it also holds a
+ * group-transposed copy of W (about L * F_in * 2 bytes), rebuilt by every call.  Less is taken where a
+ * kernel of less scratch exists, or the same one with fewer segments (the sums then round in another
+ * order).
+ * An infinity or a NaN in dY[b, l] reaches the features of l's support; on bf16 layers of 1, 2, 4 or 8
+ * labels per group with 32, 64 or 128 slots it may make other entries of row b NaN too, on other layers not.
  */
 int haste_bwd_x(const haste_desc_t *desc, const int32_t *idx, const void *W, const void *dY,
                 float *dX, int beta, void *ws, size_t ws_bytes, void *stream);
@@ -122,11 +137,13 @@ int haste_bwd_x(const haste_desc_t *desc, const int32_t *idx, const void *W, con
  * bucketed by workgroup and batch slab in the workspace, whose queried size provides for up to
  * 1024 per row (2 F_s round_up(B, 32) + 8 (L B / 512) + 4 B P bytes about; a larger P fuses when
  * ws holds that much, else composes).  Other layers run haste_fwd into dY, the gradient in place
- * (for bf16 the sigmoid then sees the logits rounded to bf16), and haste_bwd_w; for bf16 groups of
- * 1, 2, 4 or 8 labels with rows of up to 256 positives the forward kernel itself stores that same
- * gradient (bit for bit), after sorting each row's positives into the workspace (B * P * 4 bytes
- * after the X^T copy; the queried size provides for 256 per row).
- * ws: haste_workspace_bytes(desc, HASTE_OP_FWD_BCE) bytes.
+ * (for bf16 the sigmoid then sees the logits rounded to bf16), and haste_bwd_w; where the bf16 forward
+ * is one of the kernels for small, odd or wide groups, and rows have up to 256 positives, that kernel
+ * itself stores the same gradient (bit for bit), after sorting each row's positives into the workspace
+ * (B * P * 4 bytes; the queried size provides for 256 per row).  They lie after the X^T copy, or, in
+ * layers that haste_bwd_w also takes without one, at the start, where the copy is made once they have
+ * been read.
+ * ws: haste_workspace_bytes(desc, HASTE_OP_FWD_BCE) bytes.  Less is taken as long as haste_bwd_w's holds.
  */
 int haste_fwd_bce(const haste_desc_t *desc, const void *X, const int32_t *idx, const void *W,
                   const float *bias, const int32_t *pos, int32_t P, void *dY, float *dW,
@@ -145,7 +162,8 @@ int haste_fwd_bce(const haste_desc_t *desc, const void *X, const int32_t *idx, c
  * left holding the last call's data (each call writes all it reads): calls that overlap on one GPU
  * (other streams or threads) race on it, and the caller must serialise them.  The array's device
  * address is looked up on the first call on each device; the current device must be the one the
- * stream belongs to.
+ * stream belongs to.  Every bf16 layer whose haste_bwd_w takes a workspace uses the array, those that
+ * could do without it among them.
  */
 int haste_fwd_bce_static(const haste_desc_t *desc, const void *X, const int32_t *idx, const void *W,
                          const float *bias, const int32_t *pos, int32_t P, void *dY, float *dW,
@@ -257,11 +275,12 @@ int haste_group_labels(int64_t N, int64_t D, const int8_t *E, const haste_group_
  * the Section 3.3 objective): haste_fwd_bce (dY, dW, dbias as documented there) followed by
  *   dX = beta_dx * dX + scatter(dY W)        as haste_bwd_x, on the dY just formed.
  * Same arguments and rules as those two calls; beta applies to dW and dbias, beta_dx to dX.
- * Results equal the two calls' bit for bit.  For groups of 32 labels on the fused path the
+ * Results equal the two calls' bit for bit, given the parts of ws that the step gives them.  For groups of 32 labels on the fused path the
  * forward kernel also writes the transposed weights and lane-ordered supports the backward-feature
  * kernel reads, into the workspace, so that pass skips its own transposition of W.  dX NULL runs
  * haste_fwd_bce alone.  ws: haste_workspace_bytes(desc, HASTE_OP_TAIL_STEP) bytes (holds both
- * calls' workspaces side by side); too small gives HASTE_ERR_WORKSPACE and launches nothing.
+ * calls' workspaces side by side).  With less, both parts shrink to the least that the calls take;
+ * too small for that gives HASTE_ERR_WORKSPACE and launches nothing.
  */
 int haste_tail_step(const haste_desc_t *desc, const void *X, const int32_t *idx, const void *W,
                     const float *bias, const int32_t *pos, int32_t P, void *dY, float *dW,
@@ -271,8 +290,9 @@ int haste_tail_step(const haste_desc_t *desc, const void *X, const int32_t *idx,
 /*
  * The same pass with the optimizer step (Section 4: SGD with momentum): haste_fwd_bce_sgd (dY, m,
  * W_next, dbias as documented there; dW never stored) followed by haste_bwd_x on its dY with the
- * step's W (not W_next), bit-identical to the two calls.  W_next must not overlap W.
- * ws: haste_workspace_bytes(desc, HASTE_OP_TAIL_STEP_SGD) bytes.
+ * step's W (not W_next), bit-identical to the two calls, given the parts of ws that the step gives them.
+ * W_next must not overlap W.
+ * ws: haste_workspace_bytes(desc, HASTE_OP_TAIL_STEP_SGD) bytes; less as in haste_tail_step.
  */
 int haste_tail_step_sgd(const haste_desc_t *desc, const void *X, const int32_t *idx, const void *W,
                         const float *bias, const int32_t *pos, int32_t P, void *dY, float *dbias,
@@ -304,10 +324,11 @@ int haste_head_fwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void 
  * head branch):
  *   dY_h[b, h] = sigmoid(bias_h[h] + sum_f X[b, f] * W_head[h, f]) - T[b, h]
  * with T from pos[B, P] as in haste_bce_grad (ids in [0, H); -1 padding and repeats allowed).
- * The logits are not stored.  On bf16 layers whose pointers are 16-byte aligned and whose F_s
- * and H are multiples of 8 the sigmoid is taken of the fp32 logit inside the GEMM's epilogue and
- * sigmoid - T is rounded once to bf16; otherwise the logits are written into dY_h (rounded to
- * dtype) and the gradient is formed there in place, as haste_head_fwd + haste_bce_grad would.
+ * On bf16 layers whose pointers are 16-byte aligned and whose F_s and H are multiples of 8 the sigmoid
+ * is taken of the fp32 logit inside the GEMM's epilogue and sigmoid - T is rounded once to bf16.  On
+ * other layers the gradient is that of the logits rounded to dtype, bit for bit what haste_head_fwd +
+ * haste_bce_grad give: formed in the epilogue of the kernel for few tiles, else in place after the
+ * logits were written into dY_h.
  * X[B, F_s], W_head[H, F_s] (dtype), bias_h[H] fp32 (16-byte aligned) or NULL, dY_h[B, H] (dtype)
  * overwritten.  Errors: HASTE_ERR_INVALID for a bad dtype, negative sizes or P, a NULL pointer
  * that is needed, or an unaligned bias_h; nothing is launched then.
