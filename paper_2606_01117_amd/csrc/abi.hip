@@ -72,8 +72,9 @@ int report(int code, const char *fmt, ...) {
 
 namespace {
 
-// the forward kernel for a layer: small groups (G = 1, 2, 4, 8) on their own matrix-core kernel,
-// larger ones on the gather-once kernel, the rest (fp32, other G) on the vector ALUs
+// A forward kernel for a layer exists.  Which one runs: scattered tiles for any group where they are the
+// fastest, else small groups (G = 1, 2, 4, 8) on their own matrix-core kernels, larger ones on the gather-once
+// kernel, fp32 on the fp32 matrix instructions, and the rest on the vector ALUs
 bool fwd_kernel_exists(const haste::TailArgs &a) {
     return haste::fwd_dn_supported(a) || haste::fwd_sg_supported(a) || haste::fwd_mfma_supported(a) ||
            haste::valu_supported(a);

@@ -2,8 +2,9 @@
 //
 // Used for fp32 layers of one or two labels per group (standard per-label fixed fan-in, Section 3.1 /
 // Fig. 2(c): every label gathers its own F_in features, so there is no shared tile and the work is thin
-// dot products) and for the layers that no matrix-core kernel takes (more than 256 slots, wide inputs
-// with odd shapes, very large batches).
+// dot products), for layers of few slots, rows or labels, where a matrix-core kernel's fixed parts cost more
+// than the sums (the estimates below), and for the layers that no matrix-core kernel takes (more than 256
+// slots, wide inputs with odd shapes, very large batches).
 //
 // A batch tile of TB rows of X is kept transposed in LDS as fp32 (xs[f][b], row stride TB+4
 // floats so 16-byte reads stay aligned).  One thread owns one label.
