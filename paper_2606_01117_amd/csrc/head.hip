@@ -874,7 +874,8 @@ hipError_t head_fwd(int64_t B, int64_t F_s, int64_t H, int32_t dtype, const void
     // M = B, N = H, K = F_s;  A(m,k) = X[m*F_s + k];  B(k,n) = Wh[n*F_s + k]
     if (dtype == HASTE_DTYPE_BF16) {
         const bool big = gemm4_ok(B, F_s, H, {X, Wh, Yh, bias_h});
-        // (32 rows or fewer would fill an eighth of the 256-row tiles)
+        // (32 rows or fewer would fill an eighth of the 256-row tiles; past the direct kernel's limit, 16K labels,
+        // these stay)
         if ((!big || B <= 32) && dir_fwd_ok(B, F_s, H))
             return launch_dir<true, true, EPI_BF16_BIAS>(s, (const bf16_t *)X, F_s, (const bf16_t *)Wh, F_s, Yh, H, bias_h, B,
                                                          H, F_s, F_s, 1);
