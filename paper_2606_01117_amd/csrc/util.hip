@@ -154,8 +154,10 @@ unsigned grid_for(int64_t n) {
 // each, 1024 columns apart), or, where rows are not whole 16-byte groups, 8 single columns 256 apart, so
 // that every access of a wave is one contiguous run.  (Eight consecutive columns one by one touched each
 // line eight times: 131K fp32 columns, 128 rows: 73 us, 21 so.)
-// The threads set the row's positives in a bitmap of the columns together (128 rows of 131K bf16 columns, 5 / 40 /
-// 200 positives: every thread looking at each of them 12.4 / 27 / 110 us, 12.4 / 12.4 / 12.6 so).
+// A few positives are read by every thread (workgroup-uniform); more are set in a bitmap of the workgroup's
+// columns by the threads together, whose barriers cost 3% (256 rows of 655K bf16 columns, 5 / 40 positives:
+// 110 / 239 us one by one, 114 / 114 in the bitmap).
+constexpr int kBceFew = 8;
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_bce_grad(const T *Y, const int32_t *__restrict__ pos, int P, T *dY,
                                                   int64_t N, int64_t nchunk) {
@@ -164,7 +166,14 @@ __global__ __launch_bounds__(256) void k_bce_grad(const T *Y, const int32_t *__r
     const int64_t c0 = (blockIdx.x - b * nchunk) * 2048;
     const int tid = threadIdx.x;
     uint32_t t = 0;                               // bit RUN i + e: column c0 + 256 RUN i + RUN tid + e
-    if (P > 0) {                                  // kernel-uniform
+    if (P <= kBceFew) {                           // kernel-uniform
+        for (int p = 0; p < P; ++p) {
+            const int64_t d = (int64_t)pos[b * P + p] - c0;
+            if (d < 0 || d >= 2048) continue;     // workgroup-uniform
+            const int i = (int)d / (256 * RUN), e = (int)d % (256 * RUN) - RUN * tid;
+            if (e >= 0 && e < RUN) t |= 1u << (RUN * i + e);
+        }
+    } else {
         __shared__ uint32_t hit[64];              // one bit per column
         if (tid < 64) hit[tid] = 0u;
         __syncthreads();

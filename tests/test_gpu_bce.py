@@ -291,10 +291,10 @@ def test_head_fwd_bce_errors(hs):
 
 @pytest.mark.parametrize("dt", [synth.DT_BF16, synth.DT_F32])
 @pytest.mark.parametrize("N", [1, 2047, 2048, 2049, 4096, 6001])
-@pytest.mark.parametrize("P", [0, 1, 5, 256, 257, 700])
+@pytest.mark.parametrize("P", [0, 1, 8, 9, 256, 257, 700])
 def test_bce_grad_positives(dt, N, P):
     """At logits of zero the gradient is exactly 0.5, less 1 at a positive: each column of the first, a middle and the
-    last workgroup of a row, more positives than threads, repeats, and ids outside the row."""
+    last workgroup of a row, few and many positives, more than threads, repeats, and ids outside the row."""
     import torch
     import paper_2606_01117_amd as hs
     say("bce positives", dt, N, P)
