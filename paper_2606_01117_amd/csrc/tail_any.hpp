@@ -43,10 +43,19 @@ constexpr int kAxStageRow = 80;                   // bytes per staged dY row: 32
 __host__ __device__ constexpr int ax_ring(int ni) { return ni <= 8 ? 3 : 1; }
 
 // three tiles of 64-byte rows, three staged dY steps, and 64 bytes: a spare cell for writes of no slot
-// (cheaper than lane masks around the writes: 196 against 201 us on 655K labels in groups of 4), and at
-// kAxBad one bit per row whose dY is not finite somewhere
-__host__ __device__ constexpr int ax_lds(int fr, int mt) { return 3 * fr * 64 + 3 * 16 * mt * kAxStageRow + 64; }
-constexpr int kAxBad = 32;
+// (cheaper than lane masks around the writes: 196 against 201 us on 655K labels in groups of 4), at
+// kAxBad one bit per row whose dY is not finite somewhere, and at kAxFix what the pass over such rows
+// needs (kept in registers, it would crowd the producers' loop)
+__host__ __device__ constexpr int ax_lds(int fr, int mt) { return 3 * fr * 64 + 3 * 16 * mt * kAxStageRow + 160; }
+constexpr int kAxBad = 32, kAxFix = 64;
+struct AxFix {
+    const int32_t *idx;
+    const bf16_t *W, *dY;
+    float *pp;
+    int64_t L, l_begin, l_end;
+    int b0, Bp, nf, f0, G, F_in;
+};
+static_assert(sizeof(AxFix) <= 96, "fits behind kAxFix");
 
 // How dY rows (8 labels per lane) and weight pairs are read: 16 bytes and a dword where dY's rows
 // are 16-byte aligned (L a multiple of 8) and F_in is even; dwords where L and F_in are even; 2
@@ -204,9 +213,8 @@ struct AxTiles {
 // that are not finite, of the marked rows.  32 rows at a time sum in LDS (the tiles' space); a wave takes
 // every eighth run of 64 labels.
 template <int MT, int FR>
-__device__ __forceinline__ void ax_add_not_finite(const int32_t *idx, const bf16_t *W, const bf16_t *dY, float *pp, char *lds,
-                                                  int b0, int Bp, int nf, int f0, int64_t L, int G, int F_in,
-                                                  int64_t l_begin, int64_t l_end, const uint32_t *bad) {
+__device__ __forceinline__ void ax_add_not_finite(char *lds, const AxFix *fix, const uint32_t *bad) {
+    const AxFix x = *fix;
     float *sum = reinterpret_cast<float *>(lds);   // [32 rows][FR]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int r0 = 0; r0 < 16 * MT; r0 += 32) {
@@ -216,24 +224,24 @@ __device__ __forceinline__ void ax_add_not_finite(const int32_t *idx, const bf16
         __syncthreads();
         for (uint32_t m = mask; m != 0u; m &= m - 1u) {
             const int r = __builtin_ctz(m);
-            const bf16_t *y = dY + (int64_t)(b0 + r0 + r) * L;
-            for (int64_t l0 = l_begin + 64 * wave; l0 < l_end; l0 += kAxThreads) {
-                const bf16_t v = l0 + lane < l_end ? y[l0 + lane] : (bf16_t)0;
+            const bf16_t *y = x.dY + (int64_t)(x.b0 + r0 + r) * x.L;
+            for (int64_t l0 = x.l_begin + 64 * wave; l0 < x.l_end; l0 += kAxThreads) {
+                const bf16_t v = l0 + lane < x.l_end ? y[l0 + lane] : (bf16_t)0;
                 for (uint64_t at = __ballot((v & 0x7f80) == 0x7f80); at != 0u; at &= at - 1u) {
                     const int j = (int)__builtin_ctzll(at);
                     const int64_t l = l0 + j;
                     const float yv = bf16_to_f32((bf16_t)__builtin_amdgcn_readlane((int)v, j));
-                    for (int t = lane; t < F_in; t += 64) {
-                        const int f = idx[l / G * F_in + t] - f0;
-                        if (f >= 0 && f < nf) atomicAdd(&sum[r * FR + f], yv * bf16_to_f32(W[l * F_in + t]));
+                    for (int t = lane; t < x.F_in; t += 64) {
+                        const int f = x.idx[l / x.G * x.F_in + t] - x.f0;
+                        if (f >= 0 && f < x.nf) atomicAdd(&sum[r * FR + f], yv * bf16_to_f32(x.W[l * x.F_in + t]));
                     }
                 }
             }
         }
         __syncthreads();
-        for (int e = tid; e < 32 * nf; e += kAxThreads) {
+        for (int e = tid; e < 32 * x.nf; e += kAxThreads) {
             const int r = e & 31, f = e >> 5;
-            if ((mask >> r) & 1u) pp[(size_t)f * Bp + r0 + r] += sum[r * FR + f];
+            if ((mask >> r) & 1u) x.pp[(size_t)f * x.Bp + r0 + r] += sum[r * FR + f];
         }
         __syncthreads();
     }
@@ -283,7 +291,9 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
     const uint32_t sbase = lbase + 3 * TB;
     for (int e = tid; e < 3 * TB / 16; e += kAxThreads) *(lds_u32x4_t *)(uintptr_t)(lbase + 16 * e) = u32x4_t{0u, 0u, 0u, 0u};
     uint32_t *bad = reinterpret_cast<uint32_t *>(ax + 3 * TB + 3 * SB + kAxBad);   // [2]: one bit per row
+    AxFix *fix = reinterpret_cast<AxFix *>(ax + 3 * TB + 3 * SB + kAxFix);
     if (tid < 2) bad[tid] = 0u;
+    if (tid == 0) *fix = AxFix{idx, W, dY, pp, L, l_begin, l_end, b0, Bp, nf, f0, G, F_in};
     __syncthreads();                              // tiles zeroed
     const int rows = B - b0 < RW ? B - b0 : RW;
 
@@ -424,7 +434,7 @@ void k_bwd_x_any(const int32_t *__restrict__ idx, const bf16_t *__restrict__ W, 
     }
     __syncthreads();                              // partial stored, rows marked
     if ((bad[0] | bad[1]) != 0u)                  // workgroup-uniform
-        ax_add_not_finite<MT, FR>(idx, W, dY, pp, ax, b0, Bp, nf, f0, L, G, F_in, l_begin, l_end, bad);
+        ax_add_not_finite<MT, FR>(ax, fix, bad);
 }
 
 // ---------------------------------------------------------------------------------------------
